@@ -167,8 +167,8 @@ int sw_search_batch_async(sw_db* db, const uint8_t* d_queries, const int64_t* qu
  * sw_search_async; it calls no hipMalloc, hipFree or other allocating
  * routine.  Its scratch is one array of SW_NOALLOC_SCRATCH_BYTES per GPU,
  * part of the library's code object: each GPU the library runs on holds it
- * until the process ends (its address is looked up and its boundary-row
- * part cleared when a database is first loaded on that GPU).  96 MiB of it
+ * until the process ends (its address is looked up when a database is
+ * first loaded on that GPU).  96 MiB of it
  * take the inter-task boundary rows of the short bins, launched in chunks
  * that fit (512 bytes per padded bin column); the rest takes the rescoring
  * list (8 bytes per sequence), the query's profiles (about 300 bytes per
@@ -177,8 +177,7 @@ int sw_search_batch_async(sw_db* db, const uint8_t* d_queries, const int64_t* qu
  * grids shrink to what fits).  Calls that need more - a short bin longer
  * than 196,608 residues, or fixed parts plus one row of each intra-task
  * kernel beyond the array - return SW_ERANGE and enqueue nothing.
- * Every call on a GPU shares that GPU's array and leaves it in the state the
- * next call needs (zeros in the boundary-row part), so calls on one GPU must
+ * Every call on a GPU shares that GPU's array, so calls on one GPU must
  * not overlap: issue them on one stream, or order them with events; calls
  * that overlap on one GPU race and give wrong scores.  Timing (SW_OPT_TIMING)
  * is not recorded for these calls. */

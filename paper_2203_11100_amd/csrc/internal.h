@@ -31,14 +31,15 @@ constexpr int kProfRowDwords = 26;
 constexpr int kProfPairDwords = 2 * kProfRowDwords;
 constexpr uint32_t kHalfOne = 0x3c00u;   // binary16 1.0
 // Inter-task profile, strip-major for strips of R rows: strip s holds two
-// tables of R rows in the row-pair layout, the low table with dwords
-// (S(a_i, c), 1) and the high table with dwords (1, S(a_i, c)), binary16
-// (2 * R * kProfRowDwords dwords per strip).  A lane whose two sequences
-// have residues x and y reads (S(a_i, x), 1) from the low table and
-// (1, S(a_i, y)) from the high one; their packed product is (S(a_i, x),
-// S(a_i, y)), so one packed fused multiply-add forms H_diag + S for both
-// sequences.
+// tables of R rows in the row-pair layout (2 * R * kProfRowDwords dwords per
+// strip).  Binary16 form: the low table's dwords are (S(a_i, c), 1), the high
+// table's (1, S(a_i, c)), and a lane whose two sequences have residues x and y
+// multiplies (S(a_i, x), 1) by (1, S(a_i, y)) into a fused multiply-add onto
+// H_diag.  Drift form (packed16.h): the 32-bit integers S + 2 ge in the low table
+// and the same shifted up 16 bits in the high one, both added to H_diag.
 __host__ __device__ constexpr int prof_strip_dwords(int R) { return 2 * R * kProfRowDwords; }
+// Room after the last strip: the kernel copies a strip's rows in whole waves.
+constexpr int kProfSlack = 256;
 // Score given to padding (pad code, and query rows past the end).  Any value
 // <= 0 keeps padded cells from raising a maximum.
 constexpr int kPadScore = -64;
@@ -61,10 +62,22 @@ static_assert(half_bits(1) == 0x3c00 && half_bits(-64) == 0xd400 && half_bits(20
                   half_bits(11) == 0x4980 && half_bits(0) == 0,
               "binary16 encodings");
 
+// The parameters of a drift sweep (packed16.h), the same in both halves of
+// each word; group = 0: the binary16 form is used instead.
+struct DriftArgs {
+  int32_t group;              // strips until the drift starts again at its base
+  int32_t guard;              // values need the guard to stay in range
+  uint32_t c2;                // gap_open - gap_extend, at most 2048
+  uint32_t ge2;               // the drift of one row or column
+  uint32_t group2;            // the drift of a group's rows
+  uint32_t lim2, over2;       // the rescoring limit; 32768 - the limit
+};
+
 struct InterArgs {
   const uint2* res2;          // interleaved store viewed as (lo, hi) dword pairs
   const BinDesc* bins;
-  int32_t bin_begin;          // first bin of this launch
+  int32_t bin_begin, n_bins;  // the bins of this launch
+  int32_t* counter;           // bins taken from them, zero at launch
   int32_t n_strips;           // query strips of R rows
   const uint32_t* prof;       // n_strips * prof_strip_dwords(R) dwords
   uint32_t go2, ge2;          // gap penalties (binary16, capped at 2048) in both halves
@@ -75,6 +88,7 @@ struct InterArgs {
   int32_t* flag_count;        // rescoring list: count, then {sid, query}
   int2* flag_list;
   int32_t sat_limit;          // rescoring limit, at most the exact range (see effective_limit)
+  DriftArgs drift;
 };
 
 // Per-query parameters of the intra-task kernel.
@@ -216,10 +230,10 @@ static_assert(sizeof(TopkState) % 8 == 0, "TopkState keeps the arrays after it 8
 
 // Kernel launchers (return hipSuccess or the launch error).
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
-                          int m_pad, int R, int8_t* prof2, uint32_t* prof3, int m_pad2,
+                          int m_pad, int R, int drift, int8_t* prof2, uint32_t* prof3, int m_pad2,
                           int32_t* flag_count, hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-hipError_t launch_inter(int R, int W, int n_bins, const InterArgs& a, hipStream_t s);
+hipError_t launch_inter(int R, int W, int n_cus, const InterArgs& a, hipStream_t s);
 hipError_t launch_intra(int RR, int W2, int grid, const IntraArgs& a, hipStream_t s);
 // R in {2, 4, 8}, W2 in {1, 2, 4, 8}, not (8, 8) (LDS)
 hipError_t launch_intra_pairs(int R, int W2, int grid, const IntraPairArgs& a, hipStream_t s);

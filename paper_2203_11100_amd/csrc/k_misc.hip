@@ -19,7 +19,7 @@ __device__ __forceinline__ int profile_score(const uint8_t* __restrict__ q, int 
 // Entry (i, c) is S(a_i, c); rows past the query end and the pad/spare codes
 // get kPadScore.  Thread 0 also clears the rescoring list's count.
 __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
-                          uint32_t* __restrict__ prof, int m_pad, int R,
+                          uint32_t* __restrict__ prof, int m_pad, int R, int drift,
                           int8_t* __restrict__ prof2, uint32_t* __restrict__ prof3, int m_pad2,
                           int32_t* __restrict__ flag_count) {
   const int64_t n1 = (int64_t)(m_pad / R) * prof_strip_dwords(R);
@@ -27,7 +27,7 @@ __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
   const int64_t n3 = prof3 ? (int64_t)kIntraCodes * (m_pad2 / 2) : 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx == 0 && flag_count) *flag_count = 0;
+  if (idx == 0 && flag_count) flag_count[0] = flag_count[1] = 0;
   for (; idx < n1 + n2 + n3; idx += stride) {
     if (idx < n1) {
       // idx = ((strip * 2 + table) * R / 2 + pair) * kProfPairDwords + 2 * c + t
@@ -36,8 +36,14 @@ __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
       const int pair = (int)(pr % (R / 2));
       const int64_t st = pr / (R / 2);
       const int i = (int)(st >> 1) * R + 2 * pair + (rem & 1), c = rem >> 1;
-      const uint32_t v = half_bits(profile_score(q, m, mat, i, c));
-      prof[idx] = (st & 1) ? kHalfOne | (v << 16) : v | (kHalfOne << 16);
+      const int sc = profile_score(q, m, mat, i, c);
+      if (drift >= 0) {
+        const uint32_t v = (uint32_t)(sc + 2 * drift);
+        prof[idx] = (st & 1) ? v << 16 : v;
+      } else {
+        const uint32_t v = half_bits(sc);
+        prof[idx] = (st & 1) ? kHalfOne | (v << 16) : v | (kHalfOne << 16);
+      }
     } else if (idx < n1 + n2) {
       const int64_t j = idx - n1;
       const int c = (int)(j / m_pad2), i = (int)(j % m_pad2);
@@ -112,7 +118,7 @@ __global__ void k_fill(int32_t* __restrict__ p, int64_t n, int32_t v) {
 }  // namespace
 
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
-                          int m_pad, int R, int8_t* prof2, uint32_t* prof3, int m_pad2,
+                          int m_pad, int R, int drift, int8_t* prof2, uint32_t* prof3, int m_pad2,
                           int32_t* flag_count, hipStream_t s) {
   if (R <= 0 || R % 2 != 0 || m_pad % R != 0) return hipErrorInvalidValue;
   const int64_t total = (int64_t)(m_pad / R) * prof_strip_dwords(R) +
@@ -121,7 +127,7 @@ hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint
   int grid = (int)std::min<int64_t>((total + 255) / 256, 2048);
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(k_profile, dim3(grid), dim3(256), 0, s, d_query, m, mat, prof, m_pad, R,
-                     prof2, prof3, m_pad2, flag_count);
+                     drift, prof2, prof3, m_pad2, flag_count);
   return hipGetLastError();
 }
 

@@ -21,6 +21,7 @@
 #include "trace_walk.h"
 #include "internal.h"
 #include "layout.h"
+#include "packed16.h"
 
 namespace swdb {
 namespace {
@@ -409,11 +410,6 @@ int init_searcher(Searcher* S, DbData* d) {
           hipSuccess ||
       (e = S->seg_best.reserve((size_t)std::max<int64_t>(d->n_seg_items, 1))) != hipSuccess)
     return fail(SW_ENOMEM, std::string("search scratch: ") + hipGetErrorString(e));
-  // the inter-task kernel's first strip reads zeros from the boundary rows;
-  // every search leaves them zeroed again
-  if ((e = hipMemset(S->rb.p, 0, (size_t)std::max<int64_t>(P.boundary_uint4, 1) * sizeof(uint4))) !=
-      hipSuccess)
-    return hip_fail(e, "boundary-row clear");
   if ((e = hipStreamCreateWithFlags(&S->own_stream, hipStreamNonBlocking)) != hipSuccess ||
       (e = hipStreamCreateWithFlags(&S->aux_stream, hipStreamNonBlocking)) != hipSuccess)
     return hip_fail(e, "stream creation");
@@ -587,7 +583,8 @@ void time_end(Searcher* db, int idx, hipStream_t s) {
 }
 
 // The rescoring list: flags[0] is the count, {sid, query} pairs start at
-// flags + 2 (8-byte aligned).
+// flags + 2 (8-byte aligned); flags[1] counts the bins taken by a single
+// search's inter-task kernel.
 int2* flag_list(Searcher* db) { return reinterpret_cast<int2*>(db->flags.p + 2); }
 
 hipError_t reserve_flags(Searcher* db, int64_t entries) {
@@ -611,6 +608,43 @@ uint32_t half_pair(int32_t g) {
 // most 2048, below which every value is computed exactly (packed16.h).
 int32_t effective_limit(int32_t requested) {
   return std::max<int32_t>(0, std::min<int32_t>(requested, kHalfExact));
+}
+
+// The drift form's parameters for a kernel whose bins have at most `cols`
+// columns and whose strips have R rows (the arithmetic and the meaning of the
+// range: packed16.h), or group = 0 where it does not fit and the binary16 form
+// is used: gap_extend so large that the drift over the columns and one strip
+// leaves no room (above 13 at 2,048 columns).  The drift over the rows starts
+// again every `group` strips, as many as fit (all of a usual query's).
+DriftArgs drift_plan(int m, int64_t cols, int R, const Matrix& mat, int32_t go, int32_t ge,
+                     int32_t sat_limit) {
+  DriftArgs d{};
+  const int64_t limit = effective_limit(sat_limit);
+  int max_s = 0;
+  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) max_s = std::max<int>(max_s, mat.v[x]);
+  // room for the drift of columns and rows, when scores stay below what the
+  // lengths allow, or (guard) within some columns' gain of the limit
+  const int64_t top = kDriftTop - (int64_t)kDriftBase - 256;
+  const int64_t score = std::max<int64_t>(std::min<int64_t>(m, cols) * max_s, limit);
+  const int64_t guarded = limit + (int64_t)(R + 8) * max_s;
+  auto groups = [&](int64_t highest) -> int64_t {
+    if (ge == 0) return highest <= top ? INT32_MAX / R : 0;
+    return ((top - highest) / ge - cols - R - 8) / R;
+  };
+  int64_t g = groups(score);
+  if (g < 1 || (top - score) < 0) {
+    g = (top - guarded) < 0 ? 0 : groups(guarded);
+    d.guard = 1;
+  }
+  if (g < 1) return DriftArgs{};
+  d.group = (int32_t)std::min<int64_t>(g, (m + R - 1) / R);
+  auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
+  d.c2 = both(std::min<int32_t>(go - ge, kHalfExact));
+  d.ge2 = both(ge);
+  d.group2 = both((int64_t)ge * R * d.group);
+  d.lim2 = both(limit);
+  d.over2 = both(32768 - limit);
+  return d;
 }
 
 // Row length of a query's intra-task profiles: a whole number of the
@@ -672,6 +706,7 @@ struct SearchShape {
 constexpr double kInterRate = 7.0e12;
 constexpr double kPairRate = 4.5e12;
 constexpr double kBinRate = 3.0e10;
+constexpr double kPairShare = 5.0;
 
 // How many of the longest short bins a query of length m hands to the
 // long-pair kernel (RR query rows per lane).  A bin is 128 sequences on one
@@ -741,8 +776,9 @@ SearchShape search_shape(const Searcher* db, int m) {
 
 // Device scratch of one single-query search.
 struct SearchScratch {
-  uint4* rb = nullptr;        // boundary rows of every short bin, zero on entry
-  int32_t* flags = nullptr;   // rescoring list: [0] count, {sid, query} pairs from +2
+  uint4* rb = nullptr;        // boundary rows of every short bin
+  int32_t* flags = nullptr;   // rescoring list: [0] count, {sid, query} pairs from +2;
+                              // [1] the bins' work counter
   uint32_t* prof = nullptr;   // inter-task strip profile
   int8_t* prof2 = nullptr;    // intra-task int8 profile
   uint32_t* prof3 = nullptr;  // packed intra-task profile (long list present)
@@ -788,7 +824,8 @@ int reserve_search_scratch(Searcher* db, const SearchShape& sh, SearchScratch* X
   const int64_t n_long = db->d->plan.n_long;
   const int64_t off_pairs = sh.off_bins > 0 ? db->d->bin_pair_end[(size_t)sh.off_bins - 1] : 0;
   const bool pairs = n_long > 0 || off_pairs > 0;
-  if ((e = db->prof.reserve((size_t)sh.n_strips * prof_strip_dwords(sh.R))) != hipSuccess)
+  if ((e = db->prof.reserve((size_t)sh.n_strips * prof_strip_dwords(sh.R) + kProfSlack)) !=
+      hipSuccess)
     return fail(SW_ENOMEM, std::string("profile allocation: ") + hipGetErrorString(e));
   if ((e = db->prof2.reserve((size_t)kIntraCodes * sh.m_pad2)) != hipSuccess)
     return fail(SW_ENOMEM, std::string("profile allocation: ") + hipGetErrorString(e));
@@ -853,8 +890,10 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   const int64_t off_pairs = off_bins > 0 ? db->d->bin_pair_end[(size_t)off_bins - 1] : 0;
   const bool pairs = n_long > 0 || off_pairs > 0;
 
+  const DriftArgs drift =
+      drift_plan(m, db->d->plan.max_bin_len, R, mat, go, ge, db->sat_limit);
   const int t_total = time_begin(db, kTimeTotal, s);
-  if ((e = launch_profile(d_query, m, mat, X.prof, sh.m_pad, R, X.prof2,
+  if ((e = launch_profile(d_query, m, mat, X.prof, sh.m_pad, R, drift.group > 0 ? ge : -1, X.prof2,
                           pairs ? X.prof3 : nullptr, m_pad2, X.flags, s)) != hipSuccess)
     return hip_fail(e, "profile kernel");
   if (pairs && (e = hipEventRecord(db->ev_fork, s)) != hipSuccess) return hip_fail(e, "event");
@@ -877,6 +916,8 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
     a.res2 = reinterpret_cast<const uint2*>(db->d->packed.p);
     a.bins = db->d->bins.p;
     a.bin_begin = off_bins;
+    a.n_bins = n_bins - off_bins;
+    a.counter = X.flags + 1;       // cleared with the list's count by the profile kernel
     a.n_strips = sh.n_strips;
     a.prof = X.prof;
     a.go2 = half_pair(go);
@@ -887,23 +928,30 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
     a.flag_count = X.flags;
     a.flag_list = flist;
     a.sat_limit = effective_limit(db->sat_limit);
-    if (bins) return (*bins)(a, R, W, s);
-    if (n_bins > off_bins) {
-      const int ti = time_begin(db, kTimeInter, s);
-      if ((e = launch_inter(R, W, n_bins - off_bins, a, s)) != hipSuccess)
+    a.drift = drift;
+    hipStream_t bs = s;
+    if (pairs) {
+      bs = db->aux_stream;
+      if ((e = hipStreamWaitEvent(bs, db->ev_fork, 0)) != hipSuccess)
+        return hip_fail(e, "stream wait");
+    }
+    if (bins) {
+      const int rc = (*bins)(a, R, W, bs);
+      if (rc != SW_OK) return rc;
+    } else if (n_bins > off_bins) {
+      const int ti = time_begin(db, kTimeInter, bs);
+      if ((e = launch_inter(R, W, db->d->n_cus, a, bs)) != hipSuccess)
         return hip_fail(e, "inter-task kernel");
-      time_end(db, ti, s);
+      time_end(db, ti, bs);
       ++db->stats.n_inter_launches;
     }
+    if (pairs && (e = hipEventRecord(db->ev_join, bs)) != hipSuccess) return hip_fail(e, "event");
     return SW_OK;
   };
-
-  // long sequences (and handed-over bins): packed long-pair kernel on the
-  // auxiliary stream, overlapped with the inter-task bins
+  // long sequences (and handed-over bins): packed long-pair kernel, on this
+  // stream beside the bins on the auxiliary one
   auto run_pairs = [&]() -> int {
     if (!pairs) return SW_OK;
-    if ((e = hipStreamWaitEvent(db->aux_stream, db->ev_fork, 0)) != hipSuccess)
-      return hip_fail(e, "stream wait");
     IntraPairArgs la{};
     la.res = db->d->res.p;
     la.offs = db->d->offs.p;
@@ -930,33 +978,43 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
       la.scratch_stride = seg_stride(*db->d);
       grid = std::min<int>(X.grid_seg, la.count);
     }
-    const int tl = time_begin(db, kTimeIntra, db->aux_stream);
-    if ((e = launch_intra_pairs(RR, W2, grid, la, db->aux_stream)) != hipSuccess)
+    // Beside the persistent inter-task kernel the pairs take kPairShare times
+    // their share of the search's work: too many workgroups hold up the bins
+    // (the longest is the critical path of a short query), too few end after
+    // them.  Measured on the plain database (ms, m = 144 / 977 / 5,478):
+    // share x 1.2 2.64 / 15.0 / 60.0, x 2.5 1.66 / 9.24 / 38.6, x 5 1.50 / 7.71 /
+    // 38.6.
+    if (n_bins > off_bins) {
+      const int64_t pass_rows = 64 * (int64_t)RR;
+      const double rows = (double)((m + pass_rows - 1) / pass_rows * pass_rows);
+      const double pair_res = (double)db->d->long_residues +
+                              (off_bins > 0 ? (double)db->d->bin_res_cum[(size_t)off_bins] : 0.0);
+      const double t_pair = rows * pair_res / kPairRate;
+      const double t_inter = (double)m * ((double)db->d->n_res - pair_res) / kInterRate;
+      const double share = t_pair / (t_pair + t_inter);
+      grid = std::min<int>(grid, (int)(kPairShare * share * db->d->n_cus * 4 / W2) + 1);
+    }
+    const int tl = time_begin(db, kTimeIntra, s);
+    if ((e = launch_intra_pairs(RR, W2, grid, la, s)) != hipSuccess)
       return hip_fail(e, "intra-task kernel");
     db->stats.long_items = la.count;
     db->stats.long_overlap = segmented ? overlap : -1;
     if (segmented &&
         (e = launch_long_combine(db->d->d_long_pairs.p, db->d->d_pair_seg0.p,
                                  (int32_t)(db->d->n_long_pairs + off_pairs), X.seg_best,
-                                 la.sat_limit, d_out, X.flags, flist, db->aux_stream)) !=
-            hipSuccess)
+                                 la.sat_limit, d_out, X.flags, flist, s)) != hipSuccess)
       return hip_fail(e, "segment maxima");
-    time_end(db, tl, db->aux_stream);
-    if ((e = hipEventRecord(db->ev_join, db->aux_stream)) != hipSuccess)
-      return hip_fail(e, "event");
+    time_end(db, tl, s);
     return SW_OK;
   };
 
-  // The bins go first: the longest bin's workgroup is the inter-task
-  // kernel's critical path and starts at once, before the long pairs' large
-  // workgroups fill the CUs.  A bin runner (hybrid and allocation-free
-  // searches) returns only when its bins are done, so there the pairs go first.
+  // The pairs go first and on this stream: the inter-task kernel is persistent
+  // and holds every CU it gets until its queue is empty, so the pairs' share of
+  // the CUs has to be taken when it starts, a stream wait later.  Its queue
+  // evens out what the share got wrong: workgroups that find no CU free start
+  // where a pair's has ended.
   int rc;
-  if (bins) {
-    if ((rc = run_pairs()) != SW_OK || (rc = run_bins()) != SW_OK) return rc;
-  } else {
-    if ((rc = run_bins()) != SW_OK || (rc = run_pairs()) != SW_OK) return rc;
-  }
+  if ((rc = run_pairs()) != SW_OK || (rc = run_bins()) != SW_OK) return rc;
   // both packed kernels fill the rescoring list: join before consuming it
   if (pairs && (e = hipStreamWaitEvent(s, db->ev_join, 0)) != hipSuccess)
     return hip_fail(e, "stream wait");
@@ -1517,13 +1575,12 @@ int run_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, int3
 // device, looked up once per device (noalloc_setup) and kept in g_noalloc.
 //
 // Layout: the first kNoAllocRowBytes hold the inter-task boundary rows of one
-// chunk of short bins at a time.  That part holds zeros between calls: it is
-// cleared at set-up, and the last strip of every bin writes zeros back over
-// its rows, as in the handle's own boundary buffer.  The rest is laid out per
-// call (noalloc_layout): rescoring list, the three profiles, the rescoring
-// kernel's rows and the long-sequence kernel's rows; none of it has to start
-// at zero (the profile kernel clears the list's count, and the intra-task
-// kernels read a boundary row only after a pass has written it).
+// chunk of short bins at a time.  The rest is laid out per call
+// (noalloc_layout): rescoring list, the three profiles, the rescoring
+// kernel's rows and the long-sequence kernel's rows.  None of it has to start
+// at zero: the profile kernel clears the list's count, the first strip of a bin
+// drops what it reads, and the intra-task kernels read a boundary row only
+// after a pass has written it.
 static __device__ __align__(256) uint8_t scratch[SW_NOALLOC_SCRATCH_BYTES];
 
 namespace swdb {
@@ -1540,8 +1597,8 @@ struct NoAllocDevice {
 std::mutex g_noalloc_mu;
 NoAllocDevice g_noalloc[kNoAllocMaxDevices];
 
-// Looks up device `device`'s copy of the scratch array and clears its
-// boundary-row part, once per device; the device must be current.
+// Looks up device `device`'s copy of the scratch array, once per device; the
+// device must be current.
 int noalloc_setup(int device, uint8_t** out) {
   if (device < 0 || device >= kNoAllocMaxDevices)
     return fail(SW_ERANGE, "allocation-free search: device index above 63");
@@ -1551,11 +1608,6 @@ int noalloc_setup(int device, uint8_t** out) {
     void* p = nullptr;
     hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess || !p) return hip_fail(e, "scratch address");
-    // a fill kernel, then wait: set-up happens once, before any search uses it
-    if ((e = launch_fill(reinterpret_cast<int32_t*>(p), (int64_t)(kNoAllocRowBytes / 4), 0,
-                         nullptr)) != hipSuccess ||
-        (e = hipStreamSynchronize(nullptr)) != hipSuccess)
-      return hip_fail(e, "scratch clear");
     nd.ptr = reinterpret_cast<uint8_t*>(p);
   }
   *out = nd.ptr;
@@ -1586,7 +1638,7 @@ int noalloc_layout(const Searcher* db, const SearchShape& sh, uint8_t* base, NoA
   };
   L->X.rb = reinterpret_cast<uint4*>(base);
   L->X.flags = reinterpret_cast<int32_t*>(take(z.flags * 4));
-  L->X.prof = reinterpret_cast<uint32_t*>(take(z.prof * 4));
+  L->X.prof = reinterpret_cast<uint32_t*>(take(z.prof * 4));   // kProfSlack: the next part
   L->X.prof2 = reinterpret_cast<int8_t*>(take(z.prof2));
   L->X.prof3 = P.n_long > 0 ? reinterpret_cast<uint32_t*>(take(z.prof3 * 4)) : nullptr;
   L->X.seg_best =
@@ -2287,8 +2339,10 @@ static int impl_search_hybrid(swdb::Searcher* db, const uint8_t* query, int32_t 
       take = std::min(take, rem);
       front.store(b0 + take);
       a.bin_begin = (int32_t)b0;
+      a.n_bins = (int32_t)take;
       hipError_t err;
-      if ((err = launch_inter(R, W, (int)take, a, st_)) != hipSuccess)
+      if ((k > 0 && (err = launch_fill(a.counter, 1, 0, st_)) != hipSuccess) ||
+          (err = launch_inter(R, W, D.n_cus, a, st_)) != hipSuccess)
         return hip_fail(err, "inter-task kernel");
       if ((err = hipEventRecord(db->ev_chunk[k & 1], st_)) != hipSuccess)
         return hip_fail(err, "event");
@@ -2457,10 +2511,12 @@ static int impl_search_async_noalloc(swdb::Searcher* db, const uint8_t* d_query,
                  kNoAllocRowBytes)
         ++b1;
       a.bin_begin = (int32_t)b0;
+      a.n_bins = (int32_t)(b1 - b0);
       a.rb = L.X.rb;
       a.rb_base = first;
       hipError_t err;
-      if ((err = launch_inter(R, W, (int)(b1 - b0), a, st)) != hipSuccess)
+      if ((b0 > 0 && (err = launch_fill(a.counter, 1, 0, st)) != hipSuccess) ||
+          (err = launch_inter(R, W, D.n_cus, a, st)) != hipSuccess)
         return hip_fail(err, "inter-task kernel");
       ++db->stats.n_inter_launches;
       b0 = b1;
