@@ -350,7 +350,8 @@ enum sw_option {
                              16 otherwise), 32 (not with 12 or 16 waves);
                              batched searches: 12 .. 20 with 12 waves, 12 and
                              14 with 16, 16 or 32 otherwise, auto fitted to
-                             the pairs' lengths */
+                             the pairs' lengths (24 x 12 and 16 x 16 among
+                             the forms) */
   SW_OPT_WAVES = 4,       /* inter-task waves per workgroup: 0 (auto), 1, 2, 4, 8, 12,
                              16 (12 not with 32 rows; 16 with 12 or 14 rows,
                              four waves per SIMD; batched searches: 4, 8, 12,

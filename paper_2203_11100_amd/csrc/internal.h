@@ -183,7 +183,9 @@ struct IntraPairArgs {
 // Batched inter-task kernel: the two 16-bit halves of a lane hold two
 // queries (a pair) against one database sequence.  The pair's profile has
 // the inter-task layout (rows in pairs, code-major within a pair) with the
-// dword of row i and code c holding (S(a_i, c), S(b_i, c)).
+// dword of row i and code c holding (S(a_i, c), S(b_i, c)) in binary16, or
+// (drift form) the 32-bit sum of S(a_i, c) + 2 ge and, shifted up 16 bits,
+// S(b_i, c) + 2 ge.
 constexpr int kBatchRowDwords = kProfRowDwords;
 
 struct PairDesc {
@@ -203,13 +205,15 @@ struct BatchArgs {
   const uint32_t* prof;
   uint32_t go2, ge2;
   uint4* rb;                  // per-workgroup boundary rows
-  int64_t rb_stride;          // uint4 per workgroup
+  int64_t rb_stride;          // uint4 per workgroup (128 a chunk), at least the longest bin's
   const int32_t* slot_seq;
   int32_t* out;               // [n_queries][n_seqs]
   int64_t n_seqs;
   int32_t* flag_count;        // rescoring list: count, then {sid, query}
   int2* flag_list;
   int32_t sat_limit;
+  DriftArgs drift;
+  int32_t max_s;              // the matrix's largest score, at least 0
 };
 
 // Device state of the top-k selection (k_hits.hip): the radix histogram,
@@ -268,7 +272,7 @@ hipError_t launch_hit_combine(const int2* items, int32_t k, const int32_t* seg0,
 // receives the queries' packed long-pair profiles.
 hipError_t launch_batch_profiles(const uint8_t* d_queries, const int64_t* d_qoffs, int n_queries,
                                  const Matrix& mat, const PairDesc* d_pairs, int n_pairs, int R,
-                                 int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
+                                 int drift, int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
                                  int8_t* prof2, uint32_t* prof3, hipStream_t s);
 
 }  // namespace swdb

@@ -51,18 +51,10 @@
 // one or two dwords per lane per chunk, so the copy holds few registers.
 #include "internal.h"
 #include "packed16.h"
+#include "stream.h"
 
 namespace swdb {
 namespace {
-
-// Bins whose scores are being gathered in one workgroup at once: a wave that
-// would start a bin further ahead waits for the oldest to be finished.
-constexpr int kRing = 4;
-// A wave's progress: its item's number in the bits from kProgBits up (modulo
-// 2^9), finished chunks below.  Compared by signed difference: a wave is at most
-// a few items ahead of the one that waits for it.
-constexpr int kProgBits = 23;
-static_assert((SW_MAX_LEN >> 2) + 2 < (1 << kProgBits), "chunks fit the progress word");
 
 template <int R, int W, bool kDrift>
 __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
@@ -111,20 +103,8 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
   uint32_t cv = dr.c2;      // in a vector register: a 32-bit subtraction with a
   asm("" : "+v"(cv));       // scalar operand runs at the packed ops' rate only
 
-  auto peek = [&](auto* p) {
-    return __builtin_amdgcn_readfirstlane(
-        (int)__hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-  };
-  auto publish = [&](auto* p, auto v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-  };
   uint32_t known = ~0u;          // the predecessor's progress as last read
-  auto wait_pred = [&](uint32_t need) {
-    while ((int)(known - need) < 0) {
-      known = (uint32_t)peek(&lprog[pred]);
-      if ((int)(known - need) < 0) __builtin_amdgcn_s_sleep(16);
-    }
-  };
+  auto wait_pred = [&](uint32_t need) { wait_progress(&lprog[pred], known, need); };
 
   // one 64-bit LDS read per row pair and sequence gives both rows' dwords,
   // from the low table for the low half's residue and from the high table for
@@ -155,7 +135,7 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
     if (s == 0) {
       if (k > 0 || w > 0) wait_pred(there);
       if (!peek(&lend)) {
-        while (peek(&lfree[slot]) != n) __builtin_amdgcn_s_sleep(16);
+        while (peek(&lfree[slot]) != n) poll_pause();
         if (lane == 0) b = atomicAdd(a.counter, 1);
         b = __builtin_amdgcn_readfirstlane(b);
         if (b >= a.n_bins) {
@@ -187,9 +167,9 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
     uint4 b0_n, b1_n;
     auto fetch = [&](int c) {
       rr_n = *reinterpret_cast<const uint2*>(rbin + (size_t)c * 512 + lane * 8u);
-      const uint4* p = reinterpret_cast<const uint4*>(rbb + (size_t)c * 2048 + lane * 32u);
+      const uint4* p = reinterpret_cast<const uint4*>(rbb + (size_t)c * 2048 + lane * 16u);
       b0_n = p[0];
-      b1_n = p[1];
+      b1_n = p[64];
     };
     fetch(0);
 
@@ -242,13 +222,22 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
 #pragma unroll
       for (int y = 0; y < kPer; ++y) st[y] = st_src[y * 64 + lane];
       __builtin_amdgcn_sched_barrier(0);   // keep the loads ahead of the compute
-      // the strip's bottom row, (H, F) per column, stored as each column is
-      // done (column jj at 8 jj bytes of the lane's 32-byte chunk entry)
-      uint2* pbd = reinterpret_cast<uint2*>(rbb + (size_t)c * 2048 + lane * 32u);
+      // the strip's bottom row, (H, F) per column, stored two columns at a time,
+      // a kilobyte in one piece (8 bytes a column and lane, 32 apart, took four
+      // times the cache's write requests and bound the 12-row strips)
+      uint4* pbd = reinterpret_cast<uint4*>(rbb + (size_t)c * 2048 + lane * 16u);
+      uint32_t h_even = 0, f_even = 0;
       auto prof_pair = [&](int jj, int k2, uint2& pa, uint2& pb) {
         read_pair(slotp, rr, jj, k2, pa, pb);
       };
-      auto emit = [&](int jj, uint32_t h, uint32_t f) { pbd[jj] = make_uint2(h, f); };
+      auto emit = [&](int jj, uint32_t h, uint32_t f) {
+        if (jj & 1) {
+          pbd[jj / 2 * 64] = make_uint4(h_even, f_even, h, f);
+        } else {
+          h_even = h;
+          f_even = f;
+        }
+      };
       if constexpr (kDrift) {
         drift_chunk<R, true>(H, E, A, hdiag, up_h, up_f, best, cv, zc, dr.ge2, prof_pair, emit);
         zc += 4 * dr.ge2;

@@ -62,13 +62,14 @@ __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
 // Pair profiles and intra-task profiles of a batch.  blockIdx.y < n_pairs
 // selects a pair: the dword of row i and code c of its profile (n_strips * R
 // rows in the kProfRowDwords layout) holds (S(a_i, c), S(b_i, c)) as
-// binary16, kPadScore past either query's end.  Larger
+// binary16 or, with drift >= 0, the 32-bit sum of S(a_i, c) + 2 drift and,
+// shifted up 16 bits, S(b_i, c) + 2 drift; kPadScore past either query's end.  Larger
 // blockIdx.y select a query's intra-task [25][m_pad2] int8 profile and, when
 // prof3 is given, its packed [25][m_pad2 / 2] binary16 row pairs.
 __global__ void k_batch_profiles(const uint8_t* __restrict__ queries,
                                  const int64_t* __restrict__ qoffs, Matrix mat,
                                  const PairDesc* __restrict__ pairs, int n_pairs, int R,
-                                 uint32_t* __restrict__ prof,
+                                 int drift, uint32_t* __restrict__ prof,
                                  const QueryDesc* __restrict__ qdesc, int8_t* __restrict__ prof2,
                                  uint32_t* __restrict__ prof3) {
   const int y = blockIdx.y;
@@ -84,9 +85,10 @@ __global__ void k_batch_profiles(const uint8_t* __restrict__ queries,
     for (int64_t idx = start; idx < total; idx += stride) {
       const int rem = (int)(idx % kProfPairDwords);
       const int i = 2 * (int)(idx / kProfPairDwords) + (rem & 1), c = rem >> 1;
-      const uint32_t lo = half_bits(profile_score(qa, ma, mat, i, c));
-      const uint32_t hi = half_bits(profile_score(qb, mb, mat, i, c));
-      prof[pd.prof_off + idx] = lo | (hi << 16);
+      const int sa = profile_score(qa, ma, mat, i, c), sb = profile_score(qb, mb, mat, i, c);
+      prof[pd.prof_off + idx] =
+          drift >= 0 ? (uint32_t)(sa + 2 * drift) + ((uint32_t)(sb + 2 * drift) << 16)
+                     : half_bits(sa) | ((uint32_t)half_bits(sb) << 16);
     }
   } else {
     const int qi = y - n_pairs;
@@ -133,14 +135,14 @@ hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint
 
 hipError_t launch_batch_profiles(const uint8_t* d_queries, const int64_t* d_qoffs, int n_queries,
                                  const Matrix& mat, const PairDesc* d_pairs, int n_pairs, int R,
-                                 int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
+                                 int drift, int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
                                  int8_t* prof2, uint32_t* prof3, hipStream_t s) {
   const int ys = n_pairs + n_queries;
   if (ys <= 0) return hipSuccess;
   if (ys > 65535) return hipErrorInvalidValue;
   const int gx = (int)std::max<int64_t>(1, std::min<int64_t>((max_work + 255) / 256, 256));
   hipLaunchKernelGGL(k_batch_profiles, dim3(gx, ys), dim3(256), 0, s, d_queries, d_qoffs, mat,
-                     d_pairs, n_pairs, R, prof, d_qdesc, prof2, prof3);
+                     d_pairs, n_pairs, R, drift, prof, d_qdesc, prof2, prof3);
   return hipGetLastError();
 }
 

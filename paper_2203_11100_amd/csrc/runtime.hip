@@ -127,6 +127,7 @@ struct BatchPlan {
   int64_t n_items = 0, n_long_items = 0, max_pair_work = 0, max_query_work = 0;
   int64_t inter_cells = 0, intra_cells = 0;
   int grid_b = 0, grid_long = 0;
+  swdb::DriftArgs drift{};
   std::vector<int32_t> zero_queries;
   swdb::DevBuf<swdb::PairDesc> pairs;
   swdb::DevBuf<swdb::QueryDesc> qdesc;
@@ -467,12 +468,14 @@ struct Sched {
 constexpr Sched kScheds[] = {{20, 12, 0.835}, {18, 12, 0.821}, {16, 12, 0.838}, {14, 12, 0.810},
                              {12, 12, 0.814}, {14, 16, 0.868}, {12, 16, 0.863}};
 
-// The batched kernel's fitted schedules, with relative efficiencies from the
-// batched workload (220 queries, every form forced): GCUPS x padded rows /
-// rows over its pairs, divided by 10,000.
-constexpr Sched kBatchScheds[] = {{20, 12, 0.855}, {18, 12, 0.848}, {16, 12, 0.833},
-                                  {14, 12, 0.845}, {12, 12, 0.834}, {14, 16, 0.843},
-                                  {12, 16, 0.861}};
+// The batched kernel's fitted schedules, with relative efficiencies: padded
+// rows / kernel time of 24 queries of 50 .. 5,000 residues against 100,000
+// plain sequences, every form forced (186.8 ms at 24 x 12, 200.0 at 12 x 12).
+// Taller strips pay less for boundary rows and chunk starts, four waves a SIMD
+// (16 waves, <= 128 VGPRs) hide more than three.
+constexpr Sched kBatchScheds[] = {{24, 12, 1.000}, {16, 16, 0.997}, {20, 12, 0.987},
+                                  {14, 16, 0.973}, {18, 12, 0.964}, {16, 12, 0.964},
+                                  {14, 12, 0.951}, {12, 16, 0.951}, {12, 12, 0.932}};
 
 // A bin of C chunks takes ceil(S / W) rounds of its S = ceil(m / R) strips,
 // each round C supersteps of W waves' chunks, so its time is proportional
@@ -610,31 +613,45 @@ int32_t effective_limit(int32_t requested) {
   return std::max<int32_t>(0, std::min<int32_t>(requested, kHalfExact));
 }
 
+// The matrix's largest score, at least 0.
+int max_score(const Matrix& mat) {
+  int max_s = 0;
+  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) max_s = std::max<int>(max_s, mat.v[x]);
+  return max_s;
+}
+
 // The drift form's parameters for a kernel whose bins have at most `cols`
 // columns and whose strips have R rows (the arithmetic and the meaning of the
 // range: packed16.h), or group = 0 where it does not fit and the binary16 form
 // is used: gap_extend so large that the drift over the columns and one strip
 // leaves no room (above 13 at 2,048 columns).  The drift over the rows starts
 // again every `group` strips, as many as fit (all of a usual query's).
+// Batches give the columns of the short bins too: the groups are then sized so
+// that these need no guard where that leaves at least 8 strips, and the kernel
+// guards the matrices that do.
 DriftArgs drift_plan(int m, int64_t cols, int R, const Matrix& mat, int32_t go, int32_t ge,
-                     int32_t sat_limit) {
+                     int32_t sat_limit, int64_t short_cols = 0) {
   DriftArgs d{};
   const int64_t limit = effective_limit(sat_limit);
-  int max_s = 0;
-  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) max_s = std::max<int>(max_s, mat.v[x]);
+  const int max_s = max_score(mat);
   // room for the drift of columns and rows, when scores stay below what the
   // lengths allow, or (guard) within some columns' gain of the limit
   const int64_t top = kDriftTop - (int64_t)kDriftBase - 256;
-  const int64_t score = std::max<int64_t>(std::min<int64_t>(m, cols) * max_s, limit);
-  const int64_t guarded = limit + (int64_t)(R + 8) * max_s;
-  auto groups = [&](int64_t highest) -> int64_t {
-    if (ge == 0) return highest <= top ? INT32_MAX / R : 0;
-    return ((top - highest) / ge - cols - R - 8) / R;
+  auto score = [&](int64_t n) {
+    return std::max<int64_t>(std::min<int64_t>((m + R - 1) / R * R, n) * max_s, limit);
   };
-  int64_t g = groups(score);
-  if (g < 1 || (top - score) < 0) {
-    g = (top - guarded) < 0 ? 0 : groups(guarded);
+  const int64_t guarded = limit + (int64_t)(R + 8) * max_s;
+  auto groups = [&](int64_t highest, int64_t n) -> int64_t {
+    if (highest > top) return 0;
+    if (ge == 0) return INT32_MAX / R;
+    return ((top - highest) / ge - n - R - 8) / R;
+  };
+  int64_t g = groups(score(cols), cols);
+  if (g < 1) {
+    g = groups(guarded, cols);
     d.guard = 1;
+    const int64_t gs = short_cols > 0 ? groups(score(short_cols), short_cols) : 0;
+    if (gs >= 8) g = std::min(g, gs);
   }
   if (g < 1) return DriftArgs{};
   d.group = (int32_t)std::min<int64_t>(g, (m + R - 1) / R);
@@ -670,9 +687,7 @@ int64_t seg_stride(const DbData& d) {
 // segment's columns (lower bounds elsewhere).  Used when this reach is at
 // most one segment (short queries) and extend > 0.
 int64_t window_reach(int m, const Matrix& mat, int32_t ge) {
-  int max_s = 0;
-  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) max_s = std::max<int>(max_s, mat.v[x]);
-  return (int64_t)m + ((int64_t)m * max_s + ge - 1) / ge;
+  return (int64_t)m + ((int64_t)m * max_score(mat) + ge - 1) / ge;
 }
 
 int32_t seg_overlap(const DbData& d, int m, const Matrix& mat, int32_t ge) {
@@ -1248,16 +1263,16 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
       if (db->tune_brows[b]) { R = db->tune_brows[b]; W = db->tune_bwaves[b]; tuned = true; }
     }
     if (!tuned && !lens.empty()) {
-      // a pair of neighbouring lengths costs ceil(S / W) rounds of its
-      // S = ceil(m / R) strips (m the longer query) for every half bin
+      // a pair of neighbouring lengths costs its ceil(m / R) strips (m the
+      // longer query) for every half bin: the waves take strips without a seam,
+      // so no round of W is left short
       double best = 1e300;
       for (const Sched& c : kBatchScheds) {
         if ((db->opt_rows && c.R != db->opt_rows) || (db->opt_waves && c.W != db->opt_waves))
           continue;
         double cost = 0;
         for (size_t i = 0; i < lens.size(); i += 2) {
-          const int64_t strips = (lens[i] + c.R - 1) / c.R;
-          cost += (double)((strips + c.W - 1) / c.W) * c.W * c.R / c.eff;
+          cost += (double)((lens[i] + c.R - 1) / c.R * c.R) / c.eff;
         }
         if (cost < best) { best = cost; R = c.R; W = c.W; }
       }
@@ -1270,7 +1285,8 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
     W = db->opt_waves;
   if (W == 12 && R == 32) W = 8;                   // no 12-wave form of 32 rows
   if (R == 20) W = 12;                             // 20 rows: 12 waves only
-  if (W == 16 && R != 12 && R != 14) R = 12;       // 16 waves: 12- or 14-row strips
+  if (W == 16 && R != 12 && R != 14 && !(R == 16 && !db->opt_rows))
+    R = 12;                                        // 16 waves: 12- or 14-row strips, 16 fitted
   if (W != 12 && W != 16 && R != 16 && R != 32) R = 16;
   std::vector<int64_t> qv(qoffs, qoffs + nq + 1);
   if (B.valid && B.qoffs == qv && memcmp(&B.mat, &mat, sizeof(mat)) == 0 && B.go == go &&
@@ -1370,7 +1386,7 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
       (e = B.vpairs.reserve(std::max<size_t>(vpairs.size(), 1))) != hipSuccess ||
       (e = B.prof3.reserve((size_t)std::max<int64_t>(prof3_dw, 4))) != hipSuccess ||
       (e = B.qoffs_d.reserve(qv.size())) != hipSuccess ||
-      (e = B.prof.reserve((size_t)std::max<int64_t>(prof_dw, 1))) != hipSuccess ||
+      (e = B.prof.reserve((size_t)prof_dw + kProfSlack)) != hipSuccess ||
       (e = B.prof2.reserve((size_t)std::max<int64_t>(prof2_bytes, 16))) != hipSuccess)
     return fail(SW_ENOMEM, std::string("batch allocation: ") + hipGetErrorString(e));
   if ((e = put(B.pairs.p, pairs.data(), pairs.size() * sizeof(PairDesc))) != hipSuccess ||
@@ -1380,6 +1396,9 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
       (e = put(B.vpairs.p, vpairs.data(), vpairs.size() * sizeof(int2))) != hipSuccess ||
       (e = put(B.qoffs_d.p, qv.data(), qv.size() * sizeof(int64_t))) != hipSuccess)
     return hip_fail(e, "batch descriptors");
+  B.drift = n_nz ? drift_plan((int)ms[order[0]], db->d->plan.max_all_bin_len, R, mat, go, ge,
+                              db->sat_limit, db->d->plan.max_bin_len)
+                 : DriftArgs{};
   B.n_pairs = (int)pairs.size();
   B.n_items = (int64_t)items.size();
   B.n_long_items = (int64_t)litems.size();
@@ -1427,6 +1446,7 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
     return SW_OK;
   }
   if ((e = launch_batch_profiles(B.d_queries, B.qoffs_d.p, nq, B.mat, B.pairs.p, B.n_pairs, B.R,
+                                 B.drift.group > 0 ? B.ge : -1,
                                  std::max(B.max_pair_work, B.max_query_work), B.prof.p, B.qdesc.p,
                                  B.prof2.p, B.n_long_items > 0 ? B.prof3.p : nullptr, s)) !=
       hipSuccess)
@@ -1493,6 +1513,8 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
     ba.flag_count = db->flags.p;
     ba.flag_list = flag_list(db);
     ba.sat_limit = effective_limit(B.sat_limit);
+    ba.drift = B.drift;
+    ba.max_s = max_score(B.mat);
     const int ti = time_begin(db, kTimeInter, s);
     if ((e = launch_batch(B.R, B.W, B.grid_b, ba, s)) != hipSuccess)
       return hip_fail(e, "batched inter-task kernel");

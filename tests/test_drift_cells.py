@@ -29,7 +29,7 @@ def drift_plan(m, cols, R, matrix, go, ge, limit):
     """The host's rule: (strips per group, guard), or (0, _) for the other form."""
     max_s = max(0, int(matrix.max()))
     top = TOP - BASE - 256
-    score = max(min(m, cols) * max_s, limit)
+    score = max(min(-(-m // R) * R, cols) * max_s, limit)
     guarded = limit + (R + 8) * max_s
 
     def groups(highest):
@@ -137,10 +137,10 @@ def test_drift_cells_match_the_oracle(m, R, go, ge, limit, matrix):
         assert (drift_scores(q, seqs, mat, go, ge, R, min(limit, EXACT), other) == got).all()
 
 
-RING, DONE = 4, (1 << 23) - 1
+DONE = (1 << 23) - 1
 
 
-def run_stream(W, S, chunks, seed, workgroups):
+def run_stream(W, S, chunks, seed, workgroups, RING):
     """Random interleaving of the waves of some workgroups; raises on a wrong
     read, a bin scored twice or not at all, or no progress."""
     rng = random.Random(seed)
@@ -217,4 +217,4 @@ def test_strip_stream_scores_every_bin_once(W):
         r = random.Random(100 * W + t)
         S = r.choice([1, 2, 3, 5, 7, 11, 12, 13, 16, 17, 31, 40])
         chunks = [r.choice([2, 3, 5, 8, 24]) for _ in range(r.randint(1, 12))]
-        run_stream(W, S, chunks, t, r.choice([1, 1, 2, 3]))
+        run_stream(W, S, chunks, t, r.choice([1, 1, 2, 3]), r.choice([4, 16]))

@@ -86,3 +86,28 @@ def test_guarded_scores_and_long_bins(sw, m, t_long, ge):
         bad = np.nonzero(got != want)[0]
         assert len(bad) == 0, [(int(i), int(got[i]), int(want[i])) for i in bad[:5]]
         assert st["n_rescored"] == int((want >= 2048).sum())
+
+
+# batches: both cell forms, matrices with and without the guard in one launch
+# (long bins), boundary rows given out round and round (a long bin fills them),
+# queries of a single strip (more entries in flight than waves) and of many
+@pytest.mark.parametrize("go,ge,matrix", [(10, 2, "b62"), (10, 0, "b62"), (12, 4, "b62"),
+                                          (20, 14, "b62"), (12, 2, "hot")])
+@pytest.mark.parametrize("lens", [[1, 7, 13], [5] * 40, [300, 23, 2600, 900, 24], [1500, 1400]])
+def test_batches(sw, go, ge, matrix, lens):
+    res, offs, rng = _db(sum(lens), 8191)          # default threshold: short and long bins
+    qs = [swinputs.random_residues(m, rng) for m in lens]
+    sizes = np.diff(offs)
+    for i in np.argsort(sizes)[-30::3]:
+        n = int(sizes[i])
+        res[offs[i]:offs[i] + n] = np.resize(qs[0], n)
+    mat = _hot() if matrix == "hot" else B62
+    say("batch %s gaps %d/%d %s" % (lens[:5], go, ge, matrix))
+    with sw.Database(res, offs) as db:
+        got = db.search_batch(qs, mat, go, ge)
+        for _ in range(2):                          # the captured graph again
+            assert (db.search_batch(qs, mat, go, ge) == got).all()
+    for q, row in zip(qs, got):
+        want = ocpu.search(q, res, offs, mat, go, ge)
+        bad = np.nonzero(row != want)[0]
+        assert len(bad) == 0, [(int(i), int(row[i]), int(want[i])) for i in bad[:5]]
