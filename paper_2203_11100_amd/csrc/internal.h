@@ -73,6 +73,17 @@ struct DriftArgs {
   uint32_t lim2, over2;       // the rescoring limit; 32768 - the limit
 };
 
+// A global or semi-global search in the drift form (k_inter.hip): H~ = H + base
+// + ge * (row + column), the query's rows shifted down so that its last row is
+// the last strip's last.
+struct ModeShape {
+  int32_t mode;               // SW_MODE_LOCAL: the fields below are not used
+  int32_t pad;                // rows above the query's first, < R
+  int32_t base;
+  int32_t go, ge, m;
+  const int64_t* offs;        // sequence offsets
+};
+
 struct InterArgs {
   const uint2* res2;          // interleaved store viewed as (lo, hi) dword pairs
   const BinDesc* bins;
@@ -89,6 +100,7 @@ struct InterArgs {
   int2* flag_list;
   int32_t sat_limit;          // rescoring limit, at most the exact range (see effective_limit)
   DriftArgs drift;
+  ModeShape mode;
 };
 
 // Per-query parameters of the intra-task kernel.
@@ -233,8 +245,10 @@ struct TopkState {
 static_assert(sizeof(TopkState) % 8 == 0, "TopkState keeps the arrays after it 8-byte aligned");
 
 // Kernel launchers (return hipSuccess or the launch error).
+// drift: gap_extend of the drift form or -1; top: rows above the query's first,
+// of the score top_score against every code
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
-                          int m_pad, int R, int drift, int8_t* prof2, uint32_t* prof3, int m_pad2,
+                          int m_pad, int R, int drift, int top, int top_score, int8_t* prof2, uint32_t* prof3, int m_pad2,
                           int32_t* flag_count, hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_inter(int R, int W, int n_cus, const InterArgs& a, hipStream_t s);

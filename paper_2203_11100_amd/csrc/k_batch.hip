@@ -209,7 +209,7 @@ __global__ __launch_bounds__(64 * W) void k_batch(BatchArgs a) {
       // residue bytes hold 8 x code, the byte offset of the code's dword pair in
       // a row pair: one 64-bit LDS read gives two rows
       if constexpr (kDrift) {
-        drift_chunk<R, false>(H, E, A, hdiag, up_h, up_f, best, cv, zc, dr.ge2,
+        drift_chunk<R, false, true>(H, E, A, hdiag, up_h, up_f, best, cv, zc, dr.ge2,
                               [&](int jj, int k2, uint2& pa, uint2&) {
           pa = reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(slotp) +
                                               ((rr >> (8 * jj)) & 0xffu))[k2 * kBatchRowDwords];

@@ -56,8 +56,26 @@
 namespace swdb {
 namespace {
 
-template <int R, int W, bool kDrift>
+// The cell form: binary16 or drift local scores, global or semi-global scores
+// (drift form, without the floor and the maximum).
+//
+// Global and semi-global: with H(i, 0) = -w(i), w(k) = go + (k - 1) ge, and the
+// drift ge * (row + column) over 0-based rows and columns, the left border is
+// the constant base - go - ge (a border gap costs its opening only) and so is
+// the global mode's top border; the semi-global top border, H = 0, is base + ge *
+// (column - 1).  E and F start c below the borders.  The query's rows are
+// shifted down by `pad`, so that its last row is the last strip's last and its
+// H comes out of the strip's sweep; the rows above it repeat the top border:
+// in semi-global mode they score 0 against everything (0 along the diagonals),
+// in global mode they score -2 ge and E holds the border.  The score is the last
+// row's H at the sequence's last column (global) or its maximum over the
+// sequence's columns, both taken by the last strip.
+enum { kCellHalf = 0, kCellDrift = 1, kCellGlobal = 2, kCellSemi = 3 };
+
+template <int R, int W, int kForm>
 __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
+  constexpr bool kDrift = kForm == kCellDrift;
+  constexpr bool kMode = kForm == kCellGlobal || kForm == kCellSemi;
   constexpr int kSlot = prof_strip_dwords(R);
   constexpr int kHighBytes = R * kProfRowDwords * 4;   // the high table's offset
   constexpr int kStage = (kSlot + 63) / 64;            // dwords per lane per strip
@@ -180,7 +198,44 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
     uint32_t zc = twice(kDriftBase) + dr.ge2 * (uint32_t)(in_group * R);
     const uint32_t delta2 = s == 0 ? 0xffffffffu : in_group == 0 ? dr.group2 : 0u;
     const bool adjust = delta2 != 0 || dr.guard;
-    if constexpr (kDrift) {
+    const ModeShape& md = a.mode;
+    const uint32_t base2 = twice((uint32_t)md.base);
+    // the row above the query's first in global mode: H~ there, F~ below it c less
+    const uint32_t top2 = twice((uint32_t)(md.base - md.go + md.ge * (md.pad - 1)));
+    uint32_t n2 = 0, score = 0;      // modes, last strip: both sequences' lengths, their scores
+    int sid_lo = -1, sid_hi = -1;
+    if constexpr (kMode) {
+      const uint32_t left2 = twice((uint32_t)(md.base - md.go - md.ge + md.ge * md.pad));
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        H[r] = left2;
+        E[r] = left2 - dr.c2;
+      }
+      hdiag = left2;
+      if (s == 0) {
+        const uint32_t corner2 = base2 + dr.ge2 * (uint32_t)md.pad - 2 * dr.ge2;   // H(0, 0) = 0
+        hdiag = kForm == kCellGlobal && md.pad > 0 ? top2 : base2 - 2 * dr.ge2;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (r < md.pad) {
+            if (kForm == kCellGlobal) {
+              H[r] = r == md.pad - 1 ? corner2 : top2;
+              E[r] = top2;
+            } else {
+              H[r] = base2 + dr.ge2 * (uint32_t)r - dr.ge2;
+              E[r] = H[r] - dr.c2;
+            }
+          }
+        }
+      }
+      if (s == S - 1) {
+        sid_lo = a.slot_seq[bin.slot0 + 2 * lane];
+        sid_hi = a.slot_seq[bin.slot0 + 2 * lane + 1];
+        const int n_lo = sid_lo >= 0 ? (int)(md.offs[sid_lo + 1] - md.offs[sid_lo]) : 0;
+        const int n_hi = sid_hi >= 0 ? (int)(md.offs[sid_hi + 1] - md.offs[sid_hi]) : 0;
+        n2 = (uint32_t)n_lo | ((uint32_t)n_hi << 16);
+      }
+    } else if constexpr (kDrift) {
       drift_start<R>(H, E, A, hdiag, zc, dr.ge2);
     } else {
 #pragma unroll
@@ -200,7 +255,17 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
       const uint2 rr = rr_n;
       uint32_t up_h[4] = {b0_n.x, b0_n.z, b1_n.x, b1_n.z};
       uint32_t up_f[4] = {b0_n.y, b0_n.w, b1_n.y, b1_n.w};
-      if constexpr (kDrift) {
+      if constexpr (kMode) {
+        if (s == 0) {
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) {
+            up_h[jj] = kForm == kCellGlobal ? top2 : base2 + dr.ge2 * (uint32_t)(4 * c + jj) - dr.ge2;
+            up_f[jj] = kForm == kCellGlobal
+                           ? top2 - dr.c2
+                           : base2 + dr.ge2 * (uint32_t)(4 * c + jj) - twice((uint32_t)md.go);
+          }
+        }
+      } else if constexpr (kDrift) {
         if (adjust) drift_adjust(up_h, up_f, delta2, zc - dr.ge2, dr.ge2, dr.lim2);
       } else if (s == 0) {
 #pragma unroll
@@ -227,10 +292,12 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
       // times the cache's write requests and bound the 12-row strips)
       uint4* pbd = reinterpret_cast<uint4*>(rbb + (size_t)c * 2048 + lane * 16u);
       uint32_t h_even = 0, f_even = 0;
+      uint32_t bottom[4];            // modes: the bottom row's H~
       auto prof_pair = [&](int jj, int k2, uint2& pa, uint2& pb) {
         read_pair(slotp, rr, jj, k2, pa, pb);
       };
       auto emit = [&](int jj, uint32_t h, uint32_t f) {
+        if (kMode) bottom[jj] = h;
         if (jj & 1) {
           pbd[jj / 2 * 64] = make_uint4(h_even, f_even, h, f);
         } else {
@@ -238,8 +305,22 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
           f_even = f;
         }
       };
-      if constexpr (kDrift) {
-        drift_chunk<R, true>(H, E, A, hdiag, up_h, up_f, best, cv, zc, dr.ge2, prof_pair, emit);
+      if constexpr (kMode) {
+        drift_chunk<R, true, false>(H, E, A, hdiag, up_h, up_f, best, cv, zc, dr.ge2, prof_pair,
+                                    emit);
+        if (s == S - 1) {
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) {
+            // 0xffff in the halves whose sequence has this column
+            const uint32_t j2 = twice((uint32_t)(4 * c + jj));
+            const uint32_t in = umul2(umin2(usub2_sat(n2, j2), 0x00010001u), 0xffffffffu);
+            if (kForm == kCellGlobal) score = (score & ~in) | (bottom[jj] & in);
+            else score = umax2(score, (bottom[jj] - dr.ge2 * (uint32_t)(4 * c + jj)) & in);
+          }
+        }
+      } else if constexpr (kDrift) {
+        drift_chunk<R, true, true>(H, E, A, hdiag, up_h, up_f, best, cv, zc, dr.ge2, prof_pair,
+                                   emit);
         zc += 4 * dr.ge2;
         if (dr.guard) drift_guard<R>(H, E, A, hdiag, best, dr.over2, zc, dr.ge2);
       } else {
@@ -261,19 +342,37 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
     if constexpr (kDrift) drift_finish<R>(A, best, zc - dr.ge2, dr.ge2);
     if (more) buf ^= 1;
 
+    // modes: the last strip has the scores
+    if constexpr (kMode) {
+      if (s == S - 1) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const int sid = half ? sid_hi : sid_lo;
+          if (sid < 0) continue;
+          const int n_h = (int)(half ? n2 >> 16 : n2 & 0xffffu);
+          const int v = (int)(half ? score >> 16 : score & 0xffffu);
+          // H~ less base and the drift of the last row (and, global, of the last column)
+          const int rows = md.base + md.ge * (S * R - 1);
+          a.out[sid] = n_h == 0 ? -(md.go + (md.m - 1) * md.ge)
+                                : v - rows - (kForm == kCellGlobal ? md.ge * (n_h - 1) : 0);
+        }
+      }
+    }
     // the strip's maxima join the bin's; the wave that brings the last strip
     // writes the scores and gives the place in the ring to the next bin
     uint32_t ln = threadIdx.x & 63;
     asm volatile("" : "+v"(ln));      // its addresses are made here, not kept over the chunks
-    atomicMax(&lbest[slot][0][ln], best & 0xffffu);
-    atomicMax(&lbest[slot][1][ln], best >> 16);
+    if constexpr (!kMode) {
+      atomicMax(&lbest[slot][0][ln], best & 0xffffu);
+      atomicMax(&lbest[slot][1][ln], best >> 16);
+    }
     int fin = 0;
     if (lane == 0)
       fin = __hip_atomic_fetch_add(&lfin[slot], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__builtin_amdgcn_readfirstlane(fin) == S - 1) {
       const int64_t slot0 = bin.slot0 + 2 * ln;
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
+      for (int half = 0; half < (kMode ? 0 : 2); ++half) {
         const uint32_t top = lbest[slot][half][ln];
         lbest[slot][half][ln] = 0;
         const int sid = a.slot_seq[slot0 + half];
@@ -298,33 +397,46 @@ __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
   }
 }
 
-template <int R, int W, bool kDrift>
+template <int R, int W, int kForm>
 hipError_t launch_rwd(const InterArgs& a, int n_cus, hipStream_t s) {
   // one workgroup for every place on the device, at most one per bin
   static const int per_cu = [] {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &n, reinterpret_cast<const void*>(&k_inter<R, W, kDrift>), 64 * W, 0) != hipSuccess) {
+            &n, reinterpret_cast<const void*>(&k_inter<R, W, kForm>), 64 * W, 0) != hipSuccess) {
       (void)hipGetLastError();
       n = 1;
     }
     return n > 0 ? n : 1;
   }();
   const int grid = (int)std::min<int64_t>(a.n_bins, (int64_t)n_cus * per_cu);
-  hipLaunchKernelGGL((k_inter<R, W, kDrift>), dim3(grid), dim3(64 * W), 0, s, a);
+  hipLaunchKernelGGL((k_inter<R, W, kForm>), dim3(grid), dim3(64 * W), 0, s, a);
   return hipGetLastError();
 }
 
 template <int R, int W>
 hipError_t launch_rw(const InterArgs& a, int n_cus, hipStream_t s) {
-  return a.drift.group > 0 ? launch_rwd<R, W, true>(a, n_cus, s)
-                           : launch_rwd<R, W, false>(a, n_cus, s);
+  return a.drift.group > 0 ? launch_rwd<R, W, kCellDrift>(a, n_cus, s)
+                           : launch_rwd<R, W, kCellHalf>(a, n_cus, s);
+}
+
+template <int R, int W>
+hipError_t launch_mode_rw(const InterArgs& a, int n_cus, hipStream_t s) {
+  return a.mode.mode == SW_MODE_GLOBAL ? launch_rwd<R, W, kCellGlobal>(a, n_cus, s)
+                                       : launch_rwd<R, W, kCellSemi>(a, n_cus, s);
 }
 
 }  // namespace
 
 hipError_t launch_inter(int R, int W, int n_cus, const InterArgs& a, hipStream_t s) {
   if (a.n_bins <= 0) return hipSuccess;
+  if (a.mode.mode != SW_MODE_LOCAL) {
+#define SWDB_CASE(r, w) \
+  if (R == r && W == w) return launch_mode_rw<r, w>(a, n_cus, s);
+    SWDB_CASE(12, 16) SWDB_CASE(14, 16) SWDB_CASE(16, 16)
+#undef SWDB_CASE
+    return hipErrorInvalidValue;
+  }
 #define SWDB_CASE(r, w) \
   if (R == r && W == w) return launch_rw<r, w>(a, n_cus, s);
   SWDB_CASE(16, 1) SWDB_CASE(16, 2) SWDB_CASE(16, 4) SWDB_CASE(16, 8) SWDB_CASE(16, 12)

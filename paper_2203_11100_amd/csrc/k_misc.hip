@@ -20,7 +20,7 @@ __device__ __forceinline__ int profile_score(const uint8_t* __restrict__ q, int 
 // get kPadScore.  Thread 0 also clears the rescoring list's count.
 __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
                           uint32_t* __restrict__ prof, int m_pad, int R, int drift,
-                          int8_t* __restrict__ prof2, uint32_t* __restrict__ prof3, int m_pad2,
+                          int top, int top_score, int8_t* __restrict__ prof2, uint32_t* __restrict__ prof3, int m_pad2,
                           int32_t* __restrict__ flag_count) {
   const int64_t n1 = (int64_t)(m_pad / R) * prof_strip_dwords(R);
   const int64_t n2 = (int64_t)kIntraCodes * m_pad2;
@@ -36,7 +36,7 @@ __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
       const int pair = (int)(pr % (R / 2));
       const int64_t st = pr / (R / 2);
       const int i = (int)(st >> 1) * R + 2 * pair + (rem & 1), c = rem >> 1;
-      const int sc = profile_score(q, m, mat, i, c);
+      const int sc = i < top ? top_score : profile_score(q, m, mat, i - top, c);
       if (drift >= 0) {
         const uint32_t v = (uint32_t)(sc + 2 * drift);
         prof[idx] = (st & 1) ? v << 16 : v;
@@ -120,7 +120,7 @@ __global__ void k_fill(int32_t* __restrict__ p, int64_t n, int32_t v) {
 }  // namespace
 
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
-                          int m_pad, int R, int drift, int8_t* prof2, uint32_t* prof3, int m_pad2,
+                          int m_pad, int R, int drift, int top, int top_score, int8_t* prof2, uint32_t* prof3, int m_pad2,
                           int32_t* flag_count, hipStream_t s) {
   if (R <= 0 || R % 2 != 0 || m_pad % R != 0) return hipErrorInvalidValue;
   const int64_t total = (int64_t)(m_pad / R) * prof_strip_dwords(R) +
@@ -129,7 +129,7 @@ hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint
   int grid = (int)std::min<int64_t>((total + 255) / 256, 2048);
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(k_profile, dim3(grid), dim3(256), 0, s, d_query, m, mat, prof, m_pad, R,
-                     drift, prof2, prof3, m_pad2, flag_count);
+                     drift, top, top_score, prof2, prof3, m_pad2, flag_count);
   return hipGetLastError();
 }
 

@@ -196,6 +196,10 @@ __device__ __forceinline__ void sweep_chunk_ahead(uint32_t (&H)[R], uint32_t (&E
 // (min(m, columns) * max S fits, the usual case), or `guard` sets the state of
 // such a half back to Z at the end of every chunk.
 //
+// Global and semi-global scores (k_inter.hip) have no floor; their values stay
+// above base because a gap along a border costs its opening only, so `base` is
+// 3 go + 256 for them, and below it plus a bounded gain (mode_plan).
+//
 // The running maximum is of H = H~ - Z.  All cells of an anti-diagonal have
 // the same Z, so A[k] carries the maximum of the anti-diagonal through row k
 // of the last odd column: at odd columns A[k] = max(A[k + 2], the cell, the
@@ -207,7 +211,10 @@ constexpr int kDriftTop = 31743;      // the largest value the maxima order as i
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 as_u2(uint32_t a) { return __builtin_bit_cast(u16x2, a); }
 __device__ __forceinline__ uint32_t from_u2(u16x2 a) { return __builtin_bit_cast(uint32_t, a); }
-// per half: max(a, b), min(a, b), max(a - b, 0)
+// per half: a * b, max(a, b), min(a, b), max(a - b, 0)
+__device__ __forceinline__ uint32_t umul2(uint32_t a, uint32_t b) {
+  return from_u2(as_u2(a) * as_u2(b));
+}
 __device__ __forceinline__ uint32_t umax2(uint32_t a, uint32_t b) {
   return from_u2(__builtin_elementwise_max(as_u2(a), as_u2(b)));
 }
@@ -276,7 +283,9 @@ __device__ __forceinline__ void drift_finish(const uint32_t (&A)[R], uint32_t& b
 // between dependent packed ops from the next pairs (6 instead of 60 a chunk at
 // 14 rows) for registers that are not there, 20 rows spilling 25 of them, and
 // 1-3 % of the time.
-template <int R, bool kSplit, class ProfPair, class Emit>
+// Without kLocal (global and semi-global scores) there is no floor and no
+// running maximum: 5 ops, and A, best and the Z are not used.
+template <int R, bool kSplit, bool kLocal, class ProfPair, class Emit>
 __device__ __forceinline__ void drift_chunk(uint32_t (&H)[R], uint32_t (&E)[R], uint32_t (&A)[R],
                                             uint32_t& hdiag, const uint32_t (&up_h)[4],
                                             const uint32_t (&up_f)[4], uint32_t& best,
@@ -310,15 +319,15 @@ __device__ __forceinline__ void drift_chunk(uint32_t (&H)[R], uint32_t (&E)[R], 
         const uint32_t d = kSplit ? hd + pa + pb : hd + pa;
         const uint32_t h = hmax3(d, E[k], F);
         const uint32_t t = h - cv;
-        if (k == 0 && !(jj & 1)) x = umax2(A[1], h) - z;
-        if (jj & 1) {
+        if (kLocal && k == 0 && !(jj & 1)) x = umax2(A[1], h) - z;
+        if (kLocal && (jj & 1)) {
           if (k + 2 < R) A[k] = hmax3(A[k + 2], h, H[k + 1]);
           else if (k + 1 < R) A[k] = umax2(h, H[k + 1]);
           else A[k] = h;
           if (k == 0) best = hmax3(best, x, A[0] - z);
         }
         z += ge2;
-        E[k] = hmax3(E[k], t, z);
+        E[k] = kLocal ? hmax3(E[k], t, z) : umax2(E[k], t);
         F = umax2(F, t);
         hd = H[k];
         H[k] = h;

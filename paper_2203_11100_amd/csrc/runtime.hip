@@ -722,6 +722,7 @@ constexpr double kInterRate = 7.0e12;
 constexpr double kPairRate = 4.5e12;
 constexpr double kBinRate = 3.0e10;
 constexpr double kPairShare = 5.0;
+constexpr double kLongModeRate = 1.2e12;   // int32 wavefront kernel, global and semi-global
 
 // How many of the longest short bins a query of length m hands to the
 // long-pair kernel (RR query rows per lane).  A bin is 128 sequences on one
@@ -908,7 +909,8 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   const DriftArgs drift =
       drift_plan(m, db->d->plan.max_bin_len, R, mat, go, ge, db->sat_limit);
   const int t_total = time_begin(db, kTimeTotal, s);
-  if ((e = launch_profile(d_query, m, mat, X.prof, sh.m_pad, R, drift.group > 0 ? ge : -1, X.prof2,
+  if ((e = launch_profile(d_query, m, mat, X.prof, sh.m_pad, R, drift.group > 0 ? ge : -1, 0, 0,
+                          X.prof2,
                           pairs ? X.prof3 : nullptr, m_pad2, X.flags, s)) != hipSuccess)
     return hip_fail(e, "profile kernel");
   if (pairs && (e = hipEventRecord(db->ev_fork, s)) != hipSuccess) return hip_fail(e, "event");
@@ -1152,9 +1154,49 @@ int64_t mode_bound(const Searcher* db, int64_t m, int64_t go, int64_t ge) {
   return go + (ge + 128) * (m + 512 + (int64_t)db->d->plan.max_len + 1024);
 }
 
-// Global / semi-global search of one query: the int32 inter-task kernel over
-// the short bins and the int32 wavefront kernel over the long list, on the
-// auxiliary stream beside it.
+// A global or semi-global search's inter-task form: the packed drift kernel
+// (k_inter.hip) where every value stays within 16 bits, else R = 0 and the int32
+// kernel.  Values lie above base - 2 go (borders, and gaps from them) and below
+// base plus what the cells of a path can gain: max S + 2 ge for each of at most
+// min(rows, columns) matched pairs from the corner (global), or max S + ge from
+// anywhere on the top border, which itself rises to ge * columns (semi-global).
+// BLOSUM62 with gaps 10/2 fits for every query up to 2,047 columns.
+struct ModePlan {
+  int R = 0, W = 0, n_strips = 0;
+  ModeShape shape{};
+};
+ModePlan mode_plan(int m, int64_t cols, const Matrix& mat, int64_t go, int64_t ge, int mode) {
+  ModePlan p;
+  const int64_t max_s = max_score(mat);
+  // padded rows over relative rate, as for batches
+  static const Sched forms[] = {{16, 16, 1.0}, {14, 16, 0.98}, {12, 16, 0.95}};
+  double best = 1e300;
+  for (const Sched& c : forms) {
+    const double cost = (double)((m + c.R - 1) / c.R * c.R) / c.eff;
+    if (cost < best) { best = cost; p.R = c.R; p.W = c.W; }
+  }
+  p.n_strips = (m + p.R - 1) / p.R;
+  const int64_t rows = (int64_t)p.n_strips * p.R;
+  const int64_t base = 3 * go + 256;
+  const int64_t pairs = std::min<int64_t>(rows, cols);
+  const int64_t gain = mode == SW_MODE_GLOBAL ? pairs * (max_s + 2 * ge)
+                                              : pairs * (max_s + ge) + ge * cols;
+  if (base + ge * p.R + gain + 512 > kDriftTop || cols > kDriftTop) {
+    p.R = 0;
+    return p;
+  }
+  p.shape.mode = mode;
+  p.shape.pad = (int32_t)(rows - m);
+  p.shape.base = (int32_t)base;
+  p.shape.go = (int32_t)go;
+  p.shape.ge = (int32_t)ge;
+  p.shape.m = m;
+  return p;
+}
+
+// Global / semi-global search of one query: the packed inter-task kernel over
+// the short bins (the int32 one where 16 bits do not hold it) beside the int32
+// wavefront kernel over the long list, which starts first, as in a local search.
 int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const Matrix& mat,
                         int32_t go, int32_t ge, int mode, int32_t* d_out, hipStream_t s) {
   hipError_t e;
@@ -1166,33 +1208,56 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
       return hip_fail(e, "empty-query kernel");
     return SW_OK;
   }
-  // 32 rows per strip, 16 for queries of at most 16 residues: each strip
-  // pays its boundary row and profile staging, so taller strips win even
-  // with padding (144 residues: 5 strips of 32 beat 9 of 16; 16-row strips
-  // for every query ran at 1,108 GCUPS against 1,740 with 32)
-  const int R = m <= 16 ? 16 : 32;
-  const int n_strips = (m + R - 1) / R;
+  const ModePlan mp = mode_plan(m, P.max_bin_len, mat, go, ge, mode);
+  // the int32 kernel: 32 rows per strip, 16 for queries of at most 16 residues
+  // (each strip pays its boundary row and profile staging, so taller strips win
+  // even with padding; 16-row strips for every query ran at 1,108 GCUPS against
+  // 1,740 with 32)
+  const int R32 = m <= 16 ? 16 : 32;
+  const int n_strips32 = (m + R32 - 1) / R32;
   const int m_pad2 = intra_rows_pad(m);
-  const int64_t short_dwords = P.n_bins < P.n_bins + P.n_long_bins ? P.bins[4 * P.n_bins]
-                                                                  : P.packed_dwords;
-  if ((e = db->mprof.reserve((size_t)n_strips * kProfRowDwords * R)) != hipSuccess ||
-      (e = db->prof2.reserve((size_t)kIntraCodes * m_pad2)) != hipSuccess ||
-      (e = db->rb_mode.reserve((size_t)std::max<int64_t>(4 * short_dwords, 1))) != hipSuccess)
-    return fail(SW_ENOMEM, std::string("mode search scratch: ") + hipGetErrorString(e));
-  const int t_total = time_begin(db, kTimeTotal, s);
-  if ((e = launch_mode_profile(d_query, m, mat, R, n_strips, db->mprof.p, db->prof2.p, m_pad2,
-                               s)) != hipSuccess)
-    return hip_fail(e, "profile kernel");
   const int64_t n_long = P.n_long;
+  if ((e = db->prof2.reserve((size_t)kIntraCodes * m_pad2)) != hipSuccess)
+    return fail(SW_ENOMEM, std::string("mode search scratch: ") + hipGetErrorString(e));
+  if (mp.R > 0) {
+    if ((e = db->prof.reserve((size_t)mp.n_strips * prof_strip_dwords(mp.R) + kProfSlack)) !=
+        hipSuccess)
+      return fail(SW_ENOMEM, std::string("mode search scratch: ") + hipGetErrorString(e));
+  } else {
+    const int64_t short_dwords = P.n_bins < P.n_bins + P.n_long_bins ? P.bins[4 * P.n_bins]
+                                                                    : P.packed_dwords;
+    if ((e = db->mprof.reserve((size_t)n_strips32 * kProfRowDwords * R32)) != hipSuccess ||
+        (e = db->rb_mode.reserve((size_t)std::max<int64_t>(4 * short_dwords, 1))) != hipSuccess)
+      return fail(SW_ENOMEM, std::string("mode search scratch: ") + hipGetErrorString(e));
+  }
+  const int t_total = time_begin(db, kTimeTotal, s);
+  if (mp.R > 0) {
+    e = launch_profile(d_query, m, mat, db->prof.p, mp.n_strips * mp.R, mp.R, ge, mp.shape.pad,
+                       mode == SW_MODE_GLOBAL ? -2 * ge : 0, db->prof2.p, nullptr, m_pad2,
+                       db->flags.p, s);
+  } else {
+    e = launch_mode_profile(d_query, m, mat, R32, n_strips32, db->mprof.p, db->prof2.p, m_pad2, s);
+  }
+  if (e != hipSuccess) return hip_fail(e, "profile kernel");
+  hipStream_t bs = s;
   if (n_long > 0) {
-    if ((e = hipEventRecord(db->ev_fork, s)) != hipSuccess) return hip_fail(e, "event");
-    if ((e = hipStreamWaitEvent(db->aux_stream, db->ev_fork, 0)) != hipSuccess)
-      return hip_fail(e, "stream wait");
+    bs = db->aux_stream;
+    if ((e = hipEventRecord(db->ev_fork, s)) != hipSuccess ||
+        (e = hipStreamWaitEvent(bs, db->ev_fork, 0)) != hipSuccess)
+      return hip_fail(e, "stream fork");
     int RR = 8, W2 = 1;
     pick_intra(db, m, 8, &RR, &W2);
-    const int grid = (int)std::min<int64_t>(n_long, kIntraGridLong);
+    int grid = (int)std::min<int64_t>(n_long, kIntraGridLong);
     if ((e = reserve_long_scratch(db, grid)) != hipSuccess)
       return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
+    // beside the persistent packed kernel a share of the CUs, as the long pairs
+    // of a local search
+    if (mp.R > 0 && P.n_bins > 0) {
+      const double t_long = (double)db->d->long_residues / kLongModeRate;
+      const double t_inter = (double)(db->d->n_res - db->d->long_residues) / kInterRate;
+      grid = std::min<int>(grid, (int)(kPairShare * t_long / (t_long + t_inter) * db->d->n_cus *
+                                       4 / W2) + 1);
+    }
     IntraArgs la{};
     la.res = db->d->res.p;
     la.offs = db->d->offs.p;
@@ -1208,34 +1273,53 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
     la.out = d_out;
     la.mode = mode;
     la.m = m;
-    const int tl = time_begin(db, kTimeIntra, db->aux_stream);
-    if ((e = launch_intra(RR, W2, grid, la, db->aux_stream)) != hipSuccess)
+    const int tl = time_begin(db, kTimeIntra, s);
+    if ((e = launch_intra(RR, W2, grid, la, s)) != hipSuccess)
       return hip_fail(e, "intra-task kernel");
-    time_end(db, tl, db->aux_stream);
-    if ((e = hipEventRecord(db->ev_join, db->aux_stream)) != hipSuccess)
-      return hip_fail(e, "event");
+    time_end(db, tl, s);
   }
   if (P.n_bins > 0) {
-    ModeArgs a{};
-    a.res = db->d->packed.p;
-    a.bins = db->d->bins.p;
-    a.slot_seq = db->d->slot_seq.p;
-    a.offs = db->d->offs.p;
-    a.n_halfbins = (int32_t)(2 * P.n_bins);
-    a.n_strips = n_strips;
-    a.m = m;
-    a.go = go;
-    a.ge = ge;
-    a.prof = db->mprof.p;
-    a.rb = db->rb_mode.p;
-    a.out = d_out;
-    const int ti = time_begin(db, kTimeInter, s);
-    if ((e = launch_mode_inter(R, mode, a, s)) != hipSuccess)
-      return hip_fail(e, "inter-task mode kernel");
-    time_end(db, ti, s);
+    const int ti = time_begin(db, kTimeInter, bs);
+    if (mp.R > 0) {
+      InterArgs a{};
+      a.res2 = reinterpret_cast<const uint2*>(db->d->packed.p);
+      a.bins = db->d->bins.p;
+      a.n_bins = (int32_t)P.n_bins;
+      a.counter = db->flags.p + 1;     // cleared by the profile kernel
+      a.n_strips = mp.n_strips;
+      a.prof = db->prof.p;
+      a.rb = db->rb.p;
+      a.slot_seq = db->d->slot_seq.p;
+      a.out = d_out;
+      auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
+      a.drift.group = 1;
+      a.drift.c2 = both(go - ge);
+      a.drift.ge2 = both(ge);
+      a.mode = mp.shape;
+      a.mode.offs = db->d->offs.p;
+      e = launch_inter(mp.R, mp.W, db->d->n_cus, a, bs);
+    } else {
+      ModeArgs a{};
+      a.res = db->d->packed.p;
+      a.bins = db->d->bins.p;
+      a.slot_seq = db->d->slot_seq.p;
+      a.offs = db->d->offs.p;
+      a.n_halfbins = (int32_t)(2 * P.n_bins);
+      a.n_strips = n_strips32;
+      a.m = m;
+      a.go = go;
+      a.ge = ge;
+      a.prof = db->mprof.p;
+      a.rb = db->rb_mode.p;
+      a.out = d_out;
+      e = launch_mode_inter(R32, mode, a, bs);
+    }
+    if (e != hipSuccess) return hip_fail(e, "inter-task mode kernel");
+    time_end(db, ti, bs);
   }
-  if (n_long > 0 && (e = hipStreamWaitEvent(s, db->ev_join, 0)) != hipSuccess)
-    return hip_fail(e, "stream wait");
+  if (n_long > 0 && ((e = hipEventRecord(db->ev_join, bs)) != hipSuccess ||
+                     (e = hipStreamWaitEvent(s, db->ev_join, 0)) != hipSuccess))
+    return hip_fail(e, "stream join");
   time_end(db, t_total, s);
   db->stats.inter_cells += (int64_t)m * (db->d->n_res - db->d->long_residues);
   db->stats.intra_cells += (int64_t)m * db->d->long_residues;

@@ -111,3 +111,26 @@ def test_batches(sw, go, ge, matrix, lens):
         want = ocpu.search(q, res, offs, mat, go, ge)
         bad = np.nonzero(row != want)[0]
         assert len(bad) == 0, [(int(i), int(row[i]), int(want[i])) for i in bad[:5]]
+
+
+# global and semi-global: the packed form and, past its 16-bit range, the int32
+# one; queries that fill their strips and that leave rows above them
+@pytest.mark.parametrize("m", [1, 16, 42, 97, 640, 2300])
+@pytest.mark.parametrize("go,ge,matrix", [(10, 2, "b62"), (0, 0, "b62"), (11, 1, "b62"),
+                                          (40, 10, "b62"), (3000, 3, "b62"), (9000, 5, "b62"),
+                                          (100000, 7, "b62"), (12, 2, "hot")])
+def test_modes(sw, m, go, ge, matrix):
+    res, offs, rng = _db(m + go, 2047)
+    q = swinputs.random_residues(m, rng)
+    sizes = np.diff(offs)
+    for i in np.argsort(sizes)[-20::2]:
+        n = int(sizes[i])
+        res[offs[i]:offs[i] + n] = np.resize(q, n)
+    mat = _hot() if matrix == "hot" else B62
+    say("modes m=%d gaps %d/%d %s" % (m, go, ge, matrix))
+    with sw.Database(res, offs) as db:
+        for mode in ("global", "semiglobal"):
+            got = db.search_mode(q, mat, go, ge, mode)
+            want = ocpu.search_mode(q, res, offs, mat, go, ge, mode)
+            bad = np.nonzero(got != want)[0]
+            assert len(bad) == 0, (mode, [(int(i), int(got[i]), int(want[i])) for i in bad[:5]])
