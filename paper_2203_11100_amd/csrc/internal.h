@@ -64,6 +64,10 @@ static_assert(half_bits(1) == 0x3c00 && half_bits(-64) == 0xd400 && half_bits(20
 
 // The parameters of a drift sweep (packed16.h), the same in both halves of
 // each word; group = 0: the binary16 form is used instead.
+// Words before the rescoring list's entries: its count, the work counters of the
+// single search's bins and pairs, one spare.
+constexpr int kFlagWords = 4;
+
 struct DriftArgs {
   int32_t group;              // strips until the drift starts again at its base
   int32_t guard;              // values need the guard to stay in range
@@ -192,6 +196,41 @@ struct IntraPairArgs {
   const QueryDesc* queries;
 };
 
+// Long-pair kernel in the drift form (k_pairs.hip); items, segments and batches
+// as in IntraPairArgs.
+struct PairArgs {
+  const uint8_t* res;         // contiguous residues, original order
+  const int64_t* offs;
+  const int2* items;          // {sequence a, sequence b or -1}, a not shorter
+  int32_t count;
+  int32_t* counter;           // items taken, zero at launch
+  const uint8_t* prof;        // [25][m_pad2] bytes S + 2 ge + bias
+  int32_t m_pad2;
+  int32_t n_pass;             // passes of 64*R rows covering the query
+  int32_t shared;             // the profiles of all passes fit in LDS at once
+  uint32_t c2, ge2, bias2;    // gap_open - gap_extend (at most 2048), drift and bias, both halves
+  uint32_t lim2, over2;       // the rescoring limit; 32768 - the limit
+  int32_t sat_limit;
+  int32_t ring;               // pairs in flight per workgroup, 1 .. kRing
+  uint2* scratch;             // their boundary rows {H pair, F pair}, ring rows a workgroup
+  int64_t scratch_stride;     // uint2 per row
+  int32_t* out;
+  int32_t* flag_count;        // rescoring list: count, then {sid, query}
+  int2* flag_list;
+  const int2* seg_items;
+  int32_t seg_cols, seg_overlap;
+  uint32_t* seg_best;
+  const int2* batch_items;
+  const QueryDesc* queries;   // prof3_off in bytes
+};
+
+// LDS of one workgroup of the long-pair kernel: profiles (dynamic) and the rest.
+constexpr size_t kLdsBytes = 160 * 1024;
+constexpr size_t pairs_lds(int R, int W, int n_pass, bool shared) {
+  return (size_t)(shared ? n_pass : W) * kIntraCodes * 64 * R;
+}
+constexpr size_t pairs_lds_static(int W) { return (size_t)W * (1024 + 520 + 12) + 512; }
+
 // Batched inter-task kernel: the two 16-bit halves of a lane hold two
 // queries (a pair) against one database sequence.  The pair's profile has
 // the inter-task layout (rows in pairs, code-major within a pair) with the
@@ -246,20 +285,26 @@ static_assert(sizeof(TopkState) % 8 == 0, "TopkState keeps the arrays after it 8
 
 // Kernel launchers (return hipSuccess or the launch error).
 // drift: gap_extend of the drift form or -1; top: rows above the query's first,
-// of the score top_score against every code
+// of the score top_score against every code; pair_add: prof3 holds the bytes
+// S + pair_add of the long-pair kernel, or (-1) binary16 row pairs
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
-                          int m_pad, int R, int drift, int top, int top_score, int8_t* prof2, uint32_t* prof3, int m_pad2,
-                          int32_t* flag_count, hipStream_t s);
+                          int m_pad, int R, int drift, int top, int top_score, int8_t* prof2,
+                          uint32_t* prof3, int pair_add, int m_pad2, int32_t* flag_count,
+                          hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_inter(int R, int W, int n_cus, const InterArgs& a, hipStream_t s);
 hipError_t launch_intra(int RR, int W2, int grid, const IntraArgs& a, hipStream_t s);
 // R in {2, 4, 8}, W2 in {1, 2, 4, 8}, not (8, 8) (LDS)
 hipError_t launch_intra_pairs(int R, int W2, int grid, const IntraPairArgs& a, hipStream_t s);
+// The same in the drift form: R in {2, 4, 8}, W in {1, 2, 4, 8, 16}, LDS as above.
+hipError_t launch_pairs(int R, int W, int grid, const PairArgs& a, hipStream_t s);
 // Scores of segmented pairs: pair p's maximum over seg_best[seg0[p] ..
-// seg0[p+1]), written to out (or the rescoring list) per half.
+// seg0[p+1]), written to out (or the rescoring list) per half; drift: integers,
+// else binary16.
 hipError_t launch_long_combine(const int2* pairs, const int32_t* seg0, int32_t n_pairs,
                                const uint32_t* seg_best, int32_t sat_limit, int32_t* out,
-                               int32_t* flag_count, int2* flag_list, hipStream_t s);
+                               int32_t* flag_count, int2* flag_list, bool drift,
+                               hipStream_t s);
 hipError_t launch_batch(int R, int W, int grid, const BatchArgs& a, hipStream_t s);
 int batch_workgroups_per_cu(int R, int W);
 hipError_t launch_mode_profile(const uint8_t* d_query, int m, const Matrix& mat, int R,
@@ -287,6 +332,6 @@ hipError_t launch_hit_combine(const int2* items, int32_t k, const int32_t* seg0,
 hipError_t launch_batch_profiles(const uint8_t* d_queries, const int64_t* d_qoffs, int n_queries,
                                  const Matrix& mat, const PairDesc* d_pairs, int n_pairs, int R,
                                  int drift, int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
-                                 int8_t* prof2, uint32_t* prof3, hipStream_t s);
+                                 int8_t* prof2, uint32_t* prof3, int pair_add, hipStream_t s);
 
 }  // namespace swdb

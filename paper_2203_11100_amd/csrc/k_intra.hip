@@ -612,17 +612,17 @@ __global__ __launch_bounds__(64 * W2) void k_intra_f16(IntraPairArgs a) {
 __global__ void k_long_combine(const int2* __restrict__ pairs, const int32_t* __restrict__ seg0,
                                int32_t n_pairs, const uint32_t* __restrict__ seg_best,
                                int32_t sat_limit, int32_t* __restrict__ out,
-                               int32_t* flag_count, int2* __restrict__ flag_list) {
+                               int32_t* flag_count, int2* __restrict__ flag_list, int drift) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n_pairs) return;
-  uint32_t b = 0;
-  for (int x = seg0[p]; x < seg0[p + 1]; ++x) b = hmax2(b, seg_best[x]);
+  uint32_t b = 0;     // (no NaN in either form: both patterns order as integers)
+  for (int x = seg0[p]; x < seg0[p + 1]; ++x) b = umax2(b, seg_best[x]);
   const int2 item = pairs[p];
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     const int sid = half ? item.y : item.x;
     if (sid < 0) continue;
-    const int score = half_score(b, half, sat_limit);
+    const int score = drift ? drift_score(b, half, sat_limit) : half_score(b, half, sat_limit);
     if (score < 0) {
       const int idx = atomicAdd(flag_count, 1);
       flag_list[idx] = make_int2(sid, 0);
@@ -669,10 +669,11 @@ hipError_t launch_intra(int R, int W2, int grid, const IntraArgs& a, hipStream_t
 
 hipError_t launch_long_combine(const int2* pairs, const int32_t* seg0, int32_t n_pairs,
                                const uint32_t* seg_best, int32_t sat_limit, int32_t* out,
-                               int32_t* flag_count, int2* flag_list, hipStream_t s) {
+                               int32_t* flag_count, int2* flag_list, bool drift,
+                               hipStream_t s) {
   if (n_pairs <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_long_combine, dim3((n_pairs + 255) / 256), dim3(256), 0, s, pairs, seg0,
-                     n_pairs, seg_best, sat_limit, out, flag_count, flag_list);
+                     n_pairs, seg_best, sat_limit, out, flag_count, flag_list, drift ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 #include "internal.h"
 #include "layout.h"
 #include "packed16.h"
+#include "stream.h"
 
 namespace swdb {
 namespace {
@@ -128,6 +129,7 @@ struct BatchPlan {
   int64_t inter_cells = 0, intra_cells = 0;
   int grid_b = 0, grid_long = 0;
   swdb::DriftArgs drift{};
+  int pair_add = -1, pair_bias = 0;   // the long-pair kernel's form (pair_form)
   std::vector<int32_t> zero_queries;
   swdb::DevBuf<swdb::PairDesc> pairs;
   swdb::DevBuf<swdb::QueryDesc> qdesc;
@@ -407,7 +409,7 @@ int init_searcher(Searcher* S, DbData* d) {
       (e = S->rb_resc.reserve((size_t)kIntraGridRescore * (size_t)rescore_stride(P))) !=
           hipSuccess ||
       (e = S->flags.reserve(
-           (size_t)(2 + 2 * std::max<int64_t>(P.n_bins * SW_BIN_SEQS + P.n_long, 1)))) !=
+           (size_t)(kFlagWords + 2 * std::max<int64_t>(P.n_bins * SW_BIN_SEQS + P.n_long, 1)))) !=
           hipSuccess ||
       (e = S->seg_best.reserve((size_t)std::max<int64_t>(d->n_seg_items, 1))) != hipSuccess)
     return fail(SW_ENOMEM, std::string("search scratch: ") + hipGetErrorString(e));
@@ -586,12 +588,12 @@ void time_end(Searcher* db, int idx, hipStream_t s) {
 }
 
 // The rescoring list: flags[0] is the count, {sid, query} pairs start at
-// flags + 2 (8-byte aligned); flags[1] counts the bins taken by a single
-// search's inter-task kernel.
-int2* flag_list(Searcher* db) { return reinterpret_cast<int2*>(db->flags.p + 2); }
+// flags + kFlagWords (8-byte aligned); flags[1] and [2] count the bins and pairs
+// taken by a single search's kernels.
+int2* flag_list(Searcher* db) { return reinterpret_cast<int2*>(db->flags.p + kFlagWords); }
 
 hipError_t reserve_flags(Searcher* db, int64_t entries) {
-  return db->flags.reserve((size_t)(2 + 2 * std::max<int64_t>(entries, 1)));
+  return db->flags.reserve((size_t)(kFlagWords + 2 * std::max<int64_t>(entries, 1)));
 }
 
 hipError_t reserve_long_scratch(Searcher* db, int grid) {
@@ -706,11 +708,36 @@ int32_t hit_overlap(const DbData& d, int m, const Matrix& mat, int32_t ge) {
   return (int64_t)d.plan.max_len > (int64_t)d.seg_cols + reach ? (int32_t)reach : -1;
 }
 
+// The long-pair kernel's drift form (k_pairs.hip) for one set of scores: `add`
+// is what its profile bytes hold beside S (2 ge + bias), -1 where the form does
+// not fit - the drift of a superstep and two supersteps' gain past the limit
+// within the 16-bit range, scores within a byte - and k_intra_f16 is used.
+struct PairForm {
+  int add = -1, bias = 0;
+};
+PairForm pair_form(const Matrix& mat, int32_t ge, int32_t sat_limit) {
+  PairForm f;
+  int lo = 0, hi = 0;
+  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) {
+    lo = std::min<int>(lo, mat.v[x]);
+    hi = std::max<int>(hi, mat.v[x]);
+  }
+  const int64_t top = (int64_t)kDriftBase + effective_limit(sat_limit) + 140 * (int64_t)hi +
+                      (int64_t)ge * (64 + 2 * 8 + 8) + 512;
+  const int bias = std::max(0, -(lo + 2 * std::min(ge, 1024)));
+  if (top > kDriftTop || hi + 2 * (int64_t)ge + bias > 255) return f;
+  f.bias = bias;
+  f.add = 2 * ge + bias;
+  return f;
+}
+
 // Schedule of one single-query search: inter-task strips (R rows, W waves),
-// the packed long-sequence kernel (RR, W2), the rescoring kernel (RRr, W2r)
-// and the intra-task profiles' row length.
+// the packed long-pair kernel (RR, W2; `pair` its form), the rescoring kernel
+// (RRr, W2r) and the intra-task profiles' row length.
 struct SearchShape {
   int R, W, m_pad, n_strips, RR, W2, RRr, W2r, m_pad2;
+  PairForm pair;
+  int32_t overlap;            // column segments' reach (seg_overlap), -1: whole pairs
   int64_t off_bins;   // the longest short bins handed to the long-pair kernel
 };
 
@@ -771,7 +798,47 @@ int64_t pair_stride(const DbData& d) {
   return std::max<int64_t>({(int64_t)d.plan.max_long_len, (int64_t)d.plan.max_short_len, 1});
 }
 
-SearchShape search_shape(const Searcher* db, int m) {
+// Rows per lane and waves per workgroup of the drift long-pair kernel, for pairs
+// of `cols` columns together, the longest `longest`, beside `inter` cells of the
+// inter-task kernel.  In cycles, measured: a step of R rows takes `lat` in a wave
+// alone on its SIMD and `thr` of the SIMD's issue where several waves share it.
+// The longest pair is a chain of its steps (two supersteps more for every
+// further pass), in rounds when its passes outnumber the waves; the rows that
+// give the shorter of chain and work win, the cheaper work where that is close
+// (977 residues against the plain database 7.3 ms with 2, 4 or 8 rows; the long
+// mix, 2,000 residues, 9.3 / 5.7 / 6.3).  Waves: 16 beside the inter-task kernel,
+// whose workgroups share a CU with no other, so that the pairs hold few CUs and
+// fill them (457 residues, 100,000 plain sequences: 2.97 ms with 4, 2.59 with
+// 16); alone as many as a pair has passes, 4 to 16, so that the pairs spread.
+void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double longest,
+                double inter, int* R_out, int* W_out) {
+  struct Cost { int R; double lat, thr; };
+  static const Cost costs[] = {{4, 276, 153}, {8, 412, 270}, {2, 250, 95}};
+  const double simds = 4.0 * std::max(db->d->n_cus, 1);
+  double best = 1e300;
+  for (const Cost& c : costs) {
+    if (db->opt_intra_rows && c.R != db->opt_intra_rows) continue;
+    const int P = (m + 64 * c.R - 1) / (64 * c.R);
+    int W = inter > 0 ? 16 : 1;
+    while (W < 16 && (W < P || (double)W * std::max(db->d->n_cus, 1) < n_pairs * P)) W *= 2;
+    if (db->opt_intra_waves) W = db->opt_intra_waves;
+    auto fits = [&](int w) {
+      return std::min(pairs_lds(c.R, w, P, true), pairs_lds(c.R, w, P, false)) +
+                 pairs_lds_static(w) <= kLdsBytes;
+    };
+    while (W > 1 && !fits(W)) W /= 2;
+    const int at_once = std::min(P, W);
+    const double chain = (longest + 128.0 * (at_once - 1)) * ((P + W - 1) / W) *
+                         std::max(c.lat, std::max(1.0, at_once / 4.0) * c.thr);
+    const double work = cols * P * c.thr / simds / 0.85;
+    const double all = work + inter / 128.0 * 27.0 / simds;
+    const double est = std::max(chain, all) + 0.1 * chain + 0.5 * work;
+    if (est < best) { best = est; *R_out = c.R; *W_out = W; }
+  }
+}
+
+SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t ge) {
+  const DbData& D = *db->d;
   SearchShape sh{};
   sh.R = kDefaultRows;
   sh.W = kDefaultWaves;
@@ -779,26 +846,74 @@ SearchShape search_shape(const Searcher* db, int m) {
   sh.m_pad = (m + sh.R - 1) / sh.R * sh.R;
   sh.n_strips = sh.m_pad / sh.R;
   sh.RR = 8; sh.W2 = 1; sh.RRr = 8; sh.W2r = 1;
-  pick_intra(db, m, 8, &sh.RR, &sh.W2, true);   // long sequences, in pairs (binary16)
+  sh.overlap = D.plan.n_long > 0 ? seg_overlap(D, m, mat, ge) : -1;
+  sh.pair = pair_form(mat, ge, db->sat_limit);
+  const int b = tune_bucket(m);
+  if (sh.pair.add < 0) {
+    pick_intra(db, m, 8, &sh.RR, &sh.W2, true);   // long sequences, in pairs (binary16)
+  } else if (db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves) {
+    sh.RR = db->tune_irows[b];
+    sh.W2 = db->tune_iwaves[b];
+  }
+  sh.off_bins = pick_offload(db, m, sh.pair.add < 0 ? sh.RR : 4);
+  if (sh.pair.add >= 0 && !(db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves)) {
+    const double off_res = sh.off_bins > 0 ? (double)D.bin_res_cum[(size_t)sh.off_bins] : 0.0;
+    const double off_pairs = sh.off_bins > 0 ? (double)D.bin_pair_end[(size_t)sh.off_bins - 1] : 0.0;
+    double n_items = (double)D.n_long_pairs, cols = 0.5 * (double)D.long_residues;
+    double longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
+    if (sh.overlap >= 0) {
+      n_items = (double)D.n_seg_items;
+      cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
+      longest = std::min<double>(longest, std::max<double>((double)D.seg_cols + sh.overlap,
+                                                          off_pairs > 0 ? D.plan.max_short_len : 0));
+    }
+    pick_pairs(db, m, n_items + off_pairs, cols + 0.5 * off_res, longest,
+               (double)m * ((double)(D.n_res - D.long_residues) - off_res), &sh.RR, &sh.W2);
+  }
   // exact rescoring (usually a few sequences, each the only one on its CU,
   // so the latency of one sequence is what counts)
   pick_intra(db, m, 8, &sh.RRr, &sh.W2r);
   // the intra-task profiles serve every intra-task launch of the query (long
   // list, rescoring, hit ends): pad to the largest pass, 64 x 8 rows
   sh.m_pad2 = intra_rows_pad(m);
-  sh.off_bins = pick_offload(db, m, sh.RR);
   return sh;
+}
+
+// Workgroups of a pair launch over `count` items of n_pass passes: enough waves
+// for all passes, at most what the device holds.  Beside the persistent
+// inter-task kernel (inter cells, pair rows * residues) the pairs take
+// kPairShare times their share of the search's work: too many workgroups hold up
+// the bins (the longest is the critical path of a short query), too few end after
+// them.
+int pair_grid(const Searcher* db, int64_t count, int n_pass, int W, double pair_cells,
+              double inter_cells) {
+  const double cus = std::max(db->d->n_cus, 1);
+  int64_t grid = std::min<int64_t>(count, (count * n_pass + W - 1) / W);
+  const int per_cu = std::max(1, 16 / W);
+  grid = std::min<int64_t>(grid, (int64_t)(cus * per_cu));
+  if (inter_cells > 0) {
+    const double tp = pair_cells / kPairRate, ti = inter_cells / kInterRate;
+    grid = std::min<int64_t>(grid, (int64_t)(kPairShare * tp / (tp + ti) * cus * 4 / W) + 1);
+  }
+  return (int)std::max<int64_t>(grid, 1);
+}
+
+// Pairs one workgroup holds at once: each keeps a row buffer when it has more
+// than one pass.
+int pair_ring(int n_pass, int W) {
+  return n_pass > 1 ? std::min(kRing, (W + n_pass - 1) / n_pass + 1) : kRing;
 }
 
 // Device scratch of one single-query search.
 struct SearchScratch {
   uint4* rb = nullptr;        // boundary rows of every short bin
-  int32_t* flags = nullptr;   // rescoring list: [0] count, {sid, query} pairs from +2;
-                              // [1] the bins' work counter
+  int32_t* flags = nullptr;   // rescoring list: [0] count, {sid, query} pairs from
+                              // +kFlagWords; [1], [2] work counters of bins and pairs
   uint32_t* prof = nullptr;   // inter-task strip profile
   int8_t* prof2 = nullptr;    // intra-task int8 profile
   uint32_t* prof3 = nullptr;  // packed intra-task profile (long list present)
   int2* rb_long = nullptr;    // per-workgroup rows of the long-sequence kernel
+  size_t long_words = 0;      // their size (drift form)
   int grid_long = 0;          // its workgroups over whole pairs
   int grid_seg = 0;           // and over column segments (rows of seg_stride)
   uint32_t* seg_best = nullptr;   // segment maxima (long list present)
@@ -816,7 +931,7 @@ ScratchSizes scratch_sizes(const Searcher* db, const SearchShape& sh, int grid_l
   const Plan& P = db->d->plan;
   ScratchSizes z{};
   z.rb = (size_t)std::max<int64_t>(P.boundary_uint4, 1);
-  z.flags = (size_t)(2 + 2 * std::max<int64_t>(P.n_bins * SW_BIN_SEQS + P.n_long, 1));
+  z.flags = (size_t)(kFlagWords + 2 * std::max<int64_t>(P.n_bins * SW_BIN_SEQS + P.n_long, 1));
   z.prof = (size_t)sh.n_strips * prof_strip_dwords(sh.R);
   z.prof2 = (size_t)kIntraCodes * sh.m_pad2;
   z.prof3 = P.n_long > 0 ? (size_t)kIntraCodes * (sh.m_pad2 / 2) : 0;
@@ -835,7 +950,7 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
                            const BinRunner* bins = nullptr);
 
 // The searcher's own scratch for a query of this shape, grown as needed.
-int reserve_search_scratch(Searcher* db, const SearchShape& sh, SearchScratch* X) {
+int reserve_search_scratch(Searcher* db, const SearchShape& sh, int m, SearchScratch* X) {
   hipError_t e;
   const int64_t n_long = db->d->plan.n_long;
   const int64_t off_pairs = sh.off_bins > 0 ? db->d->bin_pair_end[(size_t)sh.off_bins - 1] : 0;
@@ -853,10 +968,23 @@ int reserve_search_scratch(Searcher* db, const SearchShape& sh, SearchScratch* X
   if (n_long > 0 && off_pairs > 0 &&
       (e = db->seg_best.reserve((size_t)(db->d->n_seg_items + off_pairs))) != hipSuccess)
     return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
-  if (pairs && (e = db->rb_long.reserve(std::max<size_t>(
-                    {(size_t)std::max(grid_long, 1) * (size_t)pair_stride(*db->d),
-                     (size_t)grid_seg * (size_t)seg_stride(*db->d), 1}))) != hipSuccess)
-    return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
+  if (pairs) {
+    size_t words = std::max<size_t>(
+        {(size_t)std::max(grid_long, 1) * (size_t)pair_stride(*db->d),
+         (size_t)grid_seg * (size_t)seg_stride(*db->d), 1});
+    if (sh.pair.add >= 0) {
+      const int n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
+      const bool seg = sh.overlap >= 0;
+      const int64_t count = (seg ? db->d->n_seg_items : db->d->n_long_pairs) + off_pairs;
+      const int grid = std::min<int64_t>(count, (int64_t)db->d->n_cus * std::max(1, 16 / sh.W2));
+      words = n_pass > 1 ? (size_t)grid * pair_ring(n_pass, sh.W2) *
+                               (size_t)(seg ? seg_stride(*db->d) : pair_stride(*db->d))
+                         : 1;
+    }
+    if ((e = db->rb_long.reserve(words)) != hipSuccess)
+      return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
+    X->long_words = words;
+  }
   X->rb = db->rb.p;
   X->flags = db->flags.p;
   X->prof = db->prof.p;
@@ -879,9 +1007,9 @@ int enqueue_search(Searcher* db, const uint8_t* d_query, int32_t m, const Matrix
     e = launch_fill(d_out, db->d->n_seqs, 0, s);
     return e == hipSuccess ? SW_OK : hip_fail(e, "fill");
   }
-  const SearchShape sh = search_shape(db, m);
+  const SearchShape sh = search_shape(db, m, mat, ge);
   SearchScratch X;
-  const int rc = reserve_search_scratch(db, sh, &X);
+  const int rc = reserve_search_scratch(db, sh, m, &X);
   if (rc != SW_OK) return rc;
   return enqueue_search_kernels(db, sh, X, d_query, m, mat, go, ge, d_out, s);
 }
@@ -896,11 +1024,11 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   const int m_pad2 = sh.m_pad2;
   const int64_t n_long = db->d->plan.n_long;
   const int n_bins = (int)db->d->plan.n_bins;
-  int2* const flist = reinterpret_cast<int2*>(X.flags + 2);
+  int2* const flist = reinterpret_cast<int2*>(X.flags + kFlagWords);
   // short queries: the long pairs in column segments (seg_overlap), each
   // handed-over pair one segment; the longest short bins go to the pair
   // kernel as pairs (pick_offload; the bin runners' searches hand none over)
-  const int32_t overlap = n_long > 0 ? seg_overlap(*db->d, m, mat, ge) : -1;
+  const int32_t overlap = sh.overlap;
   const bool segmented = overlap >= 0 && X.seg_best && X.grid_seg > 0;
   const int off_bins = (int)std::min<int64_t>(std::max<int64_t>(sh.off_bins, 0), n_bins);
   const int64_t off_pairs = off_bins > 0 ? db->d->bin_pair_end[(size_t)off_bins - 1] : 0;
@@ -911,7 +1039,8 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   const int t_total = time_begin(db, kTimeTotal, s);
   if ((e = launch_profile(d_query, m, mat, X.prof, sh.m_pad, R, drift.group > 0 ? ge : -1, 0, 0,
                           X.prof2,
-                          pairs ? X.prof3 : nullptr, m_pad2, X.flags, s)) != hipSuccess)
+                          pairs ? X.prof3 : nullptr, sh.pair.add, m_pad2, X.flags, s)) !=
+      hipSuccess)
     return hip_fail(e, "profile kernel");
   if (pairs && (e = hipEventRecord(db->ev_fork, s)) != hipSuccess) return hip_fail(e, "event");
 
@@ -969,57 +1098,88 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   // stream beside the bins on the auxiliary one
   auto run_pairs = [&]() -> int {
     if (!pairs) return SW_OK;
-    IntraPairArgs la{};
-    la.res = db->d->res.p;
-    la.offs = db->d->offs.p;
-    la.items = db->d->d_long_pairs.p;
-    la.count = (int32_t)(db->d->n_long_pairs + off_pairs);
-    la.prof3 = X.prof3;
-    la.m_pad2 = m_pad2;
-    la.n_pass = (m + 64 * RR - 1) / (64 * RR);
-    la.go2 = half_pair(go);
-    la.ge2 = half_pair(ge);
-    la.sat_limit = effective_limit(db->sat_limit);
-    la.scratch = X.rb_long;
-    la.scratch_stride = pair_stride(*db->d);
-    la.out = d_out;
-    la.flag_count = X.flags;
-    la.flag_list = flist;
-    int grid = std::min<int>(X.grid_long, la.count);
-    if (segmented) {
-      la.seg_items = db->d->d_seg_items.p;
-      la.count = (int32_t)(db->d->n_seg_items + off_pairs);
-      la.seg_cols = db->d->seg_cols;
-      la.seg_overlap = overlap;
-      la.seg_best = X.seg_best;
-      la.scratch_stride = seg_stride(*db->d);
-      grid = std::min<int>(X.grid_seg, la.count);
-    }
-    // Beside the persistent inter-task kernel the pairs take kPairShare times
-    // their share of the search's work: too many workgroups hold up the bins
-    // (the longest is the critical path of a short query), too few end after
-    // them.  Measured on the plain database (ms, m = 144 / 977 / 5,478):
-    // share x 1.2 2.64 / 15.0 / 60.0, x 2.5 1.66 / 9.24 / 38.6, x 5 1.50 / 7.71 /
-    // 38.6.
-    if (n_bins > off_bins) {
-      const int64_t pass_rows = 64 * (int64_t)RR;
-      const double rows = (double)((m + pass_rows - 1) / pass_rows * pass_rows);
-      const double pair_res = (double)db->d->long_residues +
-                              (off_bins > 0 ? (double)db->d->bin_res_cum[(size_t)off_bins] : 0.0);
-      const double t_pair = rows * pair_res / kPairRate;
-      const double t_inter = (double)m * ((double)db->d->n_res - pair_res) / kInterRate;
-      const double share = t_pair / (t_pair + t_inter);
-      grid = std::min<int>(grid, (int)(kPairShare * share * db->d->n_cus * 4 / W2) + 1);
-    }
+    const int64_t count = (segmented ? db->d->n_seg_items : db->d->n_long_pairs) + off_pairs;
+    const int n_pass = (m + 64 * RR - 1) / (64 * RR);
+    const int64_t stride = segmented ? seg_stride(*db->d) : pair_stride(*db->d);
+    const double pair_res = (double)db->d->long_residues +
+                            (off_bins > 0 ? (double)db->d->bin_res_cum[(size_t)off_bins] : 0.0);
+    const int want = pair_grid(db, count, n_pass, W2, 64.0 * RR * n_pass * pair_res,
+                               n_bins > off_bins ? (double)m * ((double)db->d->n_res - pair_res)
+                                                 : 0.0);
     const int tl = time_begin(db, kTimeIntra, s);
-    if ((e = launch_intra_pairs(RR, W2, grid, la, s)) != hipSuccess)
-      return hip_fail(e, "intra-task kernel");
-    db->stats.long_items = la.count;
+    if (sh.pair.add >= 0) {
+      PairArgs pa{};
+      pa.res = db->d->res.p;
+      pa.offs = db->d->offs.p;
+      pa.items = db->d->d_long_pairs.p;
+      pa.count = (int32_t)count;
+      pa.counter = X.flags + 2;
+      pa.prof = reinterpret_cast<const uint8_t*>(X.prof3);
+      pa.m_pad2 = m_pad2;
+      pa.n_pass = n_pass;
+      pa.shared = pairs_lds(RR, W2, n_pass, true) + pairs_lds_static(W2) <= kLdsBytes;
+      auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
+      pa.c2 = both(std::min<int32_t>(go - ge, kHalfExact));
+      pa.ge2 = both(ge);
+      pa.bias2 = both(sh.pair.bias);
+      pa.sat_limit = effective_limit(db->sat_limit);
+      pa.lim2 = both(pa.sat_limit);
+      pa.over2 = both(32768 - pa.sat_limit);
+      // the row buffers there are: fewer pairs in flight, then fewer workgroups
+      pa.ring = pair_ring(n_pass, W2);
+      int grid = want;
+      if (n_pass > 1) {
+        const int64_t rows = std::max<int64_t>(1, (int64_t)X.long_words / stride);
+        while (pa.ring > 1 && (int64_t)pa.ring * grid > rows) --pa.ring;
+        grid = (int)std::min<int64_t>(grid, std::max<int64_t>(1, rows / pa.ring));
+      }
+      pa.scratch = reinterpret_cast<uint2*>(X.rb_long);
+      pa.scratch_stride = stride;
+      pa.out = d_out;
+      pa.flag_count = X.flags;
+      pa.flag_list = flist;
+      if (segmented) {
+        pa.seg_items = db->d->d_seg_items.p;
+        pa.seg_cols = db->d->seg_cols;
+        pa.seg_overlap = overlap;
+        pa.seg_best = X.seg_best;
+      }
+      e = launch_pairs(RR, W2, grid, pa, s);
+    } else {
+      IntraPairArgs la{};
+      la.res = db->d->res.p;
+      la.offs = db->d->offs.p;
+      la.items = db->d->d_long_pairs.p;
+      la.count = (int32_t)count;
+      la.prof3 = X.prof3;
+      la.m_pad2 = m_pad2;
+      la.n_pass = n_pass;
+      la.go2 = half_pair(go);
+      la.ge2 = half_pair(ge);
+      la.sat_limit = effective_limit(db->sat_limit);
+      la.scratch = X.rb_long;
+      la.scratch_stride = stride;
+      la.out = d_out;
+      la.flag_count = X.flags;
+      la.flag_list = flist;
+      int grid = std::min<int>(segmented ? X.grid_seg : X.grid_long, la.count);
+      if (n_bins > off_bins) grid = std::min(grid, want);
+      if (segmented) {
+        la.seg_items = db->d->d_seg_items.p;
+        la.seg_cols = db->d->seg_cols;
+        la.seg_overlap = overlap;
+        la.seg_best = X.seg_best;
+      }
+      e = launch_intra_pairs(RR, W2, grid, la, s);
+    }
+    if (e != hipSuccess) return hip_fail(e, "intra-task kernel");
+    db->stats.long_items = (int32_t)count;
     db->stats.long_overlap = segmented ? overlap : -1;
     if (segmented &&
         (e = launch_long_combine(db->d->d_long_pairs.p, db->d->d_pair_seg0.p,
                                  (int32_t)(db->d->n_long_pairs + off_pairs), X.seg_best,
-                                 la.sat_limit, d_out, X.flags, flist, s)) != hipSuccess)
+                                 effective_limit(db->sat_limit), d_out, X.flags, flist,
+                                 sh.pair.add >= 0, s)) != hipSuccess)
       return hip_fail(e, "segment maxima");
     time_end(db, tl, s);
     return SW_OK;
@@ -1233,7 +1393,7 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
   const int t_total = time_begin(db, kTimeTotal, s);
   if (mp.R > 0) {
     e = launch_profile(d_query, m, mat, db->prof.p, mp.n_strips * mp.R, mp.R, ge, mp.shape.pad,
-                       mode == SW_MODE_GLOBAL ? -2 * ge : 0, db->prof2.p, nullptr, m_pad2,
+                       mode == SW_MODE_GLOBAL ? -2 * ge : 0, db->prof2.p, nullptr, -1, m_pad2,
                        db->flags.p, s);
   } else {
     e = launch_mode_profile(d_query, m, mat, R32, n_strips32, db->mprof.p, db->prof2.p, m_pad2, s);
@@ -1326,6 +1486,10 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
   return SW_OK;
 }
 
+// Pairs of very long sequences in flight per workgroup of a batch's long-pair
+// kernel, each with a row buffer of the longest sequence.
+constexpr int kBatchRing = 4;
+
 // Builds (or keeps) the batch plan for these queries, matrix, gaps and
 // buffers: pairs of length-sorted queries, pair and per-query descriptors,
 // the (pair, half bin) work list costliest first, and the (sequence, query)
@@ -1408,7 +1572,14 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
   const int64_t m_med = n_nz ? ms[order[n_nz / 2]] : 1;
   int RR = 8, W2 = 1, RRp = 8, W2p = 1;
   pick_intra(db, (int)m_med, 8, &RR, &W2);
-  pick_intra(db, (int)m_med, 8, &RRp, &W2p, true);
+  const PairForm form = pair_form(mat, ge, db->sat_limit);
+  if (form.add < 0) {
+    pick_intra(db, (int)m_med, 8, &RRp, &W2p, true);
+  } else {
+    // each wave stages its pass's rows, as the queries differ
+    RRp = db->opt_intra_rows ? db->opt_intra_rows : m_med > 256 ? 8 : 4;
+    W2p = db->opt_intra_waves ? db->opt_intra_waves : 8;
+  }
   const int W2r = W2;
   const bool has_vlong = db->d->plan.n_vlong > 0;
   std::vector<QueryDesc> qd((size_t)std::max(nq, 1));
@@ -1422,7 +1593,8 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
     qd[q].prof3_off = prof3_dw;
     qd[q].out_off = (int64_t)q * db->d->n_seqs;
     prof2_bytes += (int64_t)kIntraCodes * qd[q].m_pad2;
-    if (has_vlong) prof3_dw += (int64_t)kIntraCodes * (qd[q].m_pad2 / 2);
+    if (has_vlong)    // (the drift form's offsets are bytes)
+      prof3_dw += (int64_t)kIntraCodes * (form.add >= 0 ? qd[q].m_pad2 : qd[q].m_pad2 / 2);
     if (ms[q] > 0) B.max_query_work = std::max<int64_t>(B.max_query_work, (int64_t)kIntraCodes * qd[q].m_pad2);
   }
   // (pair, half bin) items, costliest first
@@ -1468,7 +1640,8 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
       (e = B.items.reserve(std::max<size_t>(items.size(), 1))) != hipSuccess ||
       (e = B.long_items.reserve(std::max<size_t>(litems.size(), 1))) != hipSuccess ||
       (e = B.vpairs.reserve(std::max<size_t>(vpairs.size(), 1))) != hipSuccess ||
-      (e = B.prof3.reserve((size_t)std::max<int64_t>(prof3_dw, 4))) != hipSuccess ||
+      (e = B.prof3.reserve((size_t)std::max<int64_t>(form.add >= 0 ? prof3_dw / 4 : prof3_dw,
+                                                    4))) != hipSuccess ||
       (e = B.qoffs_d.reserve(qv.size())) != hipSuccess ||
       (e = B.prof.reserve((size_t)prof_dw + kProfSlack)) != hipSuccess ||
       (e = B.prof2.reserve((size_t)std::max<int64_t>(prof2_bytes, 16))) != hipSuccess)
@@ -1494,13 +1667,17 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
   B.RRp = RRp;
   B.W2p = W2p;
   B.grid_b = db->d->n_cus * batch_workgroups_per_cu(R, W);
-  B.grid_long = (int)std::min<int64_t>(B.n_long_items, kIntraGridLong);
+  B.pair_add = form.add;
+  B.pair_bias = form.bias;
+  B.grid_long = (int)std::min<int64_t>(
+      B.n_long_items, form.add >= 0 ? (int64_t)db->d->n_cus * std::max(1, 16 / W2p) : kIntraGridLong);
   if ((e = db->rb_batch.reserve((size_t)B.grid_b * (size_t)(db->d->plan.max_all_bin_len / 4) * 128)) !=
           hipSuccess ||
-      (e = db->counter.reserve(1)) != hipSuccess ||
+      (e = db->counter.reserve(2)) != hipSuccess ||
       (e = reserve_flags(db, ((db->d->plan.n_bins + db->d->plan.n_long_bins) * (int64_t)SW_BIN_SEQS +
                               db->d->plan.n_vlong) * std::max(n_nz, 1))) != hipSuccess ||
-      (e = reserve_long_scratch(db, std::max(B.grid_long, 1))) != hipSuccess)
+      (e = reserve_long_scratch(db, std::max(B.grid_long, 1) * (form.add >= 0 ? kBatchRing : 1))) !=
+          hipSuccess)
     return fail(SW_ENOMEM, std::string("batch scratch: ") + hipGetErrorString(e));
   B.qoffs = qv;
   B.mat = mat;
@@ -1519,7 +1696,7 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
   hipError_t e;
   const int64_t n = db->d->n_seqs;
   const int t_total = time_begin(db, kTimeTotal, s);
-  if ((e = launch_fill(db->counter.p, 1, 0, s)) != hipSuccess ||
+  if ((e = launch_fill(db->counter.p, 2, 0, s)) != hipSuccess ||
       (e = launch_fill(db->flags.p, 1, 0, s)) != hipSuccess)
     return hip_fail(e, "reset");
   for (int32_t q : B.zero_queries)
@@ -1532,7 +1709,8 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
   if ((e = launch_batch_profiles(B.d_queries, B.qoffs_d.p, nq, B.mat, B.pairs.p, B.n_pairs, B.R,
                                  B.drift.group > 0 ? B.ge : -1,
                                  std::max(B.max_pair_work, B.max_query_work), B.prof.p, B.qdesc.p,
-                                 B.prof2.p, B.n_long_items > 0 ? B.prof3.p : nullptr, s)) !=
+                                 B.prof2.p, B.n_long_items > 0 ? B.prof3.p : nullptr,
+                                 B.pair_add, s)) !=
       hipSuccess)
     return hip_fail(e, "batch profiles");
   IntraArgs ia{};
@@ -1543,40 +1721,68 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
   ia.go = B.go;
   ia.ge = B.ge;
   ia.out = B.d_out;
-  // Very long sequences: the packed long-pair kernel (binary16, two
-  // sequences per lane), each item with its query's profile and score row,
-  // on the auxiliary stream and enqueued before the persistent batched
-  // kernel, so that its workgroups take CUs first and the batched kernel's
-  // fill the rest (the batched kernel holds every CU it gets until its list
-  // is drained); joined before the rescoring.  Sequences at the rescoring
-  // limit join the list the batched kernel fills.
+  // Very long sequences: the packed long-pair kernel (two sequences per lane),
+  // each item with its query's profile and score row, started before the
+  // persistent batched kernel on the auxiliary stream, so that its workgroups
+  // take CUs first and the batched kernel's fill the rest (the batched kernel
+  // holds every CU it gets until its list is drained); joined before the
+  // rescoring.  Sequences at the rescoring limit join the list the batched
+  // kernel fills.
   const bool vlong = B.n_long_items > 0;
+  hipStream_t bs = s;
   if (vlong) {
+    bs = db->aux_stream;
     if ((e = hipEventRecord(db->ev_fork, s)) != hipSuccess ||
-        (e = hipStreamWaitEvent(db->aux_stream, db->ev_fork, 0)) != hipSuccess)
+        (e = hipStreamWaitEvent(bs, db->ev_fork, 0)) != hipSuccess)
       return hip_fail(e, "stream fork");
-    IntraPairArgs la{};
-    la.res = db->d->res.p;
-    la.offs = db->d->offs.p;
-    la.items = B.vpairs.p;
-    la.batch_items = B.long_items.p;
-    la.queries = B.qdesc.p;
-    la.count = (int32_t)B.n_long_items;
-    la.prof3 = B.prof3.p;
-    la.go2 = half_pair(B.go);
-    la.ge2 = half_pair(B.ge);
-    la.sat_limit = effective_limit(B.sat_limit);
-    la.scratch = db->rb_long.p;
-    la.scratch_stride = std::max<int64_t>(db->d->plan.max_long_len, 1);
-    la.out = B.d_out;
-    la.flag_count = db->flags.p;
-    la.flag_list = flag_list(db);
-    const int tl = time_begin(db, kTimeIntra, db->aux_stream);
-    if ((e = launch_intra_pairs(B.RRp, B.W2p, B.grid_long, la, db->aux_stream)) != hipSuccess)
-      return hip_fail(e, "long-pair kernel");
-    time_end(db, tl, db->aux_stream);
-    if ((e = hipEventRecord(db->ev_join, db->aux_stream)) != hipSuccess)
-      return hip_fail(e, "event");
+    const int tl = time_begin(db, kTimeIntra, s);
+    if (B.pair_add >= 0) {
+      PairArgs pa{};
+      pa.res = db->d->res.p;
+      pa.offs = db->d->offs.p;
+      pa.items = B.vpairs.p;
+      pa.batch_items = B.long_items.p;
+      pa.queries = B.qdesc.p;
+      pa.count = (int32_t)B.n_long_items;
+      pa.counter = db->counter.p + 1;
+      pa.prof = reinterpret_cast<const uint8_t*>(B.prof3.p);
+      pa.n_pass = 1;
+      pa.shared = 0;
+      auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
+      pa.c2 = both(std::min<int32_t>(B.go - B.ge, kHalfExact));
+      pa.ge2 = both(B.ge);
+      pa.bias2 = both(B.pair_bias);
+      pa.sat_limit = effective_limit(B.sat_limit);
+      pa.lim2 = both(pa.sat_limit);
+      pa.over2 = both(32768 - pa.sat_limit);
+      pa.ring = kBatchRing;
+      pa.scratch = reinterpret_cast<uint2*>(db->rb_long.p);
+      pa.scratch_stride = std::max<int64_t>(db->d->plan.max_long_len, 1);
+      pa.out = B.d_out;
+      pa.flag_count = db->flags.p;
+      pa.flag_list = flag_list(db);
+      e = launch_pairs(B.RRp, B.W2p, B.grid_long, pa, s);
+    } else {
+      IntraPairArgs la{};
+      la.res = db->d->res.p;
+      la.offs = db->d->offs.p;
+      la.items = B.vpairs.p;
+      la.batch_items = B.long_items.p;
+      la.queries = B.qdesc.p;
+      la.count = (int32_t)B.n_long_items;
+      la.prof3 = B.prof3.p;
+      la.go2 = half_pair(B.go);
+      la.ge2 = half_pair(B.ge);
+      la.sat_limit = effective_limit(B.sat_limit);
+      la.scratch = db->rb_long.p;
+      la.scratch_stride = std::max<int64_t>(db->d->plan.max_long_len, 1);
+      la.out = B.d_out;
+      la.flag_count = db->flags.p;
+      la.flag_list = flag_list(db);
+      e = launch_intra_pairs(B.RRp, B.W2p, B.grid_long, la, s);
+    }
+    if (e != hipSuccess) return hip_fail(e, "long-pair kernel");
+    time_end(db, tl, s);
   }
   if (db->d->plan.n_bins + db->d->plan.n_long_bins > 0) {
     BatchArgs ba{};
@@ -1599,12 +1805,13 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
     ba.sat_limit = effective_limit(B.sat_limit);
     ba.drift = B.drift;
     ba.max_s = max_score(B.mat);
-    const int ti = time_begin(db, kTimeInter, s);
-    if ((e = launch_batch(B.R, B.W, B.grid_b, ba, s)) != hipSuccess)
+    const int ti = time_begin(db, kTimeInter, bs);
+    if ((e = launch_batch(B.R, B.W, B.grid_b, ba, bs)) != hipSuccess)
       return hip_fail(e, "batched inter-task kernel");
-    time_end(db, ti, s);
+    time_end(db, ti, bs);
   }
-  if (vlong && (e = hipStreamWaitEvent(s, db->ev_join, 0)) != hipSuccess)
+  if (vlong && ((e = hipEventRecord(db->ev_join, bs)) != hipSuccess ||
+                (e = hipStreamWaitEvent(s, db->ev_join, 0)) != hipSuccess))
     return hip_fail(e, "stream join");
   {  // exact rescoring of what both packed kernels flagged
     IntraArgs ra = ia;
@@ -1774,6 +1981,7 @@ int noalloc_layout(const Searcher* db, const SearchShape& sh, uint8_t* base, NoA
     grid_long = (int)std::max<size_t>(
         1, std::min<size_t>({left / long_row, (size_t)db->d->n_long_pairs, (size_t)kIntraGridLong}));
     L->X.rb_long = reinterpret_cast<int2*>(take((size_t)grid_long * long_row));
+    L->X.long_words = (size_t)grid_long * long_row / sizeof(int2);
     // the same rows serve the column segments, at their shorter stride
     L->X.grid_seg = (int)std::min<size_t>(
         {(size_t)grid_long * long_row / ((size_t)seg_stride(*db->d) * sizeof(int2)),
@@ -2334,10 +2542,12 @@ static int impl_search_hybrid(swdb::Searcher* db, const uint8_t* query, int32_t 
     return hip_fail(e, "query upload");
   // every short bin takes part in the split (none handed to the long-pair
   // kernel): the host takes sequences from the back of the same order
-  SearchShape sh = search_shape(db, query_len);
+  Matrix mat;
+  memcpy(mat.v, matrix, sizeof(mat.v));
+  SearchShape sh = search_shape(db, query_len, mat, gap_extend);
   sh.off_bins = 0;
   SearchScratch X;
-  if ((rc = reserve_search_scratch(db, sh, &X)) != SW_OK) return rc;
+  if ((rc = reserve_search_scratch(db, sh, query_len, &X)) != SW_OK) return rc;
 
   // the plan: expected time of the short bins with both sides working, the
   // host's expected share, and the deadline by which a host thread must be
@@ -2465,8 +2675,6 @@ static int impl_search_hybrid(swdb::Searcher* db, const uint8_t* query, int32_t 
     gpu_done = true;
     return SW_OK;
   };
-  Matrix mat;
-  memcpy(mat.v, matrix, sizeof(mat.v));
   rc = enqueue_search_kernels(db, sh, X, db->q_stage.p, query_len, mat, gap_open, gap_extend,
                               db->out_stage.p, s, &runner);
   gpu_done = true;
@@ -2599,7 +2807,9 @@ static int impl_search_async_noalloc(swdb::Searcher* db, const uint8_t* d_query,
   }
   // no bins handed to the long-pair kernel: its boundary rows here are
   // sized for the long list only
-  SearchShape sh = search_shape(db, query_len);
+  Matrix mat;
+  memcpy(mat.v, matrix, sizeof(mat.v));
+  SearchShape sh = search_shape(db, query_len, mat, gap_extend);
   sh.off_bins = 0;
   NoAllocLayout L;
   if ((rc = noalloc_layout(db, sh, base, &L)) != SW_OK) return rc;
@@ -2629,8 +2839,6 @@ static int impl_search_async_noalloc(swdb::Searcher* db, const uint8_t* d_query,
     }
     return SW_OK;
   };
-  Matrix mat;
-  memcpy(mat.v, matrix, sizeof(mat.v));
   // no timing events here: recording them may create events
   const bool timing = db->timing;
   db->timing = false;
@@ -3264,7 +3472,7 @@ int64_t sw_ctx_bytes(const sw_db* h) {
   if (!h) return -1;
   const swdb::Plan& P = h->data.plan;
   return P.boundary_uint4 * 16 + (int64_t)swdb::kIntraGridRescore * swdb::rescore_stride(P) * 8 +
-         (2 + 2 * std::max<int64_t>(P.n_bins * SW_BIN_SEQS + P.n_long, 1)) * 4 +
+         (swdb::kFlagWords + 2 * std::max<int64_t>(P.n_bins * SW_BIN_SEQS + P.n_long, 1)) * 4 +
          std::max<int64_t>(h->data.n_seg_items, 1) * 4;
 }
 

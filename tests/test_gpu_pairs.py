@@ -1,0 +1,109 @@
+"""GPU parity of the long-pair kernel at the edges of its passes, of its queue
+and of the rule on gap penalties and matrices that chooses it, against the
+oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle.cpu as ocpu
+import swinputs
+
+pytestmark = pytest.mark.gpu
+
+B62 = swinputs.blosum62()
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def sw():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2203_11100_amd as lib
+    return lib
+
+
+def _db(seed, m, rng_seqs=30):
+    """Lengths around the supersteps' 64 columns, empty sequences, and copies of
+    the query in some (scores past the limit)."""
+    rng = np.random.default_rng(seed)
+    lens = np.concatenate([[0, 0, 1, 1, 2, 63, 64, 65, 127, 128, 129, 1500],
+                           rng.integers(1, 900, rng_seqs)]).astype(np.int64)
+    res, offs = swinputs.make_database(rng.permutation(lens), rng)
+    q = swinputs.random_residues(m, rng)
+    sizes = np.diff(offs)
+    for i in np.argsort(sizes)[-9::4]:
+        n = int(sizes[i])
+        res[offs[i]:offs[i] + n] = np.resize(q, n)
+    return res, offs, q
+
+
+def _hot():
+    """Entries from -128 to 127: a score passes the limit within 17 cells."""
+    mat = np.random.default_rng(5).integers(-128, 1, (24, 24)).astype(np.int8)
+    mat[np.arange(24), np.arange(24)] = 127
+    return mat
+
+
+def _same(got, want, what):
+    bad = np.nonzero(got != want)[0]
+    assert len(bad) == 0, (what, [(int(i), int(got[i]), int(want[i])) for i in bad[:5]])
+
+
+# every sequence in the long list; queries around a pass's 64 R rows, of fewer
+# passes than waves (several pairs in flight), of more (rounds), and of more
+# passes than profiles fit at once
+@pytest.mark.parametrize("m", [1, 2, 127, 128, 129, 511, 513, 1100, 5300])
+@pytest.mark.parametrize("rows,waves", [(0, 0), (2, 1), (2, 8), (4, 2), (4, 4), (8, 1), (8, 8)])
+def test_passes(sw, m, rows, waves):
+    res, offs, q = _db(m, m)
+    say("m=%d rows %d waves %d" % (m, rows, waves))
+    want = ocpu.search(q, res, offs, B62, 10, 2)
+    with sw.Database(res, offs, long_threshold=1) as db:
+        db.set_option(sw.SW_OPT_INTRA_ROWS, rows)
+        db.set_option(sw.SW_OPT_INTRA_WAVES, waves)
+        for _ in range(2):                          # the queue again
+            _same(db.search(q, B62, 10, 2), want, (m, rows, waves))
+        assert db.stats()["n_rescored"] == int((want >= 2048).sum())
+
+
+# extension penalties up to the byte range of the profile (blosum62: 122) and
+# past it, none, opening penalties past 16 bits; a matrix that needs the guard
+@pytest.mark.parametrize("go,ge", [(10, 0), (0, 0), (14, 14), (300, 60), (130, 122), (130, 123),
+                                   (100000, 3), (100000, 100000)])
+@pytest.mark.parametrize("matrix,limit", [("b62", 32767), ("b62", 40), ("hot", 32767)])
+def test_gap_ranges(sw, go, ge, matrix, limit):
+    res, offs, q = _db(go + ge, 600)
+    mat = _hot() if matrix == "hot" else B62
+    say("gaps %d/%d %s limit %d" % (go, ge, matrix, limit))
+    want = ocpu.search(q, res, offs, mat, go, ge)
+    with sw.Database(res, offs, long_threshold=1) as db:
+        db.set_option(sw.SW_OPT_SAT_LIMIT, limit)
+        for rows in (2, 4, 8):
+            db.set_option(sw.SW_OPT_INTRA_ROWS, rows)
+            _same(db.search(q, mat, go, ge), want, rows)
+
+
+# column segments, short bins handed over beside bins that stay, batches with
+# sequences for this kernel, more pairs than workgroups
+@pytest.mark.parametrize("go,ge", [(10, 2), (200, 130)])
+def test_segments_bins_and_batches(sw, go, ge):
+    rng = np.random.default_rng(7)
+    lens = np.concatenate([[70000, 33001, 9000], rng.integers(1, 500, 3000)]).astype(np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    qs = [swinputs.random_residues(m, rng) for m in (30, 200, 600)]
+    res[offs[0] + 5000:offs[0] + 5200] = qs[1]
+    want = [ocpu.search(q, res, offs, B62, go, ge) for q in qs]
+    say("segments, gaps %d/%d" % (go, ge))
+    with sw.Database(res, offs) as db:
+        for off in (0, 3, 1000):
+            db.set_option(sw.SW_OPT_OFFLOAD_BINS, off)
+            for q, w in zip(qs, want):
+                _same(db.search(q, B62, go, ge), w, (off, len(q)))
+        for _ in range(2):
+            got = db.search_batch(qs, B62, go, ge)
+            for row, w in zip(got, want):
+                _same(row, w, "batch")
