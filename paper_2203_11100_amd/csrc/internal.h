@@ -198,6 +198,14 @@ struct IntraPairArgs {
 
 // Long-pair kernel in the drift form (k_pairs.hip); items, segments and batches
 // as in IntraPairArgs.
+// The long-pair kernel's profile: bytes S + add of a query's rows, shifted down by `top` rows of top_byte; add -1: not the byte form.
+struct PairBytes {
+  int32_t add = -1;
+  int32_t top = 0, top_byte = 0;
+  int32_t code_byte = 0;      // the pad code's
+  int32_t row_byte = 0;       // of rows past the query's end
+};
+
 struct PairArgs {
   const uint8_t* res;         // contiguous residues, original order
   const int64_t* offs;
@@ -222,6 +230,7 @@ struct PairArgs {
   uint32_t* seg_best;
   const int2* batch_items;
   const QueryDesc* queries;   // prof3_off in bytes
+  ModeShape mode;             // global and semi-global: whole pairs of one query
 };
 
 // LDS of one workgroup of the long-pair kernel: profiles (dynamic) and the rest.
@@ -285,11 +294,11 @@ static_assert(sizeof(TopkState) % 8 == 0, "TopkState keeps the arrays after it 8
 
 // Kernel launchers (return hipSuccess or the launch error).
 // drift: gap_extend of the drift form or -1; top: rows above the query's first,
-// of the score top_score against every code; pair_add: prof3 holds the bytes
-// S + pair_add of the long-pair kernel, or (-1) binary16 row pairs
+// of the score top_score against every code; pb: prof3 holds the long-pair
+// kernel's bytes or binary16 row pairs
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
                           int m_pad, int R, int drift, int top, int top_score, int8_t* prof2,
-                          uint32_t* prof3, int pair_add, int m_pad2, int32_t* flag_count,
+                          uint32_t* prof3, const PairBytes& pb, int m_pad2, int32_t* flag_count,
                           hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_inter(int R, int W, int n_cus, const InterArgs& a, hipStream_t s);
@@ -332,6 +341,7 @@ hipError_t launch_hit_combine(const int2* items, int32_t k, const int32_t* seg0,
 hipError_t launch_batch_profiles(const uint8_t* d_queries, const int64_t* d_qoffs, int n_queries,
                                  const Matrix& mat, const PairDesc* d_pairs, int n_pairs, int R,
                                  int drift, int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
-                                 int8_t* prof2, uint32_t* prof3, int pair_add, hipStream_t s);
+                                 int8_t* prof2, uint32_t* prof3, const PairBytes& pb,
+                                 hipStream_t s);
 
 }  // namespace swdb

@@ -70,8 +70,6 @@ namespace {
 // in global mode they score -2 ge and E holds the border.  The score is the last
 // row's H at the sequence's last column (global) or its maximum over the
 // sequence's columns, both taken by the last strip.
-enum { kCellHalf = 0, kCellDrift = 1, kCellGlobal = 2, kCellSemi = 3 };
-
 template <int R, int W, int kForm>
 __global__ __launch_bounds__(64 * W) void k_inter(InterArgs a) {
   constexpr bool kDrift = kForm == kCellDrift;

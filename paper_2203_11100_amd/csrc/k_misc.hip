@@ -18,18 +18,20 @@ __device__ __forceinline__ int profile_score(const uint8_t* __restrict__ q, int 
 // (c, r) = S(a_2r, c) low, S(a_2r+1, c) high); codes 0..23 and the pad code.
 // Entry (i, c) is S(a_i, c); rows past the query end and the pad/spare codes
 // get kPadScore.  Thread 0 also clears the rescoring list's count.
-// pair_add >= 0: prof3 is instead the long-pair kernel's [25][m_pad2] bytes
-// S + pair_add, four rows a dword; the pad code and rows past the query's end
-// hold a byte of `pair_pad` (a score <= 0).
+// pb.add >= 0: prof3 is instead the long-pair kernel's [25][m_pad2] bytes
+// S + p.add, four rows a dword, with p's bytes for the rows above and past the
+// query and for the pad code.
 __device__ __forceinline__ uint32_t pair_bytes(const uint8_t* __restrict__ q, int m,
-                                               const Matrix& mat, int row, int c, int pair_add,
-                                               int pair_pad) {
+                                               const Matrix& mat, int row, int c,
+                                               const PairBytes& p) {
   uint32_t v = 0;
   for (int t = 0; t < 4; ++t) {
-    const int i = row + t;
-    const uint32_t b = i >= m || c >= SW_ALPHA || q[i] >= SW_ALPHA
-                           ? (uint32_t)pair_pad
-                           : (uint32_t)(mat.v[q[i] * SW_ALPHA + c] + pair_add);
+    const int i = row + t - p.top;
+    const uint32_t b = i < 0           ? (uint32_t)p.top_byte
+                       : c >= SW_ALPHA ? (uint32_t)p.code_byte
+                       : i >= m || q[i] >= SW_ALPHA
+                           ? (uint32_t)p.row_byte
+                           : (uint32_t)(mat.v[q[i] * SW_ALPHA + c] + p.add);
     v |= (b & 0xffu) << (8 * t);
   }
   return v;
@@ -38,11 +40,11 @@ __device__ __forceinline__ uint32_t pair_bytes(const uint8_t* __restrict__ q, in
 __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
                           uint32_t* __restrict__ prof, int m_pad, int R, int drift,
                           int top, int top_score, int8_t* __restrict__ prof2, uint32_t* __restrict__ prof3,
-                          int pair_add, int pair_pad, int m_pad2,
+                          PairBytes pb, int m_pad2,
                           int32_t* __restrict__ flag_count) {
   const int64_t n1 = (int64_t)(m_pad / R) * prof_strip_dwords(R);
   const int64_t n2 = (int64_t)kIntraCodes * m_pad2;
-  const int64_t n3 = prof3 ? (int64_t)kIntraCodes * (m_pad2 / (pair_add >= 0 ? 4 : 2)) : 0;
+  const int64_t n3 = prof3 ? (int64_t)kIntraCodes * (m_pad2 / (pb.add >= 0 ? 4 : 2)) : 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < kFlagWords && flag_count) flag_count[idx] = 0;
@@ -68,9 +70,9 @@ __global__ void k_profile(const uint8_t* __restrict__ q, int m, Matrix mat,
       prof2[j] = (int8_t)profile_score(q, m, mat, i, c);
     } else {
       const int64_t j = idx - n1 - n2;
-      if (pair_add >= 0) {
+      if (pb.add >= 0) {
         const int words = m_pad2 / 4;
-        prof3[j] = pair_bytes(q, m, mat, (int)(j % words) * 4, (int)(j / words), pair_add, pair_pad);
+        prof3[j] = pair_bytes(q, m, mat, (int)(j % words) * 4, (int)(j / words), pb);
         continue;
       }
       const int half_rows = m_pad2 / 2;
@@ -94,7 +96,7 @@ __global__ void k_batch_profiles(const uint8_t* __restrict__ queries,
                                  const PairDesc* __restrict__ pairs, int n_pairs, int R,
                                  int drift, uint32_t* __restrict__ prof,
                                  const QueryDesc* __restrict__ qdesc, int8_t* __restrict__ prof2,
-                                 uint32_t* __restrict__ prof3, int pair_add, int pair_pad) {
+                                 uint32_t* __restrict__ prof3, PairBytes pb) {
   const int y = blockIdx.y;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t start = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -123,11 +125,11 @@ __global__ void k_batch_profiles(const uint8_t* __restrict__ queries,
       const int c = (int)(idx / qd.m_pad2), i = (int)(idx % qd.m_pad2);
       prof2[qd.prof2_off + idx] = (int8_t)profile_score(q, m, mat, i, c);
     }
-    if (prof3 && pair_add >= 0) {   // bytes, prof3_off in bytes
+    if (prof3 && pb.add >= 0) {   // bytes, prof3_off in bytes
       const int words = qd.m_pad2 / 4;
       for (int64_t idx = start; idx < (int64_t)kIntraCodes * words; idx += stride)
         prof3[qd.prof3_off / 4 + idx] =
-            pair_bytes(q, m, mat, (int)(idx % words) * 4, (int)(idx / words), pair_add, pair_pad);
+            pair_bytes(q, m, mat, (int)(idx % words) * 4, (int)(idx / words), pb);
     } else if (prof3) {   // packed binary16 row pairs [25][m_pad2 / 2] (the layout of k_profile)
       const int half_rows = qd.m_pad2 / 2;
       for (int64_t idx = start; idx < (int64_t)kIntraCodes * half_rows; idx += stride) {
@@ -147,42 +149,32 @@ __global__ void k_fill(int32_t* __restrict__ p, int64_t n, int32_t v) {
 
 }  // namespace
 
-namespace {
-// The long-pair kernel's byte for padding: the matrix's smallest score, or 0
-// where that is above 0.
-int pair_pad_byte(const Matrix& mat, int pair_add) {
-  int lo = 0;
-  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) lo = mat.v[x] < lo ? mat.v[x] : lo;
-  return pair_add >= 0 ? lo + pair_add : 0;
-}
-}  // namespace
-
 hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint32_t* prof,
                           int m_pad, int R, int drift, int top, int top_score, int8_t* prof2,
-                          uint32_t* prof3, int pair_add, int m_pad2, int32_t* flag_count,
+                          uint32_t* prof3, const PairBytes& pb, int m_pad2, int32_t* flag_count,
                           hipStream_t s) {
   if (R <= 0 || R % 2 != 0 || m_pad % R != 0) return hipErrorInvalidValue;
   const int64_t total = (int64_t)(m_pad / R) * prof_strip_dwords(R) +
                         (int64_t)kIntraCodes * m_pad2 +
-                        (prof3 ? (int64_t)kIntraCodes * (m_pad2 / (pair_add >= 0 ? 4 : 2)) : 0);
+                        (prof3 ? (int64_t)kIntraCodes * (m_pad2 / (pb.add >= 0 ? 4 : 2)) : 0);
   int grid = (int)std::min<int64_t>((total + 255) / 256, 2048);
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(k_profile, dim3(grid), dim3(256), 0, s, d_query, m, mat, prof, m_pad, R,
-                     drift, top, top_score, prof2, prof3, pair_add, pair_pad_byte(mat, pair_add), m_pad2, flag_count);
+                     drift, top, top_score, prof2, prof3, pb, m_pad2, flag_count);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_profiles(const uint8_t* d_queries, const int64_t* d_qoffs, int n_queries,
                                  const Matrix& mat, const PairDesc* d_pairs, int n_pairs, int R,
                                  int drift, int64_t max_work, uint32_t* prof, const QueryDesc* d_qdesc,
-                                 int8_t* prof2, uint32_t* prof3, int pair_add, hipStream_t s) {
+                                 int8_t* prof2, uint32_t* prof3, const PairBytes& pb,
+                                 hipStream_t s) {
   const int ys = n_pairs + n_queries;
   if (ys <= 0) return hipSuccess;
   if (ys > 65535) return hipErrorInvalidValue;
   const int gx = (int)std::max<int64_t>(1, std::min<int64_t>((max_work + 255) / 256, 256));
   hipLaunchKernelGGL(k_batch_profiles, dim3(gx, ys), dim3(256), 0, s, d_queries, d_qoffs, mat,
-                     d_pairs, n_pairs, R, drift, prof, d_qdesc, prof2, prof3, pair_add,
-                     pair_pad_byte(mat, pair_add));
+                     d_pairs, n_pairs, R, drift, prof, d_qdesc, prof2, prof3, pb);
   return hipGetLastError();
 }
 

@@ -37,6 +37,18 @@
 // progress words (stream.h), two supersteps behind the pass above; a pair's passes hand their bottom rows on through a row buffer
 // of its own in device memory, overwritten in place.
 //
+// Global and semi-global (kForm): no floor and no running maximum, H and F drift
+// over the rows too (base + ge * (row + column): a gap along the left border
+// costs its opening only, so that border is one value), and nothing comes off
+// between lanes.  The global top border is one value as well and its columns'
+// drift stays, the values being bounded by the gain of min(rows, columns); the
+// semi-global one, H = 0, rises with the columns, whose drift comes off every
+// superstep.  Before its column 0 a lane's cells keep the left border: they read
+// the pad code, S = -2 ge in these forms.  The query is shifted down by less than
+// R rows, as in the strips, so that its last row is the last of a lane; that
+// lane's bottom row goes to the line in the last pass, and the score is taken from
+// there, a superstep at a time.  Lanes below it compute what nobody reads.
+//
 // A step takes 8 + 6.5 R vector ops for 2 R cells (k_intra_f16: 24 + 8 R with
 // the byte permutes, and barriers every 64 steps).  Bound by a pair's own chain
 // of steps where pairs are few (columns times the time of a step), else by the
@@ -68,23 +80,24 @@ __device__ __forceinline__ uint32_t word_of(const uint2& v, int x) { return x ? 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 
-// Lane 63 of a wave whose lanes are all active writes v to LDS at byte address
+// One lane of a wave whose lanes are all active (its bit) writes x, y to LDS at byte address
 // at + off: one store between two scalar writes of the exec mask, with no branch
 // to cut the unrolled steps apart.
 template <int kOff>
-__device__ __forceinline__ void store_last_lane(uint32_t at, uint32_t x, uint32_t y) {
+__device__ __forceinline__ void store_lane(uint64_t lane_bit, uint32_t at, uint32_t x, uint32_t y) {
   asm volatile(
       "s_mov_b64 exec, %0\n\t"
       "ds_write_b64 %1, %2 offset:%3\n\t"
       "s_mov_b64 exec, -1"
       :
-      : "s"(0x8000000000000000ull), "v"(at), "v"(u32x2{x, y}), "n"(kOff));
+      : "s"(lane_bit), "v"(at), "v"(u32x2{x, y}), "n"(kOff));
 }
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-template <int R, int W>
+template <int R, int W, int kForm>
 __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
+  constexpr bool kLocal = kForm == kCellDrift;
   constexpr int ROWS = 64 * R;             // query rows per pass, bytes per code row
   constexpr int kPassBytes = kIntraCodes * ROWS;
   typedef typename ByteRows<R>::T PV;
@@ -103,7 +116,7 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
   const int w = uniform(threadIdx.x >> 6);
   const int pred = w > 0 ? w - 1 : W - 1;
   const uint32_t ge2 = a.ge2;
-  const uint32_t gr_s = ge2 * (uint32_t)(R - 1);
+  const uint32_t gr_s = kLocal ? ge2 * (uint32_t)(R - 1) : 0;
   uint32_t cv = a.c2, gr = gr_s;
   asm("" : "+v"(cv), "+v"(gr));            // 32-bit subtractions on two vector registers
   const uint32_t base2 = twice(kDriftBase);
@@ -112,8 +125,18 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
   uint32_t bias_k = 0u - a.bias2, bias_0 = bias_k - gr_s;
   asm("" : "+s"(bias_k), "+s"(bias_0));
   // H and F of a zero row above, as lane 0 takes them at step `lane`
-  const uint32_t zero_h = base2 + ge2 * (lane + R) - 2 * ge2;
-  const uint32_t zero_f = base2 + ge2 * (lane + R) - ge2;
+  uint32_t zero_h = base2 + ge2 * (lane + R) - 2 * ge2;
+  uint32_t zero_f = base2 + ge2 * (lane + R) - ge2;
+  // global and semi-global: the left border, the lane that holds the last row
+  const ModeShape& md = a.mode;
+  const uint32_t mbase2 = twice((uint32_t)md.base);
+  const uint32_t left2 = twice((uint32_t)(md.base - md.go - md.ge + md.ge * md.pad));
+  const uint32_t top2 = twice((uint32_t)(md.base - md.go + md.ge * (md.pad - 1)));
+  const int last_lane = kLocal ? 63 : (md.m + md.pad) / R - 1 - (a.n_pass - 1) * 64;
+  if constexpr (!kLocal) {
+    zero_h = kForm == kCellGlobal ? top2 : mbase2 + ge2 * lane - ge2;
+    zero_f = zero_h - a.c2;
+  }
 
   auto stage = [&](char* dst, const uint8_t* prof, int m_pad2, int pass, int from, int step) {
     constexpr int per_code = ROWS / 16;    // uint4 per code row
@@ -256,6 +279,35 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
     uint32_t hdiag = base2 + ge2 * (uint32_t)R - 3 * ge2;
     const uint32_t low_f = base2 - twice(2048) + gr_s;
     uint32_t fbot = low_f;
+    uint32_t score = 0;
+    const int out_lane = p == P - 1 ? last_lane : 63;
+    uint64_t out_bit = 1ull << 63;
+    if constexpr (!kLocal) {
+      out_bit = 1ull << uniform(out_lane);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        H[r] = left2;
+        E[r] = left2 - a.c2;
+      }
+      hdiag = left2;
+      fbot = left2 - a.c2;
+      if (p == 0 && lane == 0) {
+        const uint32_t corner2 = mbase2 + ge2 * (uint32_t)md.pad - 2 * ge2;   // H(0, 0) = 0
+        hdiag = kForm == kCellGlobal && md.pad > 0 ? top2 : mbase2 - 2 * ge2;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (r < md.pad) {
+            if (kForm == kCellGlobal) {
+              H[r] = r == md.pad - 1 ? corner2 : top2;
+              E[r] = top2;
+            } else {
+              H[r] = mbase2 + ge2 * (uint32_t)r - ge2;
+              E[r] = H[r] - a.c2;
+            }
+          }
+        }
+      }
+    }
     uint32_t code = twice((uint32_t)(SW_PAD_CODE * ROWS));
     if (C > 0) {
       if (p > 0) wait_pred(there + (uint32_t)min(2, C));
@@ -271,21 +323,22 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
         const bool up = p > 0 && jf < cols;
         // cut at the limit: such a sequence is rescored, its values only have to
         // stay in range
-        lfeed[w][lane] = make_uint4(x * ROWS | (y * ROWS) << 16,
-                                    up ? umin2(up_n.x, zero_h + a.lim2) : zero_h,
-                                    up ? umin2(up_n.y, zero_f + a.lim2) : zero_f, 0);
+        const uint32_t up_h = kLocal ? umin2(up_n.x, zero_h + a.lim2) : up_n.x;
+        const uint32_t up_f = kLocal ? umin2(up_n.y, zero_f + a.lim2) : up_n.y;
+        lfeed[w][lane] = make_uint4(x * ROWS | (y * ROWS) << 16, up ? up_h : zero_h,
+                                    up ? up_f : zero_f, 0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
       }
       if (c + 1 < C) {
         if (p > 0) wait_pred(there + (uint32_t)min(c + 3, C));
         fetch(c + 1);
       }
-      if (c > 0) {
+      if (kForm != kCellGlobal && c > 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           H[r] -= 64 * ge2;
           E[r] -= 64 * ge2;
-          A[r] -= 64 * ge2;
+          if (kLocal) A[r] -= 64 * ge2;
         }
         hdiag -= 64 * ge2;
         fbot -= 64 * ge2;
@@ -314,7 +367,7 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
           // the last step's bottom row, then this step's reads: the wait for them
           // in the next step is then for reads alone (the compiler does not count
           // the store), and nothing of that step may be scheduled before it
-          store_last_lane<8 * u>(coll, H[R - 1], fbot);
+          store_lane<8 * u>(out_bit, coll, H[R - 1], fbot);
           code = shr_in(code, f2.x);
           if (u == 5) code_63 = code;
           const u32x3 f4 = feed((8 * g + u + 4) & 63);
@@ -325,7 +378,7 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
           __builtin_amdgcn_sched_barrier(0);
           uint32_t hd = hdiag;
           hdiag = hup;
-          uint32_t F = fup - gr;
+          uint32_t F = kLocal ? fup - gr : fup;
           uint32_t z = zg + ge2 * (uint32_t)u;
 #pragma unroll
           for (int r = 0; r < R; ++r) {
@@ -335,15 +388,15 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
             const uint32_t d = hd + s + (r == 0 ? bias_0 : bias_k);
             const uint32_t h = hmax3(d, E[r], F);
             const uint32_t t = h - cv;
-            if (r == 0 && !(u & 1)) x = umax2(A[1], h) - z;
-            if (u & 1) {
+            if (kLocal && r == 0 && !(u & 1)) x = umax2(A[1], h) - z;
+            if (kLocal && (u & 1)) {
               if (r + 2 < R) A[r] = hmax3(A[r + 2], h, H[r + 1]);
               else if (r + 1 < R) A[r] = umax2(h, H[r + 1]);
               else A[r] = h;
               if (r == 0) best = hmax3(best, x, A[0] - z);
             }
             z += ge2;
-            E[r] = hmax3(E[r], t, z);
+            E[r] = kLocal ? hmax3(E[r], t, z) : umax2(E[r], t);
             F = umax2(F, t);
             hd = H[r];
             H[r] = h;
@@ -369,31 +422,60 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
         step(std::integral_constant<int, 7>());
         coll += 64;
       }
-      store_last_lane<0>(coll, H[R - 1], fbot);
+      store_lane<0>(out_bit, coll, H[R - 1], fbot);
       code = code_63;   // `code` ran two steps ahead: back to the last step's own
       asm volatile("" ::: "memory");
       const uint2 low = lcoll[w][lane + 1];
-      const int jo = c * 64 + (int)lane - 63;
+      const int jo = c * 64 + (int)lane - out_lane;
       if (p < P - 1 && jo >= 0 && jo < cols) {
-        const uint32_t off = lane == 63 ? 64 * ge2 : 0u;   // a superstep of the next pass on
+        // what the next pass finds there in its superstep, by this one's drift:
+        // lane 63's column is the first of the superstep after (local cells), or
+        // the others' are a superstep back (semi-global)
+        uint32_t off = lane == 63 ? 64 * ge2 : 0u;
+        if (kForm == kCellSemi) off -= 64 * ge2;
+        if (kForm == kCellGlobal) off = 0;
         rb[jo] = make_uint2(low.x - off, low.y - off);
+      }
+      if constexpr (!kLocal) {
+        if (p == P - 1) {
+          // 0xffff in the halves whose sequence ends with this column or has it
+          const bool ina = kForm == kCellGlobal ? jo == na - 1 : jo >= 0 && jo < na;
+          const bool inb = kForm == kCellGlobal ? jo == nb - 1 : jo >= 0 && jo < nb;
+          const uint32_t in = (ina && na > 0 ? 0xffffu : 0u) | (inb && nb > 0 ? 0xffff0000u : 0u);
+          const uint32_t v =
+              kForm == kCellGlobal ? low.x : low.x + ge2 * (uint32_t)(out_lane - (int)lane);
+          score = umax2(score, v & in);
+        }
       }
       publish(&lprog[w], here + (uint32_t)c + 1);
       // a lane whose maximum has reached the limit starts again from Z in that
       // half: what a lane takes from the one above it enters its maximum at once,
       // so no value passes the limit by more than two supersteps' gain
-      const uint32_t over = (best + a.over2) & 0x80008000u;
+      const uint32_t over = kLocal ? (best + a.over2) & 0x80008000u : 0;
       if (over != 0) {
         drift_guard<R>(H, E, A, hdiag, best, a.over2, base2 + 64 * ge2, ge2);
         const uint32_t m = (over >> 15) * 0xffffu;
         fbot = (fbot & ~m) | ((low_f + 64 * ge2) & m);
       }
     }
-    if (C > 0) drift_finish<R>(A, best, base2 + 63 * ge2, ge2);
+    if (kLocal && C > 0) drift_finish<R>(A, best, base2 + 63 * ge2, ge2);
+    if (!kLocal) best = score;
 
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) best = umax2(best, (uint32_t)__shfl_xor((int)best, off, 64));
     int fin = 0;
+    if (!kLocal && p == P - 1 && lane == 0) {
+      // H~ less base and the drift of the last row (and, global, of the last column)
+      const int rows = md.base + md.ge * (md.m + md.pad - 1);
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const int sid = half ? sb : sa, n_h = half ? nb : na;
+        if (sid < 0) continue;
+        const int v = (int)(half ? best >> 16 : best & 0xffffu);
+        a.out[sid] = n_h == 0 ? -(md.go + (md.m - 1) * md.ge)
+                              : v - rows - (kForm == kCellGlobal ? md.ge * (n_h - 1) : 0);
+      }
+    }
     if (lane == 0) {
       atomicMax(&lbest[slot][0], best & 0xffffu);
       atomicMax(&lbest[slot][1], best >> 16);
@@ -404,7 +486,9 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
       // the rescoring limit, an entry of the rescoring list
       const uint32_t b0 = lbest[slot][0], b1 = lbest[slot][1];
       lbest[slot][0] = lbest[slot][1] = 0;
-      if (a.seg_best) {
+      if (!kLocal) {
+        // the scores are out
+      } else if (a.seg_best) {
         a.seg_best[it] = b0 | (b1 << 16);
       } else {
 #pragma unroll
@@ -428,7 +512,13 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
 
 template <int R, int W>
 hipError_t launch_rw(int grid, size_t lds, const PairArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_pairs<R, W>), dim3(grid), dim3(64 * W), lds, s, a);
+  const dim3 block(64 * W);
+  if (a.mode.mode == SW_MODE_GLOBAL)
+    hipLaunchKernelGGL((k_pairs<R, W, kCellGlobal>), dim3(grid), block, lds, s, a);
+  else if (a.mode.mode == SW_MODE_SEMIGLOBAL)
+    hipLaunchKernelGGL((k_pairs<R, W, kCellSemi>), dim3(grid), block, lds, s, a);
+  else
+    hipLaunchKernelGGL((k_pairs<R, W, kCellDrift>), dim3(grid), block, lds, s, a);
   return hipGetLastError();
 }
 

@@ -205,6 +205,7 @@ __device__ __forceinline__ void sweep_chunk_ahead(uint32_t (&H)[R], uint32_t (&E
 // of the last odd column: at odd columns A[k] = max(A[k + 2], the cell, the
 // cell left and below of it), two cells an op, in place, and an anti-diagonal
 // that has reached row 0 is complete and enters `best` less its Z.
+enum { kCellHalf = 0, kCellDrift = 1, kCellGlobal = 2, kCellSemi = 3 };   // cell forms
 constexpr uint32_t kDriftBase = 2560;
 constexpr int kDriftTop = 31743;      // the largest value the maxima order as integers
 

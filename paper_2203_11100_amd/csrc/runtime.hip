@@ -129,7 +129,8 @@ struct BatchPlan {
   int64_t inter_cells = 0, intra_cells = 0;
   int grid_b = 0, grid_long = 0;
   swdb::DriftArgs drift{};
-  int pair_add = -1, pair_bias = 0;   // the long-pair kernel's form (pair_form)
+  swdb::PairBytes pair;               // the long-pair kernel's form (pair_form)
+  int pair_bias = 0;
   std::vector<int32_t> zero_queries;
   swdb::DevBuf<swdb::PairDesc> pairs;
   swdb::DevBuf<swdb::QueryDesc> qdesc;
@@ -712,8 +713,8 @@ int32_t hit_overlap(const DbData& d, int m, const Matrix& mat, int32_t ge) {
 // is what its profile bytes hold beside S (2 ge + bias), -1 where the form does
 // not fit - the drift of a superstep and two supersteps' gain past the limit
 // within the 16-bit range, scores within a byte - and k_intra_f16 is used.
-struct PairForm {
-  int add = -1, bias = 0;
+struct PairForm : PairBytes {
+  int bias = 0;
 };
 PairForm pair_form(const Matrix& mat, int32_t ge, int32_t sat_limit) {
   PairForm f;
@@ -728,6 +729,7 @@ PairForm pair_form(const Matrix& mat, int32_t ge, int32_t sat_limit) {
   if (top > kDriftTop || hi + 2 * (int64_t)ge + bias > 255) return f;
   f.bias = bias;
   f.add = 2 * ge + bias;
+  f.code_byte = f.row_byte = lo + f.add;     // the smallest score, or 0
   return f;
 }
 
@@ -1039,7 +1041,7 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   const int t_total = time_begin(db, kTimeTotal, s);
   if ((e = launch_profile(d_query, m, mat, X.prof, sh.m_pad, R, drift.group > 0 ? ge : -1, 0, 0,
                           X.prof2,
-                          pairs ? X.prof3 : nullptr, sh.pair.add, m_pad2, X.flags, s)) !=
+                          pairs ? X.prof3 : nullptr, sh.pair, m_pad2, X.flags, s)) !=
       hipSuccess)
     return hip_fail(e, "profile kernel");
   if (pairs && (e = hipEventRecord(db->ev_fork, s)) != hipSuccess) return hip_fail(e, "event");
@@ -1357,6 +1359,37 @@ ModePlan mode_plan(int m, int64_t cols, const Matrix& mat, int64_t go, int64_t g
 // Global / semi-global search of one query: the packed inter-task kernel over
 // the short bins (the int32 one where 16 bits do not hold it) beside the int32
 // wavefront kernel over the long list, which starts first, as in a local search.
+// The long-pair kernel's form for a global or semi-global search and R rows a
+// lane: the profile's bytes, and values within the 16-bit range (k_pairs.hip):
+// above 0 from `base` on (a superstep's columns may lie before a lane's), and
+// below the maxima's top by the gain of the shorter side.  add -1: the long list
+// goes through the int32 kernel.
+PairForm mode_pairs(int m, int64_t longest, const Matrix& mat, int32_t go, int32_t ge, int mode,
+                    int R, ModeShape* shape) {
+  PairForm f = pair_form(mat, ge, 1);
+  if (f.add < 0) return f;
+  const int64_t max_s = max_score(mat);
+  const int64_t rows = (int64_t)(m + R - 1) / R * R;
+  const int64_t pairs = std::min(rows, longest);
+  const bool global = mode == SW_MODE_GLOBAL;
+  const int64_t base = 3 * (int64_t)go + 256 + (global ? 0 : 128 * (int64_t)ge);
+  const int64_t gain = global ? pairs * (max_s + 2 * ge) : pairs * max_s + ge * (rows + 136);
+  if (base + ge * R + gain + 512 > kDriftTop) {
+    f.add = -1;
+    return f;
+  }
+  f.top = (int32_t)(rows - m);
+  f.top_byte = f.bias + (global ? 0 : 2 * ge);
+  f.code_byte = f.bias;
+  shape->mode = mode;
+  shape->pad = f.top;
+  shape->base = (int32_t)base;
+  shape->go = go;
+  shape->ge = ge;
+  shape->m = m;
+  return f;
+}
+
 int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const Matrix& mat,
                         int32_t go, int32_t ge, int mode, int32_t* d_out, hipStream_t s) {
   hipError_t e;
@@ -1379,6 +1412,41 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
   const int64_t n_long = P.n_long;
   if ((e = db->prof2.reserve((size_t)kIntraCodes * m_pad2)) != hipSuccess)
     return fail(SW_ENOMEM, std::string("mode search scratch: ") + hipGetErrorString(e));
+  // beside the packed inter-task kernel the long list (and bins that would
+  // outlast the rest, as in a local search) goes through the long-pair kernel
+  int RR = 8, W2 = 1, grid = 0, off_bins = 0;
+  PairForm pair;
+  PairArgs pa{};
+  if (mp.R > 0) {
+    off_bins = (int)pick_offload(db, m, 4);
+    const int64_t off_pairs = off_bins > 0 ? db->d->bin_pair_end[(size_t)off_bins - 1] : 0;
+    const double pair_res = (double)db->d->long_residues +
+                            (off_bins > 0 ? (double)db->d->bin_res_cum[(size_t)off_bins] : 0.0);
+    const double inter = (double)m * ((double)db->d->n_res - pair_res);
+    const int64_t count = db->d->n_long_pairs + off_pairs;
+    const int64_t longest = off_bins > 0 || n_long > 0 ? P.max_len : 0;
+    if (count > 0) {
+      pick_pairs(db, m, (double)count, 0.5 * pair_res, (double)longest,
+                 off_bins < P.n_bins ? inter : 0.0, &RR, &W2);
+      pair = mode_pairs(m, longest, mat, go, ge, mode, RR, &pa.mode);
+    }
+    if (pair.add >= 0) {
+      pa.count = (int32_t)count;
+      pa.n_pass = (m + 64 * RR - 1) / (64 * RR);
+      pa.ring = pair_ring(pa.n_pass, W2);
+      pa.scratch_stride = pair_stride(*db->d);
+      grid = pair_grid(db, count, pa.n_pass, W2, 64.0 * RR * pa.n_pass * pair_res,
+                       off_bins < P.n_bins ? inter : 0.0);
+      const size_t words =
+          pa.n_pass > 1 ? (size_t)grid * pa.ring * (size_t)pa.scratch_stride : (size_t)1;
+      if ((e = db->prof3.reserve((size_t)kIntraCodes * (m_pad2 / 2))) != hipSuccess ||
+          (e = db->rb_long.reserve(words)) != hipSuccess)
+        return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
+    } else {
+      off_bins = 0;
+    }
+  }
+  const bool pairs = pair.add >= 0;
   if (mp.R > 0) {
     if ((e = db->prof.reserve((size_t)mp.n_strips * prof_strip_dwords(mp.R) + kProfSlack)) !=
         hipSuccess)
@@ -1393,21 +1461,40 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
   const int t_total = time_begin(db, kTimeTotal, s);
   if (mp.R > 0) {
     e = launch_profile(d_query, m, mat, db->prof.p, mp.n_strips * mp.R, mp.R, ge, mp.shape.pad,
-                       mode == SW_MODE_GLOBAL ? -2 * ge : 0, db->prof2.p, nullptr, -1, m_pad2,
-                       db->flags.p, s);
+                       mode == SW_MODE_GLOBAL ? -2 * ge : 0, db->prof2.p,
+                       pairs ? db->prof3.p : nullptr, pair, m_pad2, db->flags.p, s);
   } else {
     e = launch_mode_profile(d_query, m, mat, R32, n_strips32, db->mprof.p, db->prof2.p, m_pad2, s);
   }
   if (e != hipSuccess) return hip_fail(e, "profile kernel");
   hipStream_t bs = s;
-  if (n_long > 0) {
+  if (n_long > 0 || pairs) {
     bs = db->aux_stream;
     if ((e = hipEventRecord(db->ev_fork, s)) != hipSuccess ||
         (e = hipStreamWaitEvent(bs, db->ev_fork, 0)) != hipSuccess)
       return hip_fail(e, "stream fork");
-    int RR = 8, W2 = 1;
+  }
+  if (pairs) {
+    auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
+    pa.res = db->d->res.p;
+    pa.offs = db->d->offs.p;
+    pa.items = db->d->d_long_pairs.p;
+    pa.counter = db->flags.p + 2;    // cleared by the profile kernel
+    pa.prof = reinterpret_cast<const uint8_t*>(db->prof3.p);
+    pa.m_pad2 = m_pad2;
+    pa.shared = pairs_lds(RR, W2, pa.n_pass, true) + pairs_lds_static(W2) <= kLdsBytes;
+    pa.c2 = both(go - ge);
+    pa.ge2 = both(ge);
+    pa.bias2 = both(pair.bias);
+    pa.scratch = reinterpret_cast<uint2*>(db->rb_long.p);
+    pa.out = d_out;
+    const int tl = time_begin(db, kTimeIntra, s);
+    if ((e = launch_pairs(RR, W2, grid, pa, s)) != hipSuccess)
+      return hip_fail(e, "long-pair kernel");
+    time_end(db, tl, s);
+  } else if (n_long > 0) {
     pick_intra(db, m, 8, &RR, &W2);
-    int grid = (int)std::min<int64_t>(n_long, kIntraGridLong);
+    grid = (int)std::min<int64_t>(n_long, kIntraGridLong);
     if ((e = reserve_long_scratch(db, grid)) != hipSuccess)
       return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
     // beside the persistent packed kernel a share of the CUs, as the long pairs
@@ -1438,13 +1525,14 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
       return hip_fail(e, "intra-task kernel");
     time_end(db, tl, s);
   }
-  if (P.n_bins > 0) {
+  if (P.n_bins > off_bins) {
     const int ti = time_begin(db, kTimeInter, bs);
     if (mp.R > 0) {
       InterArgs a{};
       a.res2 = reinterpret_cast<const uint2*>(db->d->packed.p);
       a.bins = db->d->bins.p;
-      a.n_bins = (int32_t)P.n_bins;
+      a.bin_begin = off_bins;
+      a.n_bins = (int32_t)P.n_bins - off_bins;
       a.counter = db->flags.p + 1;     // cleared by the profile kernel
       a.n_strips = mp.n_strips;
       a.prof = db->prof.p;
@@ -1477,12 +1565,14 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
     if (e != hipSuccess) return hip_fail(e, "inter-task mode kernel");
     time_end(db, ti, bs);
   }
-  if (n_long > 0 && ((e = hipEventRecord(db->ev_join, bs)) != hipSuccess ||
+  if (bs != s && ((e = hipEventRecord(db->ev_join, bs)) != hipSuccess ||
                      (e = hipStreamWaitEvent(s, db->ev_join, 0)) != hipSuccess))
     return hip_fail(e, "stream join");
   time_end(db, t_total, s);
-  db->stats.inter_cells += (int64_t)m * (db->d->n_res - db->d->long_residues);
-  db->stats.intra_cells += (int64_t)m * db->d->long_residues;
+  const int64_t pair_res =
+      db->d->long_residues + (off_bins > 0 ? db->d->bin_res_cum[(size_t)off_bins] : 0);
+  db->stats.inter_cells += (int64_t)m * (db->d->n_res - pair_res);
+  db->stats.intra_cells += (int64_t)m * pair_res;
   return SW_OK;
 }
 
@@ -1667,7 +1757,7 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
   B.RRp = RRp;
   B.W2p = W2p;
   B.grid_b = db->d->n_cus * batch_workgroups_per_cu(R, W);
-  B.pair_add = form.add;
+  B.pair = form;
   B.pair_bias = form.bias;
   B.grid_long = (int)std::min<int64_t>(
       B.n_long_items, form.add >= 0 ? (int64_t)db->d->n_cus * std::max(1, 16 / W2p) : kIntraGridLong);
@@ -1710,7 +1800,7 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
                                  B.drift.group > 0 ? B.ge : -1,
                                  std::max(B.max_pair_work, B.max_query_work), B.prof.p, B.qdesc.p,
                                  B.prof2.p, B.n_long_items > 0 ? B.prof3.p : nullptr,
-                                 B.pair_add, s)) !=
+                                 B.pair, s)) !=
       hipSuccess)
     return hip_fail(e, "batch profiles");
   IntraArgs ia{};
@@ -1736,7 +1826,7 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
         (e = hipStreamWaitEvent(bs, db->ev_fork, 0)) != hipSuccess)
       return hip_fail(e, "stream fork");
     const int tl = time_begin(db, kTimeIntra, s);
-    if (B.pair_add >= 0) {
+    if (B.pair.add >= 0) {
       PairArgs pa{};
       pa.res = db->d->res.p;
       pa.offs = db->d->offs.p;

@@ -107,3 +107,40 @@ def test_segments_bins_and_batches(sw, go, ge):
             got = db.search_batch(qs, B62, go, ge)
             for row, w in zip(got, want):
                 _same(row, w, "batch")
+
+
+# global and semi-global: every sequence in the long list, queries that fill a
+# lane's rows and that leave some above them, of one pass and of many; gaps and
+# matrices up to the form's range and past it; bins handed over
+@pytest.mark.parametrize("m", [1, 3, 8, 127, 128, 130, 509, 512, 515, 1100, 2300])
+@pytest.mark.parametrize("go,ge,matrix", [(10, 2, "b62"), (0, 0, "b62"), (11, 1, "b62"),
+                                          (60, 20, "b62"), (3000, 3, "b62"), (9000, 5, "b62"),
+                                          (12, 2, "hot")])
+def test_modes(sw, m, go, ge, matrix):
+    res, offs, q = _db(m, m)
+    mat = _hot() if matrix == "hot" else B62
+    say("modes m=%d gaps %d/%d %s" % (m, go, ge, matrix))
+    for mode in ("global", "semiglobal"):
+        want = ocpu.search_mode(q, res, offs, mat, go, ge, mode)
+        for t_long, rows, off in ((1, 2, -1), (1, 4, -1), (1, 8, -1), (700, 0, 1000), (900, 0, 0)):
+            with sw.Database(res, offs, long_threshold=t_long) as db:
+                db.set_option(sw.SW_OPT_INTRA_ROWS, rows)
+                db.set_option(sw.SW_OPT_OFFLOAD_BINS, off)
+                _same(db.search_mode(q, mat, go, ge, mode), want, (mode, t_long, rows))
+
+
+# more pairs than workgroups, the automatic choice of bins handed over, and
+# sequences whose columns' drift alone passes 16 bits
+@pytest.mark.parametrize("m", [40, 700])
+def test_modes_long_sequences(sw, m):
+    rng = np.random.default_rng(m)
+    lens = np.concatenate([[34000, 33000, 20001], rng.integers(1, 2047, 1500)]).astype(np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    q = swinputs.random_residues(m, rng)
+    res[offs[0] + 30000:offs[0] + 30000 + m] = q
+    say("modes, long sequences, m=%d" % m)
+    with sw.Database(res, offs) as db:
+        for mode in ("global", "semiglobal"):
+            want = ocpu.search_mode(q, res, offs, B62, 10, 2, mode)
+            for _ in range(2):
+                _same(db.search_mode(q, B62, 10, 2, mode), want, mode)
