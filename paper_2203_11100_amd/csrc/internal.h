@@ -142,9 +142,27 @@ struct IntraArgs {
   uint8_t* dir;               // non-null (with ends): the traceback codes of every
                               // cell, item it's at dir + dir_off[it], column-major
                               // with dir_ld bytes (>= the query's padded rows) per
-                              // column; see k_intra.hip
+                              // column, kTracePad columns on either side of the
+                              // sequence's own; see k_intra.hip
   const int64_t* dir_off;
   int64_t dir_ld;
+};
+
+// Columns of traceback codes before and after a sequence's: what the lanes of a
+// wave store before their first column and after the last one.
+constexpr int kTracePad = 63;
+
+// Traceback walk (k_trace.hip), one item per workgroup.
+struct TraceWalkArgs {
+  const uint8_t* dir;         // codes, as in IntraArgs
+  const int64_t* dir_off;
+  int64_t dir_ld;
+  const int4* ends;           // {sequence, score, query end, database end}
+  uint32_t* rev;              // each item's runs, last first, at rev + rev_off[it]
+  const int64_t* rev_off;
+  int4* heads;                // {runs or -1, query begin, database begin, place in runs}
+  uint32_t* runs;             // all items' runs, (length << 2 | op), first first
+  int32_t* total;             // their number, zero at launch
 };
 
 // Global / semi-global inter-task kernel (k_modes.hip): one database
@@ -300,6 +318,8 @@ hipError_t launch_profile(const uint8_t* d_query, int m, const Matrix& mat, uint
                           int m_pad, int R, int drift, int top, int top_score, int8_t* prof2,
                           uint32_t* prof3, const PairBytes& pb, int m_pad2, int32_t* flag_count,
                           hipStream_t s);
+// R: rows per lane of the kernel that left the codes
+hipError_t launch_trace_walk(int R, int count, const TraceWalkArgs& a, hipStream_t s);
 hipError_t launch_fill(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_inter(int R, int W, int n_cus, const InterArgs& a, hipStream_t s);
 hipError_t launch_intra(int RR, int W2, int grid, const IntraArgs& a, hipStream_t s);

@@ -12,10 +12,10 @@
 // from lane l-1, which computed them in the previous step.  That exchange is
 // one cross-lane DPP move per value (wave_shr:1), with no LDS and no barrier
 // inside the wave.  Lane 0 is fed the previous pass's bottom row (H and the F
-// flowing into the next row) from a per-workgroup buffer, and the last lane's
-// bottom row is collected (wave_shl:1) for the next pass.  Residue codes and
-// the boundary row enter 64 columns at a time and move down the wave one
-// lane per step.
+// flowing into the next row) from a per-workgroup buffer and the residue codes by a
+// line of 64 columns in LDS that every lane reads, and the last lane's bottom row
+// goes to a second line, for the next pass (as in k_pairs.hip; k_intra_f16 rotates
+// them through registers).
 //
 // The W2 waves take passes round robin and run as a pipeline, like the
 // strips of the inter-task kernel: a superstep is 64 steps, wave w runs
@@ -52,8 +52,11 @@
 // reads its R rows for its own residue code, R contiguous bytes at
 // code*64R + R*l, so the 64 reads of a wave cover consecutive bytes of one
 // code row each and never conflict on banks.
+#include <type_traits>
+
 #include "internal.h"
 #include "packed16.h"
+#include "stream.h"
 
 namespace swdb {
 namespace {
@@ -130,18 +133,18 @@ __device__ __forceinline__ bool end_before(int s, int c, int r, int s2, int c2, 
 // the query's last row reads the score from the sequence's own columns in
 // the last pass.
 //
-// kVarTrace: kVarEnds plus one traceback code per cell (i, j), so that the
-// host can walk an optimal alignment back from the end: bits 0-1 say where
-// H(i, j) came from (0: it is 0, the alignment starts after this cell; 1:
-// the diagonal H(i-1, j-1) + S; 3: F(i, j); 2: E(i, j); the first that
-// equals H in the order 0, diagonal, F, E), bit 2 that E(i, j+1) comes from
-// opening a gap after H(i, j) rather than extending E(i, j), bit 3 the same
-// for F(i+1, j) (opening preferred on ties).  The clamped E and F give the
-// same choices wherever the walk can be: it enters E or F only where they
-// are positive, and a positive value never comes from a clamped 0.  Codes
-// are bytes [column][row] (row = 0-based query position), one 8-, 4- or
-// 2-byte store per lane and step for its R rows, written for the sequence's
-// own columns only.
+// kVarTrace: kVarEnds plus one traceback code per cell (i, j), from which an
+// optimal alignment can be walked back from the end (k_trace.hip): five bits, the
+// signs of d - H, F - H and 0 - H (H is the diagonal's, F's, 0, else E's: the first
+// that equals it in the order 0, diagonal, F, E) and of (H - go) - (E - ge) and
+// (H - go) - (F - ge) (E(i, j+1) and F(i+1, j) extend rather than open; opening
+// preferred on ties), each shifted in by one op, where comparing and selecting
+// took three.  The clamped E and F give the same choices wherever the walk can
+// be: it enters E or F only where they are positive, and a positive value never
+// comes from a clamped 0.  The codes of R rows (of 4, twice, for R = 8), first
+// row highest, are one word of as many bytes, [column][row] (row = 0-based query
+// position): one store per lane and step, of every lane while one of them is at a
+// column of the sequence, into the columns left free on both sides by the others.
 enum { kVarScore = 0, kVarEnds = 1, kVarGlobal = 2, kVarSemi = 3, kVarTrace = 4 };
 constexpr int kNegInf = -(1 << 29);
 
@@ -154,6 +157,8 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
   constexpr bool kLocal = V == kVarScore || kEnds;
   constexpr int ROWS = 64 * R;   // query rows per pass
   __shared__ __align__(16) int8_t lprof_all[W2][kIntraCodes * ROWS];
+  __shared__ uint4 lfeed[W2][64];       // {code offset, H, F, -} of a superstep's columns
+  __shared__ uint2 lcoll[W2][65];       // lane 63's bottom row, step by step from 1
   __shared__ int lbest[W2];
   __shared__ int lpos[kEnds ? 2 * W2 : 1];
   typedef typename ProfVec<R>::T PV;
@@ -161,6 +166,8 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int8_t* lprof = &lprof_all[w][0];
+  const int8_t* const lrows = lprof + lane * R;
+  const uint32_t coll_at = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&lcoll[w][0];
   const int count = a.count_ptr ? *a.count_ptr : a.count;
   int2* __restrict__ rb = a.scratch + (size_t)blockIdx.x * a.scratch_stride;
   const int go = a.go, ge = a.ge;
@@ -242,90 +249,131 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
         H[k] = kLocal ? 0 : -gapw(top + k + 1, go, ge);   // H(i, 0)
         E[k] = kLocal ? 0 : H[k] - go;                    // E(i, 1)
       }
-      int hdiag = kLocal ? 0 : -gapw(top, go, ge), code = SW_PAD_CODE;
-      int hbot = H[R - 1], fbot = 0;
+      uint32_t tcode[(R + 3) / 4] = {};         // kTrace: the last steps' codes
+      int hdiag = kLocal ? 0 : -gapw(top, go, ge);
+      uint32_t code = SW_PAD_CODE * ROWS;
+      int fbot = 0;
       int pbest = 0, pcol = 0, pk = 0;          // kEnds: this pass's first maximum
+      // kTrace: step t's codes go to columns t - lane, kTracePad on
+      uint8_t* dir_step = dir;
+      const uint32_t dir_lane =
+          kTrace ? (uint32_t)(kTracePad - lane) * (uint32_t)a.dir_ld + (uint32_t)top : 0u;
       for (int c = 0; c < C2; ++c) {
-        int fcode = fcode_n, fh = fh_n, ff = ff_n;
+        lfeed[w][lane] = make_uint4((uint32_t)(fcode_n * ROWS), (uint32_t)fh_n, (uint32_t)ff_n, 0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
         if (c + 1 < C2) fetch(p, c + 1);
         else if (more) fetch(p + W2, 0);
-        int collh = 0, collf = 0;
-#pragma unroll 2
-        for (int tau = 0; tau < 64; ++tau) {
-          code = shr_in(code, fcode);
-          const int hup = shr_in(hbot, fh);
-          const int fup = shr_in(fbot, ff);
-          fcode = shl_in(fcode, SW_PAD_CODE);
-          fh = shl_in(fh, 0);
-          ff = shl_in(ff, 0);
-          const PV pv = *reinterpret_cast<const PV*>(lprof + code * ROWS + lane * R);
-          int prof[R];
-          unpack_profile<R>(pv, prof);
-          int hd = hdiag;
-          hdiag = hup;
-          int F = fup;
-          const int col = c * 64 + tau - lane;    // this step's column
-          uint32_t tcode[(R + 3) / 4];             // kTrace: this step's codes
+        // the profile is read two steps and the line four steps ahead, as in
+        // the long-pair kernel (k_pairs.hip); past the line's end the first again
+        auto feed = [&](int i) { return *reinterpret_cast<const u32x3*>(&lfeed[w][i]); };
+        u32x3 f0 = feed(0), f1 = feed(1), f2 = feed(2), f3 = feed(3);
+        PV pv[2];
 #pragma unroll
-          for (int x = 0; x < (R + 3) / 4; ++x) tcode[x] = 0;
-          if (kLocal || col >= 0) {
-#pragma unroll
-            for (int k = 0; k < R; ++k) {
-              const int d = hd + prof[k];
-              const int h = imax(imax(d, E[k]), F);
-              if constexpr (kTrace) {
-                const uint32_t src = h == 0 ? 0u : h == d ? 1u : h == F ? 3u : 2u;
-                const uint32_t op = (h - go >= E[k] - ge ? 4u : 0u) | (h - go >= F - ge ? 8u : 0u);
-                tcode[k >> 2] |= (src | op) << (8 * (k & 3));
-              }
-              hd = H[k];
-              H[k] = h;
-              if constexpr (kEnds) {
-                if (h > pbest) { pbest = h; pcol = col; pk = k; }
-              } else if constexpr (kLocal) {
-                best = imax(best, h);
-              }
-              const int t = h - go;
-              if constexpr (kLocal) {
-                E[k] = imax(imax(E[k] - ge, t), 0);
-                F = imax(imax(F - ge, t), 0);
-              } else {
-                E[k] = imax(E[k] - ge, t);
-                F = imax(F - ge, t);
-              }
-            }
-          }
-          if constexpr (kTrace) {
-            if (col >= 0 && col < n) {
-              uint8_t* at = dir + (size_t)col * a.dir_ld + (size_t)top;
-              if constexpr (R == 8) {
-                *reinterpret_cast<uint2*>(at) = make_uint2(tcode[0], tcode[1]);
-              } else if constexpr (R == 4) {
-                *reinterpret_cast<uint32_t*>(at) = tcode[0];
-              } else {
-                *reinterpret_cast<uint16_t*>(at) = (uint16_t)tcode[0];
-              }
-            }
-          }
-          if constexpr (!kLocal) {
-            if (last_pass && lane == lstar && col >= 0 && col < n) {
-              int v = H[0];
-#pragma unroll
-              for (int k = 1; k < R; ++k) v = k == kstar ? H[k] : v;
-              if (V == kVarGlobal) {
-                if (col == n - 1) best = v;
-              } else {
-                best = imax(best, v);
-              }
-            }
-          }
-          hbot = H[R - 1];
-          fbot = F;
-          collh = shl_in(collh, hbot);
-          collf = shl_in(collf, fbot);
+        for (int i = 0; i < 2; ++i) {
+          code = (uint32_t)shr_in((int)code, (int)(i == 0 ? f0.x : f1.x));
+          pv[i] = *reinterpret_cast<const PV*>(lrows + code);
         }
+        uint32_t coll = coll_at, code_63 = 0;
+        for (int g = 0; g < 8; ++g) {
+          auto step = [&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            store_lane<8 * u>(1ull << 63, coll, (uint32_t)H[R - 1], (uint32_t)fbot);
+            code = (uint32_t)shr_in((int)code, (int)f2.x);
+            if (u == 5) code_63 = code;
+            const u32x3 f4 = feed((8 * g + u + 4) & 63);
+            const PV pv_n = *reinterpret_cast<const PV*>(lrows + code);
+            const int hup = shr_in(H[R - 1], (int)f0.y);
+            const int fup = shr_in(fbot, (int)f0.z);
+            __builtin_amdgcn_sched_barrier(0);
+            int prof[R];
+            unpack_profile<R>(pv[0], prof);
+            int hd = hdiag;
+            hdiag = hup;
+            int F = fup;
+            const int col = c * 64 + 8 * g + u - lane;    // this step's column
+            int top_h = 0;                           // kEnds: this step's maximum
+            if (kLocal || col >= 0) {
+#pragma unroll
+              for (int k = 0; k < R; ++k) {
+                const int d = hd + prof[k];
+                const int h = imax(imax(d, E[k]), F);
+                if constexpr (kTrace) {
+                  uint32_t& tc = tcode[k >> 2];
+                  for (int x : {d - h, F - h, -h, (h - go) - (E[k] - ge), (h - go) - (F - ge)})
+                    tc = __builtin_amdgcn_alignbit(tc, (uint32_t)x, 31);
+                }
+                hd = H[k];
+                H[k] = h;
+                if constexpr (kEnds) top_h = k == 0 ? h : imax(top_h, h);
+                else if constexpr (kLocal) best = imax(best, h);
+                const int t = h - go;
+                if constexpr (kLocal) {
+                  E[k] = imax(imax(E[k] - ge, t), 0);
+                  F = imax(imax(F - ge, t), 0);
+                } else {
+                  E[k] = imax(E[k] - ge, t);
+                  F = imax(F - ge, t);
+                }
+              }
+            }
+            if constexpr (kEnds) {
+              if (top_h > pbest) {     // seldom: a lane's maximum rises a few dozen times
+                pbest = top_h;
+                pcol = col;
+#pragma unroll
+                for (int k = R - 1; k >= 0; --k) pk = H[k] == top_h ? k : pk;
+              }
+            }
+            if constexpr (kTrace) {
+              if (64 * c + 8 * g + u < n + kTracePad) {    // uniform
+                uint8_t* at = dir_step + dir_lane;
+                if constexpr (R == 8) {
+                  *reinterpret_cast<uint2*>(at) = make_uint2(tcode[0], tcode[1]);
+                } else if constexpr (R == 4) {
+                  *reinterpret_cast<uint32_t*>(at) = tcode[0];
+                } else {
+                  *reinterpret_cast<uint16_t*>(at) = (uint16_t)tcode[0];
+                }
+              }
+              dir_step += a.dir_ld;
+            }
+            if constexpr (!kLocal) {
+              if (last_pass && lane == lstar && col >= 0 && col < n) {
+                int v = H[0];
+#pragma unroll
+                for (int k = 1; k < R; ++k) v = k == kstar ? H[k] : v;
+                if (V == kVarGlobal) {
+                  if (col == n - 1) best = v;
+                } else {
+                  best = imax(best, v);
+                }
+              }
+            }
+            fbot = F;
+            __builtin_amdgcn_sched_barrier(0);
+            pv[0] = pv[1];
+            pv[1] = pv_n;
+            f0 = f1;
+            f1 = f2;
+            f2 = f3;
+            f3 = f4;
+          };
+          step(std::integral_constant<int, 0>());
+          step(std::integral_constant<int, 1>());
+          step(std::integral_constant<int, 2>());
+          step(std::integral_constant<int, 3>());
+          step(std::integral_constant<int, 4>());
+          step(std::integral_constant<int, 5>());
+          step(std::integral_constant<int, 6>());
+          step(std::integral_constant<int, 7>());
+          coll += 64;
+        }
+        store_lane<0>(1ull << 63, coll, (uint32_t)H[R - 1], (uint32_t)fbot);
+        code = code_63;   // `code` ran two steps ahead: back to the last step's own
+        asm volatile("" ::: "memory");
+        const uint2 low = lcoll[w][lane + 1];
         const int jo = c * 64 + lane - 63;
-        if (!last_pass && jo >= 0 && jo < n) rb[jo] = make_int2(collh, collf);
+        if (!last_pass && jo >= 0 && jo < n) rb[jo] = make_int2((int)low.x, (int)low.y);
         __syncthreads();
       }
       if constexpr (kEnds) {

@@ -77,22 +77,6 @@ __device__ __forceinline__ uint32_t word_of(const uint16_t& v, int) { return v; 
 __device__ __forceinline__ uint32_t word_of(const uint32_t& v, int) { return v; }
 __device__ __forceinline__ uint32_t word_of(const uint2& v, int x) { return x ? v.y : v.x; }
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
-
-// One lane of a wave whose lanes are all active (its bit) writes x, y to LDS at byte address
-// at + off: one store between two scalar writes of the exec mask, with no branch
-// to cut the unrolled steps apart.
-template <int kOff>
-__device__ __forceinline__ void store_lane(uint64_t lane_bit, uint32_t at, uint32_t x, uint32_t y) {
-  asm volatile(
-      "s_mov_b64 exec, %0\n\t"
-      "ds_write_b64 %1, %2 offset:%3\n\t"
-      "s_mov_b64 exec, -1"
-      :
-      : "s"(lane_bit), "v"(at), "v"(u32x2{x, y}), "n"(kOff));
-}
-
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 template <int R, int W, int kForm>

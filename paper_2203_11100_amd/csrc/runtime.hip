@@ -18,7 +18,6 @@
 #include <thread>
 
 #include "cpu_scorer.h"
-#include "trace_walk.h"
 #include "internal.h"
 #include "layout.h"
 #include "packed16.h"
@@ -286,9 +285,9 @@ struct Searcher {
   DevBuf<int32_t> topk;             // top-k selection state, candidates, hit items
   DevBuf<int4> hits_stage;          // hit list of host-buffer top-k calls
   DevBuf<uint8_t> trace_dir;        // traceback codes of one group of sequences
-  DevBuf<int2> trace_items;         // {sequence, 0} of the group
-  DevBuf<int64_t> trace_off;        // each item's code offset
-  DevBuf<int4> trace_ends;          // each item's {sequence, score, query end, db end}
+  DevBuf<uint8_t> trace_in;         // its offsets and items, the runs' counter, the query
+  DevBuf<uint32_t> trace_rev;       // the walks' runs, last first
+  DevBuf<uint8_t> trace_out;        // each item's end and head, then all runs
   DevBuf<int32_t> mprof;            // int32 strip profile of global / semi-global searches
   DevBuf<int2> rb_mode;             // their boundary rows, 8 bytes per short-bin cell column
   hipStream_t own_stream = nullptr; // host-buffer calls and batch graphs
@@ -346,8 +345,8 @@ void release_searcher(Searcher* db) {
   db->out_stage.release();
   db->batch.release(); db->rb_batch.release(); db->counter.release();
   db->topk.release(); db->hits_stage.release(); db->mprof.release(); db->rb_mode.release();
-  db->trace_dir.release(); db->trace_items.release(); db->trace_off.release();
-  db->trace_ends.release();
+  db->trace_dir.release(); db->trace_in.release(); db->trace_rev.release();
+  db->trace_out.release();
   if (db->users.caller_pending) (void)hipEventSynchronize(db->ev_caller);
   db->users.caller_pending = false;
   for (hipEvent_t* e : {&db->ev_fork, &db->ev_join, &db->ev_in, &db->ev_out, &db->ev_caller,
@@ -386,7 +385,7 @@ void bind_buffers(Searcher* S) {
   S->out_stage.users = u;
   S->rb_batch.users = S->counter.users = S->flags.users = u;
   S->topk.users = S->hits_stage.users = u;
-  S->trace_dir.users = S->trace_items.users = S->trace_off.users = S->trace_ends.users = u;
+  S->trace_dir.users = S->trace_in.users = S->trace_rev.users = S->trace_out.users = u;
   S->mprof.users = S->rb_mode.users = u;
   BatchPlan& B = S->batch;
   B.pairs.users = u; B.qdesc.users = u; B.items.users = u; B.long_items.users = u;
@@ -2317,6 +2316,8 @@ namespace {
 // groups whose codes fit (one sequence alone may have up to kTraceMaxBox).
 constexpr int64_t kTraceGroupBytes = int64_t(1) << 30;
 constexpr int64_t kTraceMaxBox = int64_t(4) << 30;
+// Bytes of operation runs that come down with the ends.
+constexpr size_t kTraceFirstBytes = 32768;
 
 }  // namespace
 }  // namespace swdb
@@ -2359,48 +2360,68 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
   } else {
     int RR = 8, W2 = 1;
     pick_intra(db, query_len, 8, &RR, &W2);
-    if ((e = db->q_stage.reserve((size_t)query_len)) != hipSuccess ||
-        (e = db->prof2.reserve((size_t)kIntraCodes * ld)) != hipSuccess)
+    if ((e = db->prof2.reserve((size_t)kIntraCodes * ld)) != hipSuccess)
       return fail(SW_ENOMEM, std::string("traceback scratch: ") + hipGetErrorString(e));
-    if ((e = hipMemcpyAsync(db->q_stage.p, query, (size_t)query_len, hipMemcpyHostToDevice, s)) !=
-        hipSuccess)
-      return hip_fail(e, "query upload");
     Matrix mat;
     memcpy(mat.v, matrix, sizeof(mat.v));
-    if ((e = launch_mode_profile(db->q_stage.p, query_len, mat, 16, 0, nullptr, db->prof2.p,
-                                 (int)ld, s)) != hipSuccess)
-      return hip_fail(e, "traceback profile");
-    std::vector<uint8_t> h_dir;
     int32_t t0 = 0;
     while (t0 < n_items) {
       // a group: as many sequences as fit kTraceGroupBytes (at least one)
       int32_t t1 = t0;
-      int64_t bytes = 0;
+      int64_t bytes = 0, rev_words = 0;
       std::vector<int64_t> off;
-      std::vector<int2> items;
       while (t1 < n_items) {
-        const int64_t box = (offs[(size_t)seqs[t1] + 1] - offs[(size_t)seqs[t1]]) * ld;
+        const int64_t len = offs[(size_t)seqs[t1] + 1] - offs[(size_t)seqs[t1]];
+        const int64_t box = (len + 2 * kTracePad) * ld;
         if (t1 > t0 && bytes + box > kTraceGroupBytes) break;
         off.push_back(bytes);
-        items.push_back(make_int2(seqs[t1], 0));
         bytes += box;
+        rev_words += len + query_len + 2;
         ++t1;
       }
       const int32_t k = t1 - t0;
-      if ((e = db->trace_dir.reserve((size_t)std::max<int64_t>(bytes, 8))) != hipSuccess ||
-          (e = db->trace_items.reserve((size_t)k)) != hipSuccess ||
-          (e = db->trace_off.reserve((size_t)k)) != hipSuccess ||
-          (e = db->trace_ends.reserve((size_t)k)) != hipSuccess)
+      // one upload: code and run offsets, items, the runs' counter, the query; one
+      // download: ends, heads and the first runs (all of them but for many or
+      // long alignments)
+      const size_t items_at = 16 * (size_t)k, count_at = items_at + 8 * (size_t)k;
+      const size_t query_at = count_at + 16, in_bytes = query_at + (size_t)query_len;
+      const size_t runs_at = 32 * (size_t)k;
+      const size_t first = std::min<size_t>((size_t)rev_words * 4, kTraceFirstBytes);
+      std::vector<uint8_t> up, down;
+      try {
+        up.resize(in_bytes);
+        down.resize(runs_at + first);
+      } catch (...) {
+        return fail(SW_ENOMEM, "host allocation failed");
+      }
+      int64_t* const u_off = reinterpret_cast<int64_t*>(up.data());
+      int2* const u_items = reinterpret_cast<int2*>(up.data() + items_at);
+      int64_t rev_at = 0;
+      for (int32_t x = 0; x < k; ++x) {
+        const int32_t sid = seqs[t0 + x];
+        u_off[x] = off[(size_t)x];
+        u_off[k + x] = rev_at;
+        u_items[x] = make_int2(sid, 0);
+        rev_at += offs[(size_t)sid + 1] - offs[(size_t)sid] + query_len + 2;
+      }
+      memset(up.data() + count_at, 0, 16);
+      memcpy(up.data() + query_at, query, (size_t)query_len);
+      if ((e = db->trace_dir.reserve((size_t)bytes)) != hipSuccess ||
+          (e = db->trace_in.reserve(in_bytes)) != hipSuccess ||
+          (e = db->trace_rev.reserve((size_t)rev_words)) != hipSuccess ||
+          (e = db->trace_out.reserve(runs_at + (size_t)rev_words * 4)) != hipSuccess)
         return fail(SW_ENOMEM, std::string("traceback codes: ") + hipGetErrorString(e));
-      if ((e = hipMemcpyAsync(db->trace_items.p, items.data(), (size_t)k * sizeof(int2),
-                              hipMemcpyHostToDevice, s)) != hipSuccess ||
-          (e = hipMemcpyAsync(db->trace_off.p, off.data(), (size_t)k * sizeof(int64_t),
-                              hipMemcpyHostToDevice, s)) != hipSuccess)
-        return hip_fail(e, "traceback items");
+      uint8_t* const d_in = db->trace_in.p;
+      uint8_t* const d_res = db->trace_out.p;
+      if ((e = hipMemcpyAsync(d_in, up.data(), in_bytes, hipMemcpyHostToDevice, s)) != hipSuccess)
+        return hip_fail(e, "traceback upload");
+      if (t0 == 0 && (e = launch_mode_profile(d_in + query_at, query_len, mat, 16, 0, nullptr,
+                                              db->prof2.p, (int)ld, s)) != hipSuccess)
+        return hip_fail(e, "traceback profile");
       IntraArgs ta{};
       ta.res = db->d->res.p;
       ta.offs = db->d->offs.p;
-      ta.items = db->trace_items.p;
+      ta.items = reinterpret_cast<const int2*>(d_in + items_at);
       ta.count_ptr = nullptr;
       ta.count = k;
       ta.prof2 = db->prof2.p;
@@ -2414,62 +2435,57 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
       ta.scratch = db->rb_resc.p;
       ta.scratch_stride = rescore_stride(db->d->plan);
       ta.out = nullptr;
-      ta.ends = db->trace_ends.p;
+      ta.ends = reinterpret_cast<int4*>(d_res);
       ta.dir = db->trace_dir.p;
-      ta.dir_off = db->trace_off.p;
+      ta.dir_off = reinterpret_cast<const int64_t*>(d_in);
       ta.dir_ld = ld;
       if ((e = launch_intra(RR, W2, std::min<int>(k, kIntraGridRescore), ta, s)) != hipSuccess)
         return hip_fail(e, "traceback kernel");
-      if ((e = hipMemcpyAsync(ends.data() + t0, db->trace_ends.p, (size_t)k * sizeof(int4),
-                              hipMemcpyDeviceToHost, s)) != hipSuccess ||
+      TraceWalkArgs wa{};
+      wa.dir = ta.dir;
+      wa.dir_off = ta.dir_off;
+      wa.dir_ld = ld;
+      wa.ends = ta.ends;
+      wa.rev = db->trace_rev.p;
+      wa.rev_off = ta.dir_off + k;
+      wa.heads = ta.ends + k;
+      wa.runs = reinterpret_cast<uint32_t*>(d_res + runs_at);
+      wa.total = reinterpret_cast<int32_t*>(d_in + count_at);
+      if ((e = launch_trace_walk(RR, k, wa, s)) != hipSuccess) return hip_fail(e, "traceback walk");
+      if ((e = hipMemcpyAsync(down.data(), d_res, runs_at + first, hipMemcpyDeviceToHost, s)) !=
+              hipSuccess ||
           (e = hipStreamSynchronize(s)) != hipSuccess)
         return hip_fail(e, "traceback download");
-      // of each sequence's codes only the columns the walk can visit (up to
-      // the end's), one contiguous copy per sequence (a strided copy to
-      // pageable memory goes column by column and took ~2 ms per sequence)
-      std::vector<int64_t> hld((size_t)k, ld), hoff((size_t)k, 0);
-      int64_t hbytes = 0;
+      const int4* const heads = reinterpret_cast<const int4*>(down.data()) + k;
+      int64_t n_runs = 0;
       for (int32_t x = 0; x < k; ++x) {
-        const int4 en = ends[(size_t)(t0 + x)];
-        hoff[(size_t)x] = hbytes;
-        if (en.y > 0) hbytes += ld * ((int64_t)en.w + 1);
+        if (heads[x].x < 0) return fail(SW_EDEVICE, "traceback codes do not form a path");
+        n_runs += heads[x].x;
       }
       try {
-        h_dir.resize((size_t)std::max<int64_t>(hbytes, 1));
+        if ((size_t)n_runs * 4 > first) down.resize(runs_at + (size_t)n_runs * 4);
       } catch (...) {
         return fail(SW_ENOMEM, "host allocation failed");
       }
+      if ((size_t)n_runs * 4 > first &&
+          ((e = hipMemcpyAsync(down.data() + runs_at + first, d_res + runs_at + first,
+                               (size_t)n_runs * 4 - first, hipMemcpyDeviceToHost, s)) !=
+               hipSuccess ||
+           (e = hipStreamSynchronize(s)) != hipSuccess))
+        return hip_fail(e, "traceback download");
+      const int4* const h_ends = reinterpret_cast<const int4*>(down.data());
+      const uint32_t* const h_runs = reinterpret_cast<const uint32_t*>(down.data() + runs_at);
       for (int32_t x = 0; x < k; ++x) {
-        const int4 en = ends[(size_t)(t0 + x)];
-        if (en.y <= 0) continue;
-        if ((e = hipMemcpyAsync(h_dir.data() + hoff[(size_t)x], db->trace_dir.p + off[(size_t)x],
-                                (size_t)(ld * ((int64_t)en.w + 1)), hipMemcpyDeviceToHost, s)) !=
-            hipSuccess)
-          return hip_fail(e, "traceback download");
-      }
-      if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "traceback download");
-      // the walks, one host thread per sequence of the group
-      std::atomic<int32_t> next{0};
-      std::atomic<bool> bad{false};
-      auto work = [&]() {
-        for (int32_t x; (x = next.fetch_add(1)) < k;) {
-          const int4 en = ends[(size_t)(t0 + x)];
-          if (en.y <= 0) continue;
-          if (!walk_alignment(h_dir.data() + hoff[(size_t)x], hld[(size_t)x], en.z, en.w,
-                              &qb[(size_t)(t0 + x)], &dbb[(size_t)(t0 + x)],
-                              &runs[(size_t)(t0 + x)]))
-            bad = true;
+        const int4 hd = h_ends[k + x];
+        ends[(size_t)(t0 + x)] = h_ends[x];
+        qb[(size_t)(t0 + x)] = hd.y;
+        dbb[(size_t)(t0 + x)] = hd.z;
+        try {
+          runs[(size_t)(t0 + x)].assign(h_runs + hd.w, h_runs + hd.w + hd.x);
+        } catch (...) {
+          return fail(SW_ENOMEM, "host allocation failed");
         }
-      };
-      const int nt = std::max(1, std::min<int>(k, (int)std::thread::hardware_concurrency()));
-      std::vector<std::thread> pool;
-      try {
-        for (int x = 1; x < nt; ++x) pool.emplace_back(work);
-      } catch (...) {
       }
-      work();
-      for (auto& th : pool) th.join();
-      if (bad) return fail(SW_EDEVICE, "traceback codes do not form a path");
       t0 = t1;
     }
   }
