@@ -256,7 +256,7 @@ constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t pairs_lds(int R, int W, int n_pass, bool shared) {
   return (size_t)(shared ? n_pass : W) * kIntraCodes * 64 * R;
 }
-constexpr size_t pairs_lds_static(int W) { return (size_t)W * (1024 + 520 + 12) + 512; }
+constexpr size_t pairs_lds_static(int W) { return (size_t)W * (1024 + 1024 + 12) + 512; }
 
 // Batched inter-task kernel: the two 16-bit halves of a lane hold two
 // queries (a pair) against one database sequence.  The pair's profile has

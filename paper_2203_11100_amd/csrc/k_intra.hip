@@ -158,7 +158,7 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
   constexpr int ROWS = 64 * R;   // query rows per pass
   __shared__ __align__(16) int8_t lprof_all[W2][kIntraCodes * ROWS];
   __shared__ uint4 lfeed[W2][64];       // {code offset, H, F, -} of a superstep's columns
-  __shared__ uint2 lcoll[W2][65];       // lane 63's bottom row, step by step from 1
+  __shared__ uint2 lcoll[W2][128];      // the bottom row, as in k_pairs.hip
   __shared__ int lbest[W2];
   __shared__ int lpos[kEnds ? 2 * W2 : 1];
   typedef typename ProfVec<R>::T PV;
@@ -167,7 +167,6 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int8_t* lprof = &lprof_all[w][0];
   const int8_t* const lrows = lprof + lane * R;
-  const uint32_t coll_at = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&lcoll[w][0];
   const int count = a.count_ptr ? *a.count_ptr : a.count;
   int2* __restrict__ rb = a.scratch + (size_t)blockIdx.x * a.scratch_stride;
   const int go = a.go, ge = a.ge;
@@ -273,11 +272,12 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
           code = (uint32_t)shr_in((int)code, (int)(i == 0 ? f0.x : f1.x));
           pv[i] = *reinterpret_cast<const PV*>(lrows + code);
         }
-        uint32_t coll = coll_at, code_63 = 0;
+        uint2* coll = &lcoll[w][63 - lane];
+        uint32_t code_63 = 0;
         for (int g = 0; g < 8; ++g) {
           auto step = [&](auto uc) {
             constexpr int u = decltype(uc)::value;
-            store_lane<8 * u>(1ull << 63, coll, (uint32_t)H[R - 1], (uint32_t)fbot);
+            coll[u] = make_uint2((uint32_t)H[R - 1], (uint32_t)fbot);
             code = (uint32_t)shr_in((int)code, (int)f2.x);
             if (u == 5) code_63 = code;
             const u32x3 f4 = feed((8 * g + u + 4) & 63);
@@ -366,9 +366,9 @@ __global__ __launch_bounds__(64 * W2) void k_intra_i32(IntraArgs a) {
           step(std::integral_constant<int, 5>());
           step(std::integral_constant<int, 6>());
           step(std::integral_constant<int, 7>());
-          coll += 64;
+          coll += 8;
         }
-        store_lane<0>(1ull << 63, coll, (uint32_t)H[R - 1], (uint32_t)fbot);
+        coll[0] = make_uint2((uint32_t)H[R - 1], (uint32_t)fbot);
         code = code_63;   // `code` ran two steps ahead: back to the last step's own
         asm volatile("" ::: "memory");
         const uint2 low = lcoll[w][lane + 1];

@@ -87,7 +87,11 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
   typedef typename ByteRows<R>::T PV;
   extern __shared__ __align__(16) char lprof_all[];
   __shared__ uint4 lfeed[W][64];           // {code offsets, H, F, -} of a superstep's columns
-  __shared__ uint2 lcoll[W][65];           // lane 63's bottom row, step by step from 1
+  // the bottom row, step by step from 1.  Every lane writes, lane 63 (in general:
+  // the one whose row it is) at the step's place and the others ahead of it, where
+  // the steps to come write over them: no exec mask to change, and the compiler
+  // counts the store among the reads it waits for
+  __shared__ uint2 lcoll[W][128];
   __shared__ uint32_t lprog[W];            // each wave's progress
   __shared__ int2 lpos[W];                 // its item: {ordinal, pass}
   __shared__ int litem[kRing];             // ordinal n's entry of the list, at n % ring
@@ -265,9 +269,7 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
     uint32_t fbot = low_f;
     uint32_t score = 0;
     const int out_lane = p == P - 1 ? last_lane : 63;
-    uint64_t out_bit = 1ull << 63;
     if constexpr (!kLocal) {
-      out_bit = 1ull << uniform(out_lane);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         H[r] = left2;
@@ -297,8 +299,6 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
       if (p > 0) wait_pred(there + (uint32_t)min(2, C));
       fetch(0);
     }
-    const uint32_t coll_at =
-        (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&lcoll[w][0];
     for (int c = 0; c < C; ++c) {
       {
         const int jf = c * 64 + (int)lane;
@@ -342,16 +342,16 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
         va[i] = *reinterpret_cast<const PV*>(lb + (code & 0xffffu));
         vb[i] = *reinterpret_cast<const PV*>(lb + (code >> 16));
       }
-      uint32_t coll = coll_at, code_63 = 0;
+      uint2* coll = &lcoll[w][(out_lane - (int)lane) & 63];
+      uint32_t code_63 = 0;
       uint32_t x = 0;
       for (int g = 0; g < 8; ++g) {
         const uint32_t zg = base2 + ge2 * (uint32_t)(8 * g);
         auto step = [&](auto uc) {
           constexpr int u = decltype(uc)::value;
-          // the last step's bottom row, then this step's reads: the wait for them
-          // in the next step is then for reads alone (the compiler does not count
-          // the store), and nothing of that step may be scheduled before it
-          store_lane<8 * u>(out_bit, coll, H[R - 1], fbot);
+          // the last step's bottom row, then this step's reads; nothing of the next
+          // step may be scheduled before them
+          coll[u] = make_uint2(H[R - 1], fbot);
           code = shr_in(code, f2.x);
           if (u == 5) code_63 = code;
           const u32x3 f4 = feed((8 * g + u + 4) & 63);
@@ -404,9 +404,9 @@ __global__ __launch_bounds__(64 * W) void k_pairs(PairArgs a) {
         step(std::integral_constant<int, 5>());
         step(std::integral_constant<int, 6>());
         step(std::integral_constant<int, 7>());
-        coll += 64;
+        coll += 8;
       }
-      store_lane<0>(out_bit, coll, H[R - 1], fbot);
+      coll[0] = make_uint2(H[R - 1], fbot);
       code = code_63;   // `code` ran two steps ahead: back to the last step's own
       asm volatile("" ::: "memory");
       const uint2 low = lcoll[w][lane + 1];

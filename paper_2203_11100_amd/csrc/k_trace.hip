@@ -19,7 +19,7 @@ namespace {
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// kRows: rows a code word holds (2: 16 bits, 4: 32 bits)
+// kRows: rows a code word holds, as many bytes
 template <int kRows>
 __global__ __launch_bounds__(64) void k_trace_walk(TraceWalkArgs a) {
   __shared__ __align__(16) uint8_t tile[64 * 64];    // [column][row]

@@ -814,7 +814,7 @@ int64_t pair_stride(const DbData& d) {
 void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double longest,
                 double inter, int* R_out, int* W_out) {
   struct Cost { int R; double lat, thr; };
-  static const Cost costs[] = {{4, 276, 153}, {8, 412, 270}, {2, 250, 95}};
+  static const Cost costs[] = {{4, 260, 153}, {8, 400, 270}, {2, 215, 95}};
   const double simds = 4.0 * std::max(db->d->n_cus, 1);
   double best = 1e300;
   for (const Cost& c : costs) {

@@ -43,20 +43,6 @@ __device__ __forceinline__ void wait_progress(const uint32_t* p, uint32_t& known
   }
 }
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
-
-// One lane of a wave whose lanes are all active (its bit) writes x, y to LDS at byte address
-// at + off: one store between two scalar writes of the exec mask, with no branch
-// to cut the unrolled steps apart.
-template <int kOff>
-__device__ __forceinline__ void store_lane(uint64_t lane_bit, uint32_t at, uint32_t x, uint32_t y) {
-  asm volatile(
-      "s_mov_b64 exec, %0\n\t"
-      "ds_write_b64 %1, %2 offset:%3\n\t"
-      "s_mov_b64 exec, -1"
-      :
-      : "s"(lane_bit), "v"(at), "v"(u32x2{x, y}), "n"(kOff));
-}
 
 }  // namespace swdb
