@@ -41,8 +41,8 @@ METRIC = "GCUPS on 1 MI355X (plain vs batched/served) + p50/p99 query latency"
 # converted to bytes with the counters' readings for a 1 GiB device copy.
 # Valid only for the kernel and schedule-selection code it was taken on: bench
 # reports null when the digest of that code (comments removed) differs.
-TRAFFIC = {"bytes_per_launch": 2.2661e+10, "fetch_bytes": 57.47e9, "write_bytes": 395.74e9,
-           "launches": 20, "sources_sha256": "a249759c32e92080bf266af662cbc83bbeded4f712924ea5003a8c8b2876af53"}
+TRAFFIC = {"bytes_per_launch": 2.4847e+10, "fetch_bytes": 92.28e9, "write_bytes": 404.66e9,
+           "launches": 20, "sources_sha256": "abc21c8dc0a0cceb5b2940deee35a398ea47c176ff507f88938ccabd877416bb"}
 TRAFFIC_SOURCES = ("k_inter.hip", "packed16.h", "internal.h", "runtime.hip")
 # of runtime.hip only the schedule selection (the fitted tables and the
 # choice of rows and waves per query) shapes the inter-task kernel's traffic
@@ -55,14 +55,15 @@ PEAK_HALF_TOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 # 2 subtract (E - extend, F - extend), 2 max (new E, new F).  The roofline
 # fraction `frac` counts these 10 per cell against the packed 16-bit peak.
 OPS_PER_CELL = 10
-# Packed binary16 instructions the inter-task kernel issues per cell (half-ops
-# per cell): 1 fused multiply-add forming H_diag + S for both halves (the
-# profile dwords hold (S, 1) and (1, S)), 3 subtract and 3 three-input max for
-# the cell, 1/2 three-input max for the running maximum (two rows per op).  A
-# three-input max does two of the 10 algorithmic maxima in one issue slot, so
-# 10 ops take 7.5 slots and `frac` can exceed 1; `frac_issue` is the fraction
-# of the issue slots the kernel's own instruction count needs.
-ISSUE_PER_CELL = 7.5
+# Packed 16-bit instructions the inter-task kernel issues per cell (half-ops per
+# cell), drift form: 1 three-input addition forming H_diag + S for both halves, 2
+# three-input max (H; E with its floor), 1 subtract, 1 max (F), 1/2 three-input max
+# for the running maximum (two cells per op); gaps are extended for nothing.  A
+# three-input max does two of the 10 algorithmic maxima in one issue slot and the
+# drift takes 2 subtractions out, so 10 ops take 5.5 slots and `frac` can exceed 1;
+# `frac_issue` is the fraction of the issue slots the kernel's own instruction
+# count needs.
+ISSUE_PER_CELL = 5.5
 
 
 def code_text(src):
@@ -214,13 +215,13 @@ def main():
             "traffic": measured_traffic(),
             "traffic_unit": "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, mean over the "
                             "step's 20 launches)",
-            "kernel": "k_inter_f16 (rows, waves fitted per query; last query: %d, %d)"
+            "kernel": "k_inter (rows, waves fitted per query; last query: %d, %d)"
                       % (st["rows"], st["waves"]),
             "avg_launch_ms": st["ms_inter"] / n_launch}
     result = {
         "metric": METRIC, "value": gcups, "unit": "GCUPS", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": dt / args.steps * 1e3, "higher_is_better": True,
-        "scaling": "weak", "vs_baseline": None, "dtype": "f16+int32", "data": "synthetic",
+        "scaling": "weak", "vs_baseline": None, "dtype": "int16+int32", "data": "synthetic",
         "config": {"workload": "plain: 20 queries (144..5478 residues) vs %d synthetic "
                                "sequences (%d residues), BLOSUM62, gaps 10/2, one search per "
                                "query" % (w.n_seqs, w.n_residues),
@@ -351,12 +352,10 @@ def topk_leg(db, w, k=1000, queries=(0, 8, 19)):
     return out
 
 
-# int32 operations per cell of the global / semi-global recurrence (no floor,
-# no running maximum): 1 add, 2 max for H, 1 subtract for the open, 2
-# subtract for the extends, 2 max for E and F
+# Operations per cell of the global / semi-global recurrence (no floor, no
+# running maximum): 1 add, 2 max for H, 1 subtract for the open, 2 subtract for
+# the extends, 2 max for E and F; counted against the packed 16-bit peak
 MODE_OPS_PER_CELL = 8
-# MI355X unpacked 32-bit VALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
-PEAK_I32_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
 
 def modes_leg(db, w, queries=(0, 8, 14)):
@@ -383,9 +382,10 @@ def modes_leg(db, w, queries=(0, 8, 14)):
         achieved = inter_cells * MODE_OPS_PER_CELL / (inter_ms / 1e3) / 1e12 if inter_ms else None
         out[mode] = {"gcups": cells / ms_tot / 1e6, "ms": ms_tot,
                      "queries": [len(w.queries[i]) for i in queries],
-                     "roofline": {"bound": "alu", "kernel": "k_mode_inter", "achieved": achieved,
-                                  "peak": PEAK_I32_TOPS, "unit": "Tops/s (int32)",
-                                  "frac": achieved / PEAK_I32_TOPS if achieved else None,
+                     "roofline": {"bound": "alu", "kernel": "k_inter (mode forms; k_mode_inter past 16 bits)",
+                                  "achieved": achieved, "peak": PEAK_HALF_TOPS,
+                                  "unit": "Tops/s",
+                                  "frac": achieved / PEAK_HALF_TOPS if achieved else None,
                                   "ops_per_cell": MODE_OPS_PER_CELL}}
     log("modes: %s" % out)
     return out

@@ -17,20 +17,20 @@
  *
  * Scores are exact 32-bit integers, identical to Gotoh's H/E/F recurrence
  * evaluated in unbounded integers.  Internally most cells are computed in
- * packed IEEE half precision, which is exact for integers up to 2048; any
- * sequence whose half-precision score reaches the rescoring limit (at most
- * 2048) is rescored exactly in 32-bit integer arithmetic.  Which kernel
+ * packed 16-bit arithmetic (integers, or IEEE half precision, exact for
+ * integers up to 2048, where gap penalties do not fit the integer form); any
+ * sequence whose 16-bit score reaches the rescoring limit (at most 2048) is
+ * rescored exactly in 32-bit integer arithmetic.  Which kernel
  * scores a sequence depends on its length (paper section 2.3: inter-task or
  * intra-task parallelism depending on the sequence length):
- *  - shorter than `long_threshold`: the packed half-precision inter-task
+ *  - shorter than `long_threshold`: the packed 16-bit inter-task
  *    kernel (two sequences per lane);
  *  - single searches, at least `long_threshold`: an anti-diagonal wavefront
  *    (intra-task) kernel computing two such sequences at once in the two
- *    packed half-precision halves of every register, with the same exact
- *    rescoring;
+ *    16-bit halves of every register, with the same exact rescoring;
  *  - batched searches: sequences below 4 x `long_threshold` go through the
  *    packed batched inter-task kernel (two queries per lane), longer ones
- *    through the 32-bit intra-task kernel.
+ *    through the intra-task kernel of single searches.
  *
  * Conventions (all entry points):
  *  - Residue codes are bytes 0..23 in BLOSUM order
@@ -229,8 +229,8 @@ int sw_search_topk_async(sw_db* db, const uint8_t* d_query, int32_t query_len,
  * reports.  The exact 32-bit intra-task kernel recomputes each sequence's
  * matrix, keeping one traceback code per cell in device memory (query
  * length rounded up to 512 bytes per sequence residue; sequences go in
- * groups of up to 1 GiB of codes); the codes come back to the host, where
- * one thread per sequence walks back from the end.  Of several optimal
+ * groups of up to 1 GiB of codes), and a second kernel walks back from the
+ * end, one wave per sequence.  Of several optimal
  * alignments it returns the one that, walking back, prefers a matched pair,
  * then a query residue against a gap, then a database residue against a
  * gap, and ends a gap at the first place it can.
@@ -319,10 +319,10 @@ int sw_host_search(const uint8_t* residues, const int64_t* offsets, int64_t n_se
  *                        (the query's best placement inside each sequence).
  * Scores are exact 32-bit integers and may be negative.  Calls whose scores
  * could leave +-2^28 - gap_open + (gap_extend + 128) x (query_len + 512 +
- * longest sequence + 1024) > 2^28 - return SW_ERANGE.  Sequences shorter
- * than the long threshold run in the int32 inter-task kernel (one sequence
- * per lane), longer ones in the int32 intra-task wavefront kernel.  Buffers
- * as sw_search / sw_search_async. */
+ * longest sequence + 1024) > 2^28 - return SW_ERANGE.  Calls whose
+ * values fit 16 bits run in the packed inter-task and intra-task kernels, the
+ * others in 32-bit ones (one sequence per lane or workgroup).  Buffers as
+ * sw_search / sw_search_async. */
 enum sw_mode { SW_MODE_LOCAL = 0, SW_MODE_GLOBAL = 1, SW_MODE_SEMIGLOBAL = 2 };
 int sw_search_mode(sw_db* db, const uint8_t* query, int32_t query_len, const int8_t* matrix,
                    int32_t gap_open, int32_t gap_extend, int32_t mode, int32_t* out_scores);
@@ -339,7 +339,7 @@ const char* sw_last_error(void);
  * SW_EINVAL.  */
 enum sw_option {
   SW_OPT_TIMING = 1,      /* 0/1: record HIP events around every kernel */
-  SW_OPT_SAT_LIMIT = 2,   /* 0..32767: a sequence whose half-precision score
+  SW_OPT_SAT_LIMIT = 2,   /* 0..32767: a sequence whose 16-bit score
                              reaches min(limit, 2048) is rescored in 32-bit
                              integers (default 32767, i.e. the whole exact
                              range; 0 rescores everything) */

@@ -1,7 +1,7 @@
 // Inter-task Smith-Waterman/Gotoh kernel: every lane scores two database
 // sequences against the query (paper section 2.2: inter-task parallelism,
 // one independent alignment matrix per processing element, no communication
-// between elements), in packed half-precision arithmetic.
+// between elements), in packed 16-bit arithmetic.
 //
 // Cells follow Gotoh's recurrence over query rows i and database columns j:
 //   E(i,j) = max(E(i,j-1) - e, H(i,j-1) - o)
@@ -35,7 +35,8 @@
 // alone on it.  Bound by the VALU: on the plain database (71 M residues, m =
 // 5,478, 14 x 16) the kernel takes 38.8 ms, 85 % of the VALU's issue slots at
 // the clock the card holds (2.2 GHz); binary16 cells with barriers and one bin
-// a workgroup took 52.6 ms, drift cells alone 45.6, without the barriers 43.
+// a workgroup took 52.6 ms, drift cells alone 45.6, without the barriers 43
+// (36.7 with the long pairs in drift cells beside it).
 //
 // The query profile rows of the current strip are staged in LDS as two
 // tables (internal.h, prof_strip_dwords), one dword a row and code, for 26 codes

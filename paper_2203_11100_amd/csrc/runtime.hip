@@ -806,11 +806,13 @@ int64_t pair_stride(const DbData& d) {
 // The longest pair is a chain of its steps (two supersteps more for every
 // further pass), in rounds when its passes outnumber the waves; the rows that
 // give the shorter of chain and work win, the cheaper work where that is close
-// (977 residues against the plain database 7.3 ms with 2, 4 or 8 rows; the long
-// mix, 2,000 residues, 9.3 / 5.7 / 6.3).  Waves: 16 beside the inter-task kernel,
-// whose workgroups share a CU with no other, so that the pairs hold few CUs and
-// fill them (457 residues, 100,000 plain sequences: 2.97 ms with 4, 2.59 with
-// 16); alone as many as a pair has passes, 4 to 16, so that the pairs spread.
+// (977 residues against the plain database 7.3 ms with 4 or 8 rows; the long mix,
+// 2,000 residues, 9.3 / 5.7 / 6.0 with 2, 4, 8; 2,000 short sequences 0.19 / 0.21
+// with 2, 4).  Waves: 16 beside the inter-task kernel, whose workgroups share a CU
+// with no other, so that the pairs hold few CUs and fill them (457 residues,
+// 100,000 plain sequences: 2.96 ms with 4, 2.50 with 16); alone the fewest that
+// hold a pair's passes and, over the device, all pairs at once, so that few pairs
+// spread over the CUs.
 void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double longest,
                 double inter, int* R_out, int* W_out) {
   struct Cost { int R; double lat, thr; };

@@ -83,7 +83,7 @@ class VirtualClock:
 
 def request_bytes(n_seqs: int, query_len: int) -> int:
     """Device bytes one request holds while launched: its int32 score row,
-    its query codes, and its profiles (the binary16 pair profile, 26 codes x
+    its query codes, and its profiles (the 16-bit pair profile, 26 codes x
     4 bytes per row, and the 32-bit kernel's int8 profile, 25 codes per row
     padded to 512 rows)."""
     return 4 * n_seqs + query_len + 104 * (query_len + 32) + 25 * (query_len + 512)
