@@ -808,11 +808,15 @@ int64_t pair_stride(const DbData& d) {
 // give the shorter of chain and work win, the cheaper work where that is close
 // (977 residues against the plain database 7.3 ms with 4 or 8 rows; the long mix,
 // 2,000 residues, 9.3 / 5.7 / 6.0 with 2, 4, 8; 2,000 short sequences 0.19 / 0.21
-// with 2, 4).  Waves: 16 beside the inter-task kernel, whose workgroups share a CU
-// with no other, so that the pairs hold few CUs and fill them (457 residues,
-// 100,000 plain sequences: 2.96 ms with 4, 2.50 with 16); alone the fewest that
-// hold a pair's passes and, over the device, all pairs at once, so that few pairs
-// spread over the CUs.
+// with 2, 4).  Waves: alone the fewest that hold a pair's passes and, over the
+// device, all pairs at once, so that few pairs spread over the CUs.  Beside the
+// inter-task kernel, whose workgroups share a CU with no other, 16, so that the
+// pairs hold few CUs and fill them (457 residues, 100,000 plain sequences: 2.96 /
+// 2.70 / 2.50 ms with 4, 8, 16; 144 and 200,000: 1.176 ms with 16, 1.191 with 8), but
+// 8 where the longest pair is what the search waits for - its chain clearly longer
+// than the bins and than twice the pairs' steps spread over the device - and its
+// waves then share their SIMDs with fewer others (47 residues, 3,083 sequences of the
+// long mix: 0.57 ms with 16, 0.43 with 8; 80 and 6,322: 0.59, 0.46).
 void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double longest,
                 double inter, int* R_out, int* W_out) {
   struct Cost { int R; double lat, thr; };
@@ -822,8 +826,12 @@ void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double l
   for (const Cost& c : costs) {
     if (db->opt_intra_rows && c.R != db->opt_intra_rows) continue;
     const int P = (m + 64 * c.R - 1) / (64 * c.R);
-    int W = inter > 0 ? 16 : 1;
-    while (W < 16 && (W < P || (double)W * std::max(db->d->n_cus, 1) < n_pairs * P)) W *= 2;
+    const double beside = inter / 128.0 * 27.0 / simds;
+    const bool waits = cols * P / simds < 0.5 * longest && longest * c.lat > 1.4 * beside;
+    int W = inter <= 0 ? 1 : waits ? 8 : 16;
+    while (W < 16 && (W < P || (inter <= 0 &&
+                                (double)W * std::max(db->d->n_cus, 1) < n_pairs * P)))
+      W *= 2;
     if (db->opt_intra_waves) W = db->opt_intra_waves;
     auto fits = [&](int w) {
       return std::min(pairs_lds(c.R, w, P, true), pairs_lds(c.R, w, P, false)) +
@@ -834,7 +842,7 @@ void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double l
     const double chain = (longest + 128.0 * (at_once - 1)) * ((P + W - 1) / W) *
                          std::max(c.lat, std::max(1.0, at_once / 4.0) * c.thr);
     const double work = cols * P * c.thr / simds / 0.85;
-    const double all = work + inter / 128.0 * 27.0 / simds;
+    const double all = work + beside;
     const double est = std::max(chain, all) + 0.1 * chain + 0.5 * work;
     if (est < best) { best = est; *R_out = c.R; *W_out = W; }
   }
