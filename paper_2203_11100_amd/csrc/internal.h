@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/swdb.h"
+#include "plans.h"
 
 namespace swdb {
 
@@ -15,11 +16,6 @@ struct BinDesc {
   int64_t slot0;     // index of the bin's first slot in slot_seq
 };
 static_assert(sizeof(BinDesc) == 32, "BinDesc must match the 4 x int64 host layout");
-
-// Scoring matrix passed by value to the profile kernel.
-struct Matrix {
-  int8_t v[SW_ALPHA * SW_ALPHA];
-};
 
 // Profile rows: 26 codes per query row (codes 0..23, the pad code 24, one
 // spare), one dword per row and code.  Rows are stored in pairs, code-major
@@ -43,13 +39,6 @@ constexpr int kProfSlack = 256;
 // Score given to padding (pad code, and query rows past the end).  Any value
 // <= 0 keeps padded cells from raising a maximum.
 constexpr int kPadScore = -64;
-// Intra-task profile (int8, [code][row]) has the 24 codes plus the pad code.
-constexpr int kIntraCodes = 25;
-
-// The packed inter-task kernels compute in IEEE binary16, which holds every
-// integer of magnitude <= 2048 exactly.
-constexpr int kHalfExact = 2048;
-
 // binary16 bit pattern of an integer n with |n| <= kHalfExact (exact).
 __host__ __device__ constexpr uint16_t half_bits(int n) {
   const unsigned a = n < 0 ? (unsigned)-n : (unsigned)n;
@@ -62,31 +51,9 @@ static_assert(half_bits(1) == 0x3c00 && half_bits(-64) == 0xd400 && half_bits(20
                   half_bits(11) == 0x4980 && half_bits(0) == 0,
               "binary16 encodings");
 
-// The parameters of a drift sweep (packed16.h), the same in both halves of
-// each word; group = 0: the binary16 form is used instead.
 // Words before the rescoring list's entries: its count, the work counters of the
 // single search's bins and pairs, one spare.
 constexpr int kFlagWords = 4;
-
-struct DriftArgs {
-  int32_t group;              // strips until the drift starts again at its base
-  int32_t guard;              // values need the guard to stay in range
-  uint32_t c2;                // gap_open - gap_extend, at most 2048
-  uint32_t ge2;               // the drift of one row or column
-  uint32_t group2;            // the drift of a group's rows
-  uint32_t lim2, over2;       // the rescoring limit; 32768 - the limit
-};
-
-// A global or semi-global search in the drift form (k_inter.hip): H~ = H + base
-// + ge * (row + column), the query's rows shifted down so that its last row is
-// the last strip's last.
-struct ModeShape {
-  int32_t mode;               // SW_MODE_LOCAL: the fields below are not used
-  int32_t pad;                // rows above the query's first, < R
-  int32_t base;
-  int32_t go, ge, m;
-  const int64_t* offs;        // sequence offsets
-};
 
 struct InterArgs {
   const uint2* res2;          // interleaved store viewed as (lo, hi) dword pairs
@@ -216,14 +183,6 @@ struct IntraPairArgs {
 
 // Long-pair kernel in the drift form (k_pairs.hip); items, segments and batches
 // as in IntraPairArgs.
-// The long-pair kernel's profile: bytes S + add of a query's rows, shifted down by `top` rows of top_byte; add -1: not the byte form.
-struct PairBytes {
-  int32_t add = -1;
-  int32_t top = 0, top_byte = 0;
-  int32_t code_byte = 0;      // the pad code's
-  int32_t row_byte = 0;       // of rows past the query's end
-};
-
 struct PairArgs {
   const uint8_t* res;         // contiguous residues, original order
   const int64_t* offs;
@@ -250,13 +209,6 @@ struct PairArgs {
   const QueryDesc* queries;   // prof3_off in bytes
   ModeShape mode;             // global and semi-global: whole pairs of one query
 };
-
-// LDS of one workgroup of the long-pair kernel: profiles (dynamic) and the rest.
-constexpr size_t kLdsBytes = 160 * 1024;
-constexpr size_t pairs_lds(int R, int W, int n_pass, bool shared) {
-  return (size_t)(shared ? n_pass : W) * kIntraCodes * 64 * R;
-}
-constexpr size_t pairs_lds_static(int W) { return (size_t)W * (1024 + 1024 + 12) + 512; }
 
 // Batched inter-task kernel: the two 16-bit halves of a lane hold two
 // queries (a pair) against one database sequence.  The pair's profile has

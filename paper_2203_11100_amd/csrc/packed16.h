@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plans.h"
+
 namespace swdb {
 
 typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
@@ -206,8 +208,6 @@ __device__ __forceinline__ void sweep_chunk_ahead(uint32_t (&H)[R], uint32_t (&E
 // cell left and below of it), two cells an op, in place, and an anti-diagonal
 // that has reached row 0 is complete and enters `best` less its Z.
 enum { kCellHalf = 0, kCellDrift = 1, kCellGlobal = 2, kCellSemi = 3 };   // cell forms
-constexpr uint32_t kDriftBase = 2560;
-constexpr int kDriftTop = 31743;      // the largest value the maxima order as integers
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 as_u2(uint32_t a) { return __builtin_bit_cast(u16x2, a); }

@@ -1,0 +1,237 @@
+// The rules by which the host chooses the packed kernels' forms and launches:
+// ranges of 16-bit values, profile bytes, workgroups and their row buffers.
+// Plain C++, so that CPU tests compile and call them.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "../../include/swdb.h"
+
+namespace swdb {
+
+// Scoring matrix passed by value to the profile kernel.
+struct Matrix {
+  int8_t v[SW_ALPHA * SW_ALPHA];
+};
+
+// Intra-task profile (int8, [code][row]) has the 24 codes plus the pad code.
+constexpr int kIntraCodes = 25;
+
+// The packed inter-task kernels compute in IEEE binary16, which holds every
+// integer of magnitude <= 2048 exactly.
+constexpr int kHalfExact = 2048;
+
+// Values of the drift form (packed16.h): what they start from, and the largest
+// one the maxima order as integers.
+constexpr uint32_t kDriftBase = 2560;
+constexpr int kDriftTop = 31743;
+
+// Matrices (ordinals) whose results are being gathered in one workgroup at
+// once: the wave that would start one further ahead waits for the oldest to be
+// finished.  At least as many as a workgroup has waves, so that queries of a
+// single strip keep every wave busy.
+constexpr int kRing = 16;
+
+// The parameters of a drift sweep (packed16.h), the same in both halves of
+// each word; group = 0: the binary16 form is used instead.
+struct DriftArgs {
+  int32_t group;              // strips until the drift starts again at its base
+  int32_t guard;              // values need the guard to stay in range
+  uint32_t c2;                // gap_open - gap_extend, at most 2048
+  uint32_t ge2;               // the drift of one row or column
+  uint32_t group2;            // the drift of a group's rows
+  uint32_t lim2, over2;       // the rescoring limit; 32768 - the limit
+};
+
+// A global or semi-global search in the drift form (k_inter.hip): H~ = H + base
+// + ge * (row + column), the query's rows shifted down so that its last row is
+// the last strip's last.
+struct ModeShape {
+  int32_t mode;               // SW_MODE_LOCAL: the fields below are not used
+  int32_t pad;                // rows above the query's first, < R
+  int32_t base;
+  int32_t go, ge, m;
+  const int64_t* offs;        // sequence offsets
+};
+
+// The long-pair kernel's profile: bytes S + add of a query's rows, shifted down
+// by `top` rows of top_byte; add -1: not the byte form.
+struct PairBytes {
+  int32_t add = -1;
+  int32_t top = 0, top_byte = 0;
+  int32_t code_byte = 0;      // the pad code's
+  int32_t row_byte = 0;       // of rows past the query's end
+};
+
+// LDS of one workgroup of the long-pair kernel: profiles (dynamic) and the rest.
+constexpr size_t kLdsBytes = 160 * 1024;
+constexpr size_t pairs_lds(int R, int W, int n_pass, bool shared) {
+  return (size_t)(shared ? n_pass : W) * kIntraCodes * 64 * R;
+}
+constexpr size_t pairs_lds_static(int W) { return (size_t)W * (1024 + 1024 + 12) + 512; }
+
+// Rescoring limit of the packed kernels: the requested limit, at most 2048,
+// below which every value is computed exactly (packed16.h).
+inline int32_t effective_limit(int32_t requested) {
+  return std::max<int32_t>(0, std::min<int32_t>(requested, kHalfExact));
+}
+
+// The matrix's largest score, at least 0.
+inline int max_score(const Matrix& mat) {
+  int max_s = 0;
+  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) max_s = std::max<int>(max_s, mat.v[x]);
+  return max_s;
+}
+
+// The drift form's parameters for a kernel whose bins have at most `cols`
+// columns and whose strips have R rows (the arithmetic and the meaning of the
+// range: packed16.h), or group = 0 where it does not fit and the binary16 form
+// is used: gap_extend so large that the drift over the columns and one strip
+// leaves no room (above 12 at 2,048 columns and the default limit).  The drift over the rows starts
+// again every `group` strips, as many as fit (all of a usual query's).
+// Batches give the columns of the short bins too: the groups are then sized so
+// that these need no guard where that leaves at least 8 strips, and the kernel
+// guards the matrices that do.
+inline DriftArgs drift_plan(int m, int64_t cols, int R, const Matrix& mat, int32_t go, int32_t ge,
+                     int32_t sat_limit, int64_t short_cols = 0) {
+  DriftArgs d{};
+  const int64_t limit = effective_limit(sat_limit);
+  const int max_s = max_score(mat);
+  // room for the drift of columns and rows, when scores stay below what the
+  // lengths allow, or (guard) within some columns' gain of the limit
+  const int64_t top = kDriftTop - (int64_t)kDriftBase - 256;
+  auto score = [&](int64_t n) {
+    return std::max<int64_t>(std::min<int64_t>((m + R - 1) / R * R, n) * max_s, limit);
+  };
+  const int64_t guarded = limit + (int64_t)(R + 8) * max_s;
+  auto groups = [&](int64_t highest, int64_t n) -> int64_t {
+    if (highest > top) return 0;
+    if (ge == 0) return INT32_MAX / R;
+    return ((top - highest) / ge - n - R - 8) / R;
+  };
+  int64_t g = groups(score(cols), cols);
+  if (g < 1) {
+    g = groups(guarded, cols);
+    d.guard = 1;
+    const int64_t gs = short_cols > 0 ? groups(score(short_cols), short_cols) : 0;
+    if (gs >= 8) g = std::min(g, gs);
+  }
+  if (g < 1) return DriftArgs{};
+  d.group = (int32_t)std::min<int64_t>(g, (m + R - 1) / R);
+  auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
+  d.c2 = both(std::min<int32_t>(go - ge, kHalfExact));
+  d.ge2 = both(ge);
+  d.group2 = both((int64_t)ge * R * d.group);
+  d.lim2 = both(limit);
+  d.over2 = both(32768 - limit);
+  return d;
+}
+
+// The long-pair kernel's drift form (k_pairs.hip) for one set of scores: `add`
+// is what its profile bytes hold beside S (2 ge + bias), -1 where the form does
+// not fit - the drift of a superstep and two supersteps' gain past the limit
+// within the 16-bit range, scores within a byte - and k_intra_f16 is used.
+struct PairForm : PairBytes {
+  int bias = 0;
+};
+inline PairForm pair_form(const Matrix& mat, int32_t ge, int32_t sat_limit) {
+  PairForm f;
+  int lo = 0, hi = 0;
+  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) {
+    lo = std::min<int>(lo, mat.v[x]);
+    hi = std::max<int>(hi, mat.v[x]);
+  }
+  const int64_t top = (int64_t)kDriftBase + effective_limit(sat_limit) + 140 * (int64_t)hi +
+                      (int64_t)ge * (64 + 2 * 8 + 8) + 512;
+  const int bias = std::max(0, -(lo + 2 * std::min(ge, 1024)));
+  if (top > kDriftTop || hi + 2 * (int64_t)ge + bias > 255) return f;
+  f.bias = bias;
+  f.add = 2 * ge + bias;
+  f.code_byte = f.row_byte = lo + f.add;     // the smallest score, or 0
+  return f;
+}
+
+// Pairs one workgroup holds at once: each keeps a row buffer when it has more
+// than one pass.
+inline int pair_ring(int n_pass, int W) {
+  return n_pass > 1 ? std::min(kRing, (W + n_pass - 1) / n_pass + 1) : kRing;
+}
+
+// A global or semi-global search's inter-task form: the packed drift kernel
+// (k_inter.hip) where every value stays within 16 bits, else R = 0 and the int32
+// kernel.  Values lie above base - 2 go (borders, and gaps from them) and below
+// base plus what the cells of a path can gain: max S + 2 ge for each of at most
+// min(rows, columns) matched pairs from the corner (global), or max S + ge from
+// anywhere on the top border, which itself rises to ge * columns (semi-global).
+// BLOSUM62 with gaps 10/2 fits for every query up to 2,047 columns.
+struct ModePlan {
+  int R = 0, W = 0, n_strips = 0;
+  ModeShape shape{};
+};
+inline ModePlan mode_plan(int m, int64_t cols, const Matrix& mat, int64_t go, int64_t ge, int mode) {
+  ModePlan p;
+  const int64_t max_s = max_score(mat);
+  // padded rows over relative rate, as for batches
+  struct Form {
+    int R, W;
+    double eff;
+  };
+  static const Form forms[] = {{16, 16, 1.0}, {14, 16, 0.98}, {12, 16, 0.95}};
+  double best = 1e300;
+  for (const Form& c : forms) {
+    const double cost = (double)((m + c.R - 1) / c.R * c.R) / c.eff;
+    if (cost < best) { best = cost; p.R = c.R; p.W = c.W; }
+  }
+  p.n_strips = (m + p.R - 1) / p.R;
+  const int64_t rows = (int64_t)p.n_strips * p.R;
+  const int64_t base = 3 * go + 256;
+  const int64_t pairs = std::min<int64_t>(rows, cols);
+  const int64_t gain = mode == SW_MODE_GLOBAL ? pairs * (max_s + 2 * ge)
+                                              : pairs * (max_s + ge) + ge * cols;
+  if (base + ge * p.R + gain + 512 > kDriftTop || cols > kDriftTop) {
+    p.R = 0;
+    return p;
+  }
+  p.shape.mode = mode;
+  p.shape.pad = (int32_t)(rows - m);
+  p.shape.base = (int32_t)base;
+  p.shape.go = (int32_t)go;
+  p.shape.ge = (int32_t)ge;
+  p.shape.m = m;
+  return p;
+}
+
+// The long-pair kernel's form for a global or semi-global search and R rows a
+// lane: the profile's bytes, and values within the 16-bit range (k_pairs.hip):
+// above 0 from `base` on (a superstep's columns may lie before a lane's), and
+// below the maxima's top by the gain of the shorter side.  add -1: the long list
+// goes through the int32 kernel.
+inline PairForm mode_pairs(int m, int64_t longest, const Matrix& mat, int32_t go, int32_t ge, int mode,
+                    int R, ModeShape* shape) {
+  PairForm f = pair_form(mat, ge, 1);
+  if (f.add < 0) return f;
+  const int64_t max_s = max_score(mat);
+  const int64_t rows = (int64_t)(m + R - 1) / R * R;
+  const int64_t pairs = std::min(rows, longest);
+  const bool global = mode == SW_MODE_GLOBAL;
+  const int64_t base = 3 * (int64_t)go + 256 + (global ? 0 : 128 * (int64_t)ge);
+  const int64_t gain = global ? pairs * (max_s + 2 * ge) : pairs * max_s + ge * (rows + 136);
+  if (base + ge * R + gain + 512 > kDriftTop) {
+    f.add = -1;
+    return f;
+  }
+  f.top = (int32_t)(rows - m);
+  f.top_byte = f.bias + (global ? 0 : 2 * ge);
+  f.code_byte = f.bias;
+  shape->mode = mode;
+  shape->pad = f.top;
+  shape->base = (int32_t)base;
+  shape->go = go;
+  shape->ge = ge;
+  shape->m = m;
+  return f;
+}
+
+}  // namespace swdb

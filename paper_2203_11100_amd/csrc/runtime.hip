@@ -609,63 +609,6 @@ uint32_t half_pair(int32_t g) {
   return h | (h << 16);
 }
 
-// Rescoring limit of the half-precision kernels: the requested limit, at
-// most 2048, below which every value is computed exactly (packed16.h).
-int32_t effective_limit(int32_t requested) {
-  return std::max<int32_t>(0, std::min<int32_t>(requested, kHalfExact));
-}
-
-// The matrix's largest score, at least 0.
-int max_score(const Matrix& mat) {
-  int max_s = 0;
-  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) max_s = std::max<int>(max_s, mat.v[x]);
-  return max_s;
-}
-
-// The drift form's parameters for a kernel whose bins have at most `cols`
-// columns and whose strips have R rows (the arithmetic and the meaning of the
-// range: packed16.h), or group = 0 where it does not fit and the binary16 form
-// is used: gap_extend so large that the drift over the columns and one strip
-// leaves no room (above 13 at 2,048 columns).  The drift over the rows starts
-// again every `group` strips, as many as fit (all of a usual query's).
-// Batches give the columns of the short bins too: the groups are then sized so
-// that these need no guard where that leaves at least 8 strips, and the kernel
-// guards the matrices that do.
-DriftArgs drift_plan(int m, int64_t cols, int R, const Matrix& mat, int32_t go, int32_t ge,
-                     int32_t sat_limit, int64_t short_cols = 0) {
-  DriftArgs d{};
-  const int64_t limit = effective_limit(sat_limit);
-  const int max_s = max_score(mat);
-  // room for the drift of columns and rows, when scores stay below what the
-  // lengths allow, or (guard) within some columns' gain of the limit
-  const int64_t top = kDriftTop - (int64_t)kDriftBase - 256;
-  auto score = [&](int64_t n) {
-    return std::max<int64_t>(std::min<int64_t>((m + R - 1) / R * R, n) * max_s, limit);
-  };
-  const int64_t guarded = limit + (int64_t)(R + 8) * max_s;
-  auto groups = [&](int64_t highest, int64_t n) -> int64_t {
-    if (highest > top) return 0;
-    if (ge == 0) return INT32_MAX / R;
-    return ((top - highest) / ge - n - R - 8) / R;
-  };
-  int64_t g = groups(score(cols), cols);
-  if (g < 1) {
-    g = groups(guarded, cols);
-    d.guard = 1;
-    const int64_t gs = short_cols > 0 ? groups(score(short_cols), short_cols) : 0;
-    if (gs >= 8) g = std::min(g, gs);
-  }
-  if (g < 1) return DriftArgs{};
-  d.group = (int32_t)std::min<int64_t>(g, (m + R - 1) / R);
-  auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
-  d.c2 = both(std::min<int32_t>(go - ge, kHalfExact));
-  d.ge2 = both(ge);
-  d.group2 = both((int64_t)ge * R * d.group);
-  d.lim2 = both(limit);
-  d.over2 = both(32768 - limit);
-  return d;
-}
-
 // Row length of a query's intra-task profiles: a whole number of the
 // largest pass (64 lanes x 8 rows), so every (R, W2) can read them.
 int intra_rows_pad(int m) { return (m + 511) / 512 * 512; }
@@ -706,30 +649,6 @@ int32_t hit_overlap(const DbData& d, int m, const Matrix& mat, int32_t ge) {
   if (ge <= 0) return -1;
   const int64_t reach = window_reach(m, mat, ge);
   return (int64_t)d.plan.max_len > (int64_t)d.seg_cols + reach ? (int32_t)reach : -1;
-}
-
-// The long-pair kernel's drift form (k_pairs.hip) for one set of scores: `add`
-// is what its profile bytes hold beside S (2 ge + bias), -1 where the form does
-// not fit - the drift of a superstep and two supersteps' gain past the limit
-// within the 16-bit range, scores within a byte - and k_intra_f16 is used.
-struct PairForm : PairBytes {
-  int bias = 0;
-};
-PairForm pair_form(const Matrix& mat, int32_t ge, int32_t sat_limit) {
-  PairForm f;
-  int lo = 0, hi = 0;
-  for (int x = 0; x < SW_ALPHA * SW_ALPHA; ++x) {
-    lo = std::min<int>(lo, mat.v[x]);
-    hi = std::max<int>(hi, mat.v[x]);
-  }
-  const int64_t top = (int64_t)kDriftBase + effective_limit(sat_limit) + 140 * (int64_t)hi +
-                      (int64_t)ge * (64 + 2 * 8 + 8) + 512;
-  const int bias = std::max(0, -(lo + 2 * std::min(ge, 1024)));
-  if (top > kDriftTop || hi + 2 * (int64_t)ge + bias > 255) return f;
-  f.bias = bias;
-  f.add = 2 * ge + bias;
-  f.code_byte = f.row_byte = lo + f.add;     // the smallest score, or 0
-  return f;
 }
 
 // Schedule of one single-query search: inter-task strips (R rows, W waves),
@@ -907,12 +826,6 @@ int pair_grid(const Searcher* db, int64_t count, int n_pass, int W, double pair_
     grid = std::min<int64_t>(grid, (int64_t)(kPairShare * tp / (tp + ti) * cus * 4 / W) + 1);
   }
   return (int)std::max<int64_t>(grid, 1);
-}
-
-// Pairs one workgroup holds at once: each keeps a row buffer when it has more
-// than one pass.
-int pair_ring(int n_pass, int W) {
-  return n_pass > 1 ? std::min(kRing, (W + n_pass - 1) / n_pass + 1) : kRing;
 }
 
 // Device scratch of one single-query search.
@@ -1325,80 +1238,9 @@ int64_t mode_bound(const Searcher* db, int64_t m, int64_t go, int64_t ge) {
   return go + (ge + 128) * (m + 512 + (int64_t)db->d->plan.max_len + 1024);
 }
 
-// A global or semi-global search's inter-task form: the packed drift kernel
-// (k_inter.hip) where every value stays within 16 bits, else R = 0 and the int32
-// kernel.  Values lie above base - 2 go (borders, and gaps from them) and below
-// base plus what the cells of a path can gain: max S + 2 ge for each of at most
-// min(rows, columns) matched pairs from the corner (global), or max S + ge from
-// anywhere on the top border, which itself rises to ge * columns (semi-global).
-// BLOSUM62 with gaps 10/2 fits for every query up to 2,047 columns.
-struct ModePlan {
-  int R = 0, W = 0, n_strips = 0;
-  ModeShape shape{};
-};
-ModePlan mode_plan(int m, int64_t cols, const Matrix& mat, int64_t go, int64_t ge, int mode) {
-  ModePlan p;
-  const int64_t max_s = max_score(mat);
-  // padded rows over relative rate, as for batches
-  static const Sched forms[] = {{16, 16, 1.0}, {14, 16, 0.98}, {12, 16, 0.95}};
-  double best = 1e300;
-  for (const Sched& c : forms) {
-    const double cost = (double)((m + c.R - 1) / c.R * c.R) / c.eff;
-    if (cost < best) { best = cost; p.R = c.R; p.W = c.W; }
-  }
-  p.n_strips = (m + p.R - 1) / p.R;
-  const int64_t rows = (int64_t)p.n_strips * p.R;
-  const int64_t base = 3 * go + 256;
-  const int64_t pairs = std::min<int64_t>(rows, cols);
-  const int64_t gain = mode == SW_MODE_GLOBAL ? pairs * (max_s + 2 * ge)
-                                              : pairs * (max_s + ge) + ge * cols;
-  if (base + ge * p.R + gain + 512 > kDriftTop || cols > kDriftTop) {
-    p.R = 0;
-    return p;
-  }
-  p.shape.mode = mode;
-  p.shape.pad = (int32_t)(rows - m);
-  p.shape.base = (int32_t)base;
-  p.shape.go = (int32_t)go;
-  p.shape.ge = (int32_t)ge;
-  p.shape.m = m;
-  return p;
-}
-
 // Global / semi-global search of one query: the packed inter-task kernel over
 // the short bins (the int32 one where 16 bits do not hold it) beside the int32
 // wavefront kernel over the long list, which starts first, as in a local search.
-// The long-pair kernel's form for a global or semi-global search and R rows a
-// lane: the profile's bytes, and values within the 16-bit range (k_pairs.hip):
-// above 0 from `base` on (a superstep's columns may lie before a lane's), and
-// below the maxima's top by the gain of the shorter side.  add -1: the long list
-// goes through the int32 kernel.
-PairForm mode_pairs(int m, int64_t longest, const Matrix& mat, int32_t go, int32_t ge, int mode,
-                    int R, ModeShape* shape) {
-  PairForm f = pair_form(mat, ge, 1);
-  if (f.add < 0) return f;
-  const int64_t max_s = max_score(mat);
-  const int64_t rows = (int64_t)(m + R - 1) / R * R;
-  const int64_t pairs = std::min(rows, longest);
-  const bool global = mode == SW_MODE_GLOBAL;
-  const int64_t base = 3 * (int64_t)go + 256 + (global ? 0 : 128 * (int64_t)ge);
-  const int64_t gain = global ? pairs * (max_s + 2 * ge) : pairs * max_s + ge * (rows + 136);
-  if (base + ge * R + gain + 512 > kDriftTop) {
-    f.add = -1;
-    return f;
-  }
-  f.top = (int32_t)(rows - m);
-  f.top_byte = f.bias + (global ? 0 : 2 * ge);
-  f.code_byte = f.bias;
-  shape->mode = mode;
-  shape->pad = f.top;
-  shape->base = (int32_t)base;
-  shape->go = go;
-  shape->ge = ge;
-  shape->m = m;
-  return f;
-}
-
 int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const Matrix& mat,
                         int32_t go, int32_t ge, int mode, int32_t* d_out, hipStream_t s) {
   hipError_t e;

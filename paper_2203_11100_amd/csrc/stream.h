@@ -6,14 +6,10 @@
 #include <stdint.h>
 
 #include "../../include/swdb.h"
+#include "plans.h"
 
 namespace swdb {
 
-// Matrices (ordinals) whose results are being gathered in one workgroup at
-// once: the wave that would start one further ahead waits for the oldest to be
-// finished.  At least as many as a workgroup has waves, so that queries of a
-// single strip keep every wave busy.
-constexpr int kRing = 16;
 // A wave's progress: its item's number in the bits from kProgBits up (modulo
 // 2^9), finished chunks below.  Compared by signed difference: a wave is at most
 // kRing items ahead of the one that waits for it.

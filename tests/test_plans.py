@@ -1,0 +1,130 @@
+"""The host's rules for the packed kernels (csrc/plans.h), compiled and called:
+which calls the 16-bit forms take, and that at the edge of the rules every value
+of the recurrence stays where the kernels' maxima order integers."""
+import numpy as np
+import pytest
+
+import plans_shim as plans
+import swinputs
+from test_drift_cells import drift_plan
+
+B62 = swinputs.blosum62()
+DNA = swinputs.dna_matrix(5, 4, -2)
+TOP, GLOBAL, SEMI = 31743, 1, 2
+
+
+def _hot():
+    mat = np.random.default_rng(5).integers(-128, 1, (24, 24)).astype(np.int8)
+    mat[np.arange(24), np.arange(24)] = 127
+    return mat
+
+
+def test_drift_rule_is_the_one_the_cell_model_checks():
+    rng = np.random.default_rng(1)
+    for _ in range(4000):
+        mat = (B62, DNA, _hot())[int(rng.integers(3))]
+        m, cols = int(rng.integers(1, 6000)), int(rng.choice([96, 400, 2048, 8192, 20000]))
+        ge = int(rng.choice([0, 1, 2, 4, 10, 12, 13, 14, 28, 100]))
+        go = ge + int(rng.choice([0, 8, 3000]))
+        limit, R = int(rng.choice([0, 40, 2048])), int(rng.choice([12, 14, 16, 20, 32]))
+        got = plans.drift(m, cols, R, mat, go, ge, limit)
+        group, guard = drift_plan(m, cols, R, mat, go, ge, limit)
+        assert got["group"] == group
+        if group:
+            assert bool(got["guard"]) == guard
+            assert got["c2"] == min(go - ge, 2048) * 0x10001
+            assert got["group2"] == (ge * R * group) * 0x10001 and ge * R * group < 65536
+
+
+def test_drift_edge_at_the_default_limit():
+    for R in (12, 14, 16, 18, 20):
+        for m in (100, 700, 5000):
+            assert plans.drift(m, 2048, R, B62, 12, 12)["group"] >= 1
+            assert plans.drift(m, 2048, R, B62, 13, 13)["group"] == 0
+
+
+def test_pair_bytes_hold_every_score():
+    for mat in (B62, DNA, _hot(), np.full((24, 24), -128, np.int8)):
+        lo, hi = int(mat.min()), int(mat.max())
+        for limit in (0, 2048):
+            for ge in list(range(0, 140)) + [1000, 5000, 100000]:
+                f = plans.pair(mat, ge, limit)
+                if f["add"] < 0:
+                    continue
+                assert 0 <= lo + f["add"] and hi + f["add"] <= 255
+                assert f["add"] == 2 * ge + f["bias"] and 0 <= f["code_byte"] <= 255
+                # a superstep's drift and what a score past the limit can gain
+                assert 2560 + min(limit, 2048) + 136 * max(hi, 0) + ge * 88 <= TOP
+    assert plans.pair(B62, 122)["add"] >= 0 and plans.pair(B62, 123)["add"] < 0
+
+
+def _values(q, b, matrix, go, ge, mode, base, pad, pad_score, lanes=None):
+    """Every 16-bit value of a global or semi-global matrix in its drift frame:
+    base + ge * (row + column), the query's rows behind `pad` rows of the top
+    border; b holds -1 where the sequence has ended.  lanes = R: the long-pair
+    kernel's frame, in which (semi-global) the columns count from the superstep."""
+    m, n = len(q), len(b)
+    neg = -(1 << 40)
+    w = lambda k: go + (k - 1) * ge if k > 0 else 0                     # noqa: E731
+    H = np.array([-w(j) if mode == GLOBAL else 0 for j in range(n + 1)], np.int64)
+    F = np.full(n + 1, neg, np.int64)
+    cols = np.arange(n)
+    low, high, c = [], [], go - ge
+    for i in range(1, m + 1):
+        row = i - 1 + pad
+        off = (cols + row // lanes % 64) // 64 * 64 if lanes and mode == SEMI else 0
+        tilde = lambda x, r=row: x + base + ge * (r + cols - off)       # noqa: E731
+        sc = np.where(b >= 0, matrix[q[i - 1], np.maximum(b, 0)].astype(np.int64), pad_score)
+        F = np.maximum(F - ge, H - go)                                  # F(i, j)
+        d = H[:-1] + sc
+        h = np.empty(n + 1, np.int64)
+        h[0] = -w(i)                                                    # H(i, 0)
+        # E(i, j) = max over k < j of H(i, k) - go - (j - k - 1) ge, where opening a
+        # gap after a cell that came from E never pays
+        g = np.concatenate([h[:1], np.maximum(d, F[1:])])
+        e = np.maximum.accumulate(g + ge * np.arange(n + 1))[:-1] - go - ge * cols
+        h[1:] = np.maximum(g[1:], e)
+        for x in (tilde(d), tilde(h[1:]), tilde(h[1:]) - c, tilde(F[1:]), tilde(e)):
+            low.append(int(x.min()))
+            high.append(int(x.max()))
+        H = h
+    return min(low), max(high)
+
+
+def _worst(matrix, m, n, rng):
+    """Query and sequences that gain, and lose, the most."""
+    a, b = np.unravel_index(int(np.argmax(matrix)), matrix.shape)
+    x, y = np.unravel_index(int(np.argmin(matrix)), matrix.shape)
+    yield np.full(m, a), np.full(n, b)
+    yield np.full(m, x), np.full(n, y)
+    yield np.full(m, a), np.concatenate([np.full(n // 2, b), np.full(n - n // 2, -1)])
+    yield rng.integers(0, 20, m), rng.integers(0, 20, n)
+
+
+def _edge(ok, lo, hi):
+    """The largest value in [lo, hi] for which ok holds (ok(lo) does)."""
+    while lo < hi:
+        mid = (lo + hi + 1) // 2
+        lo, hi = (mid, hi) if ok(mid) else (lo, mid - 1)
+    return lo
+
+
+# calls at the last query length, and with the last opening penalty, that the
+# rule still gives to the packed forms
+@pytest.mark.parametrize("mode", [GLOBAL, SEMI])
+@pytest.mark.parametrize("go,ge,matrix,cols", [(10, 2, "b62", 700), (40, 10, "b62", 400),
+                                               (12, 2, "hot", 260), (9, 0, "dna", 300)])
+def test_mode_values_stay_in_range(mode, go, ge, matrix, cols):
+    mat = {"b62": B62, "dna": DNA, "hot": _hot()}[matrix]
+    rng = np.random.default_rng(go)
+    strips = lambda m, g=go: plans.mode(m, cols, mat, g, ge, mode)["R"] > 0             # noqa: E731
+    wave = lambda m, g=go, R=4: plans.mode_pairs(m, cols, mat, g, ge, mode, R)["add"] >= 0  # noqa: E731
+    for ok, lanes, pad_score in ((strips, None, -64), (wave, 4, -2 * ge)):
+        m = _edge(ok, 1, 600)
+        g = _edge(lambda v: ok(m, v), go, 31000)
+        for gap in (go, g):
+            p = (plans.mode_pairs(m, cols, mat, gap, ge, mode, 4) if lanes
+                 else plans.mode(m, cols, mat, gap, ge, mode))
+            for q, b in _worst(mat, m, cols, rng):
+                lo, hi = _values(q, b, mat, gap, ge, mode, p["base"], p["pad"], pad_score, lanes)
+                assert 0 <= lo and hi <= TOP, (m, gap, lanes, lo, hi)
