@@ -159,6 +159,35 @@ inline int pair_ring(int n_pass, int W) {
   return n_pass > 1 ? std::min(kRing, (W + n_pass - 1) / n_pass + 1) : kRing;
 }
 
+// The row buffers of a launch of the long-pair kernel over `items` pairs (or
+// segments, or pairs times queries) of `stride` columns at most: `ring` for each
+// of `grid` workgroups, for the workgroups that are launched and no others.  Fewer
+// pairs in flight, down to one, where all of them would take more than 512 MiB and
+// more than one row for each of the items or 1,024 (what k_intra_f16 takes, and the
+// binary16 searches took: at 2^24 residues a row has 134 MB); with `have` rows
+// given instead, what fits in those.
+constexpr int kIntraGridLong = 1024;   // workgroups sweeping the long list
+constexpr int64_t kPairRowBytes = int64_t(512) << 20;
+struct PairRows {
+  int ring = 1, grid = 1;
+  int64_t rows = 0;           // all of them; none for queries of one pass
+};
+inline PairRows pair_rows(int ring, int grid, int n_pass, int64_t items, int64_t stride,
+                          int64_t have = -1) {
+  PairRows r;
+  r.ring = ring;
+  r.grid = grid;
+  if (n_pass <= 1) return r;
+  const int64_t most = std::max<int64_t>(
+      1, have >= 0 ? have
+                   : std::max<int64_t>(std::min<int64_t>(items, kIntraGridLong),
+                                       kPairRowBytes / (8 * std::max<int64_t>(stride, 1))));
+  while (r.ring > 1 && (int64_t)r.ring * r.grid > most) --r.ring;
+  r.grid = (int)std::min<int64_t>(r.grid, std::max<int64_t>(1, most / r.ring));
+  r.rows = (int64_t)r.ring * r.grid;
+  return r;
+}
+
 // A global or semi-global search's inter-task form: the packed drift kernel
 // (k_inter.hip) where every value stays within 16 bits, else R = 0 and the int32
 // kernel.  Values lie above base - 2 go (borders, and gaps from them) and below

@@ -107,7 +107,6 @@ struct DevBuf {
   }
 };
 
-constexpr int kIntraGridLong = 1024;   // workgroups sweeping the long list
 constexpr int kIntraGridRescore = 512; // workgroups sweeping the rescoring list
 
 }  // namespace
@@ -126,7 +125,7 @@ struct BatchPlan {
   int n_pairs = 0;
   int64_t n_items = 0, n_long_items = 0, max_pair_work = 0, max_query_work = 0;
   int64_t inter_cells = 0, intra_cells = 0;
-  int grid_b = 0, grid_long = 0;
+  int grid_b = 0, grid_long = 0, ring_long = 0;
   swdb::DriftArgs drift{};
   swdb::PairBytes pair;               // the long-pair kernel's form (pair_form)
   int pair_bias = 0;
@@ -659,6 +658,8 @@ struct SearchShape {
   PairForm pair;
   int32_t overlap;            // column segments' reach (seg_overlap), -1: whole pairs
   int64_t off_bins;   // the longest short bins handed to the long-pair kernel
+  int64_t items, stride;      // the long-pair kernel's items, columns of a row buffer
+  int n_pass, grid;           // and its launch: passes, workgroups
 };
 
 // Rates of the search kernels on a 256-CU MI355X (cells per second),
@@ -767,48 +768,6 @@ void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double l
   }
 }
 
-SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t ge) {
-  const DbData& D = *db->d;
-  SearchShape sh{};
-  sh.R = kDefaultRows;
-  sh.W = kDefaultWaves;
-  pick_schedule(db, m, &sh.R, &sh.W);
-  sh.m_pad = (m + sh.R - 1) / sh.R * sh.R;
-  sh.n_strips = sh.m_pad / sh.R;
-  sh.RR = 8; sh.W2 = 1; sh.RRr = 8; sh.W2r = 1;
-  sh.overlap = D.plan.n_long > 0 ? seg_overlap(D, m, mat, ge) : -1;
-  sh.pair = pair_form(mat, ge, db->sat_limit);
-  const int b = tune_bucket(m);
-  if (sh.pair.add < 0) {
-    pick_intra(db, m, 8, &sh.RR, &sh.W2, true);   // long sequences, in pairs (binary16)
-  } else if (db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves) {
-    sh.RR = db->tune_irows[b];
-    sh.W2 = db->tune_iwaves[b];
-  }
-  sh.off_bins = pick_offload(db, m, sh.pair.add < 0 ? sh.RR : 4);
-  if (sh.pair.add >= 0 && !(db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves)) {
-    const double off_res = sh.off_bins > 0 ? (double)D.bin_res_cum[(size_t)sh.off_bins] : 0.0;
-    const double off_pairs = sh.off_bins > 0 ? (double)D.bin_pair_end[(size_t)sh.off_bins - 1] : 0.0;
-    double n_items = (double)D.n_long_pairs, cols = 0.5 * (double)D.long_residues;
-    double longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
-    if (sh.overlap >= 0) {
-      n_items = (double)D.n_seg_items;
-      cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
-      longest = std::min<double>(longest, std::max<double>((double)D.seg_cols + sh.overlap,
-                                                          off_pairs > 0 ? D.plan.max_short_len : 0));
-    }
-    pick_pairs(db, m, n_items + off_pairs, cols + 0.5 * off_res, longest,
-               (double)m * ((double)(D.n_res - D.long_residues) - off_res), &sh.RR, &sh.W2);
-  }
-  // exact rescoring (usually a few sequences, each the only one on its CU,
-  // so the latency of one sequence is what counts)
-  pick_intra(db, m, 8, &sh.RRr, &sh.W2r);
-  // the intra-task profiles serve every intra-task launch of the query (long
-  // list, rescoring, hit ends): pad to the largest pass, 64 x 8 rows
-  sh.m_pad2 = intra_rows_pad(m);
-  return sh;
-}
-
 // Workgroups of a pair launch over `count` items of n_pass passes: enough waves
 // for all passes, at most what the device holds.  Beside the persistent
 // inter-task kernel (inter cells, pair rows * residues) the pairs take
@@ -826,6 +785,54 @@ int pair_grid(const Searcher* db, int64_t count, int n_pass, int W, double pair_
     grid = std::min<int64_t>(grid, (int64_t)(kPairShare * tp / (tp + ti) * cus * 4 / W) + 1);
   }
   return (int)std::max<int64_t>(grid, 1);
+}
+
+// offload: short bins may be handed to the long-pair kernel
+SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t ge, bool offload) {
+  const DbData& D = *db->d;
+  SearchShape sh{};
+  sh.R = kDefaultRows;
+  sh.W = kDefaultWaves;
+  pick_schedule(db, m, &sh.R, &sh.W);
+  sh.m_pad = (m + sh.R - 1) / sh.R * sh.R;
+  sh.n_strips = sh.m_pad / sh.R;
+  sh.RR = 8; sh.W2 = 1; sh.RRr = 8; sh.W2r = 1;
+  sh.overlap = D.plan.n_long > 0 ? seg_overlap(D, m, mat, ge) : -1;
+  sh.pair = pair_form(mat, ge, db->sat_limit);
+  const int b = tune_bucket(m);
+  if (sh.pair.add < 0) {
+    pick_intra(db, m, 8, &sh.RR, &sh.W2, true);   // long sequences, in pairs (binary16)
+  } else if (db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves) {
+    sh.RR = db->tune_irows[b];
+    sh.W2 = db->tune_iwaves[b];
+  }
+  sh.off_bins = offload ? pick_offload(db, m, sh.pair.add < 0 ? sh.RR : 4) : 0;
+  const double off_res = sh.off_bins > 0 ? (double)D.bin_res_cum[(size_t)sh.off_bins] : 0.0;
+  const int64_t off_pairs = sh.off_bins > 0 ? D.bin_pair_end[(size_t)sh.off_bins - 1] : 0;
+  const double inter = (double)m * ((double)(D.n_res - D.long_residues) - off_res);
+  sh.items = (sh.overlap >= 0 ? D.n_seg_items : D.n_long_pairs) + off_pairs;
+  sh.stride = sh.overlap >= 0 ? seg_stride(D) : pair_stride(D);
+  if (sh.pair.add >= 0 && !(db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves)) {
+    double cols = 0.5 * (double)D.long_residues;
+    double longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
+    if (sh.overlap >= 0) {
+      cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
+      longest = std::min<double>(longest, std::max<double>((double)D.seg_cols + sh.overlap,
+                                                          off_pairs > 0 ? D.plan.max_short_len : 0));
+    }
+    pick_pairs(db, m, (double)sh.items, cols + 0.5 * off_res, longest, inter, &sh.RR, &sh.W2);
+  }
+  sh.n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
+  sh.grid = pair_grid(db, sh.items, sh.n_pass, sh.W2,
+                      64.0 * sh.RR * sh.n_pass * ((double)D.long_residues + off_res),
+                      D.plan.n_bins > sh.off_bins ? inter : 0.0);
+  // exact rescoring (usually a few sequences, each the only one on its CU,
+  // so the latency of one sequence is what counts)
+  pick_intra(db, m, 8, &sh.RRr, &sh.W2r);
+  // the intra-task profiles serve every intra-task launch of the query (long
+  // list, rescoring, hit ends): pad to the largest pass, 64 x 8 rows
+  sh.m_pad2 = intra_rows_pad(m);
+  return sh;
 }
 
 // Device scratch of one single-query search.
@@ -874,7 +881,7 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
                            const BinRunner* bins = nullptr);
 
 // The searcher's own scratch for a query of this shape, grown as needed.
-int reserve_search_scratch(Searcher* db, const SearchShape& sh, int m, SearchScratch* X) {
+int reserve_search_scratch(Searcher* db, const SearchShape& sh, SearchScratch* X) {
   hipError_t e;
   const int64_t n_long = db->d->plan.n_long;
   const int64_t off_pairs = sh.off_bins > 0 ? db->d->bin_pair_end[(size_t)sh.off_bins - 1] : 0;
@@ -893,19 +900,13 @@ int reserve_search_scratch(Searcher* db, const SearchShape& sh, int m, SearchScr
       (e = db->seg_best.reserve((size_t)(db->d->n_seg_items + off_pairs))) != hipSuccess)
     return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
   if (pairs) {
-    size_t words = std::max<size_t>(
-        {(size_t)std::max(grid_long, 1) * (size_t)pair_stride(*db->d),
-         (size_t)grid_seg * (size_t)seg_stride(*db->d), 1});
-    if (sh.pair.add >= 0) {
-      const int n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
-      const bool seg = sh.overlap >= 0;
-      const int64_t count = (seg ? db->d->n_seg_items : db->d->n_long_pairs) + off_pairs;
-      const int grid = std::min<int64_t>(count, (int64_t)db->d->n_cus * std::max(1, 16 / sh.W2));
-      words = n_pass > 1 ? (size_t)grid * pair_ring(n_pass, sh.W2) *
-                               (size_t)(seg ? seg_stride(*db->d) : pair_stride(*db->d))
-                         : 1;
-    }
-    if ((e = db->rb_long.reserve(words)) != hipSuccess)
+    const size_t words =
+        sh.pair.add >= 0
+            ? (size_t)pair_rows(pair_ring(sh.n_pass, sh.W2), sh.grid, sh.n_pass, sh.items, sh.stride)
+                      .rows * (size_t)sh.stride
+            : std::max<size_t>((size_t)std::max(grid_long, 1) * (size_t)pair_stride(*db->d),
+                               (size_t)grid_seg * (size_t)seg_stride(*db->d));
+    if ((e = db->rb_long.reserve(std::max<size_t>(words, 1))) != hipSuccess)
       return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
     X->long_words = words;
   }
@@ -931,9 +932,9 @@ int enqueue_search(Searcher* db, const uint8_t* d_query, int32_t m, const Matrix
     e = launch_fill(d_out, db->d->n_seqs, 0, s);
     return e == hipSuccess ? SW_OK : hip_fail(e, "fill");
   }
-  const SearchShape sh = search_shape(db, m, mat, ge);
+  const SearchShape sh = search_shape(db, m, mat, ge, true);
   SearchScratch X;
-  const int rc = reserve_search_scratch(db, sh, m, &X);
+  const int rc = reserve_search_scratch(db, sh, &X);
   if (rc != SW_OK) return rc;
   return enqueue_search_kernels(db, sh, X, d_query, m, mat, go, ge, d_out, s);
 }
@@ -953,7 +954,7 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   // handed-over pair one segment; the longest short bins go to the pair
   // kernel as pairs (pick_offload; the bin runners' searches hand none over)
   const int32_t overlap = sh.overlap;
-  const bool segmented = overlap >= 0 && X.seg_best && X.grid_seg > 0;
+  const bool segmented = overlap >= 0;
   const int off_bins = (int)std::min<int64_t>(std::max<int64_t>(sh.off_bins, 0), n_bins);
   const int64_t off_pairs = off_bins > 0 ? db->d->bin_pair_end[(size_t)off_bins - 1] : 0;
   const bool pairs = n_long > 0 || off_pairs > 0;
@@ -1022,26 +1023,18 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   // stream beside the bins on the auxiliary one
   auto run_pairs = [&]() -> int {
     if (!pairs) return SW_OK;
-    const int64_t count = (segmented ? db->d->n_seg_items : db->d->n_long_pairs) + off_pairs;
-    const int n_pass = (m + 64 * RR - 1) / (64 * RR);
-    const int64_t stride = segmented ? seg_stride(*db->d) : pair_stride(*db->d);
-    const double pair_res = (double)db->d->long_residues +
-                            (off_bins > 0 ? (double)db->d->bin_res_cum[(size_t)off_bins] : 0.0);
-    const int want = pair_grid(db, count, n_pass, W2, 64.0 * RR * n_pass * pair_res,
-                               n_bins > off_bins ? (double)m * ((double)db->d->n_res - pair_res)
-                                                 : 0.0);
     const int tl = time_begin(db, kTimeIntra, s);
     if (sh.pair.add >= 0) {
       PairArgs pa{};
       pa.res = db->d->res.p;
       pa.offs = db->d->offs.p;
       pa.items = db->d->d_long_pairs.p;
-      pa.count = (int32_t)count;
+      pa.count = (int32_t)sh.items;
       pa.counter = X.flags + 2;
       pa.prof = reinterpret_cast<const uint8_t*>(X.prof3);
       pa.m_pad2 = m_pad2;
-      pa.n_pass = n_pass;
-      pa.shared = pairs_lds(RR, W2, n_pass, true) + pairs_lds_static(W2) <= kLdsBytes;
+      pa.n_pass = sh.n_pass;
+      pa.shared = pairs_lds(RR, W2, sh.n_pass, true) + pairs_lds_static(W2) <= kLdsBytes;
       auto both = [](int64_t v) { return (uint32_t)v | ((uint32_t)v << 16); };
       pa.c2 = both(std::min<int32_t>(go - ge, kHalfExact));
       pa.ge2 = both(ge);
@@ -1049,16 +1042,12 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
       pa.sat_limit = effective_limit(db->sat_limit);
       pa.lim2 = both(pa.sat_limit);
       pa.over2 = both(32768 - pa.sat_limit);
-      // the row buffers there are: fewer pairs in flight, then fewer workgroups
-      pa.ring = pair_ring(n_pass, W2);
-      int grid = want;
-      if (n_pass > 1) {
-        const int64_t rows = std::max<int64_t>(1, (int64_t)X.long_words / stride);
-        while (pa.ring > 1 && (int64_t)pa.ring * grid > rows) --pa.ring;
-        grid = (int)std::min<int64_t>(grid, std::max<int64_t>(1, rows / pa.ring));
-      }
+      const PairRows rows =     // in the buffers there are
+          pair_rows(pair_ring(sh.n_pass, W2), sh.grid, sh.n_pass, sh.items, sh.stride,
+                    (int64_t)X.long_words / sh.stride);
+      pa.ring = rows.ring;
       pa.scratch = reinterpret_cast<uint2*>(X.rb_long);
-      pa.scratch_stride = stride;
+      pa.scratch_stride = sh.stride;
       pa.out = d_out;
       pa.flag_count = X.flags;
       pa.flag_list = flist;
@@ -1068,26 +1057,26 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
         pa.seg_overlap = overlap;
         pa.seg_best = X.seg_best;
       }
-      e = launch_pairs(RR, W2, grid, pa, s);
+      e = launch_pairs(RR, W2, rows.grid, pa, s);
     } else {
       IntraPairArgs la{};
       la.res = db->d->res.p;
       la.offs = db->d->offs.p;
       la.items = db->d->d_long_pairs.p;
-      la.count = (int32_t)count;
+      la.count = (int32_t)sh.items;
       la.prof3 = X.prof3;
       la.m_pad2 = m_pad2;
-      la.n_pass = n_pass;
+      la.n_pass = sh.n_pass;
       la.go2 = half_pair(go);
       la.ge2 = half_pair(ge);
       la.sat_limit = effective_limit(db->sat_limit);
       la.scratch = X.rb_long;
-      la.scratch_stride = stride;
+      la.scratch_stride = sh.stride;
       la.out = d_out;
       la.flag_count = X.flags;
       la.flag_list = flist;
       int grid = std::min<int>(segmented ? X.grid_seg : X.grid_long, la.count);
-      if (n_bins > off_bins) grid = std::min(grid, want);
+      if (n_bins > off_bins) grid = std::min(grid, sh.grid);
       if (segmented) {
         la.seg_items = db->d->d_seg_items.p;
         la.seg_cols = db->d->seg_cols;
@@ -1097,7 +1086,7 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
       e = launch_intra_pairs(RR, W2, grid, la, s);
     }
     if (e != hipSuccess) return hip_fail(e, "intra-task kernel");
-    db->stats.long_items = (int32_t)count;
+    db->stats.long_items = (int32_t)sh.items;
     db->stats.long_overlap = segmented ? overlap : -1;
     if (segmented &&
         (e = launch_long_combine(db->d->d_long_pairs.p, db->d->d_pair_seg0.p,
@@ -1284,12 +1273,15 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
     if (pair.add >= 0) {
       pa.count = (int32_t)count;
       pa.n_pass = (m + 64 * RR - 1) / (64 * RR);
-      pa.ring = pair_ring(pa.n_pass, W2);
       pa.scratch_stride = pair_stride(*db->d);
-      grid = pair_grid(db, count, pa.n_pass, W2, 64.0 * RR * pa.n_pass * pair_res,
-                       off_bins < P.n_bins ? inter : 0.0);
-      const size_t words =
-          pa.n_pass > 1 ? (size_t)grid * pa.ring * (size_t)pa.scratch_stride : (size_t)1;
+      const PairRows rows = pair_rows(
+          pair_ring(pa.n_pass, W2),
+          pair_grid(db, count, pa.n_pass, W2, 64.0 * RR * pa.n_pass * pair_res,
+                    off_bins < P.n_bins ? inter : 0.0),
+          pa.n_pass, count, pa.scratch_stride);
+      pa.ring = rows.ring;
+      grid = rows.grid;
+      const size_t words = (size_t)std::max<int64_t>(rows.rows * pa.scratch_stride, 1);
       if ((e = db->prof3.reserve((size_t)kIntraCodes * (m_pad2 / 2))) != hipSuccess ||
           (e = db->rb_long.reserve(words)) != hipSuccess)
         return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
@@ -1612,13 +1604,16 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
   B.pair_bias = form.bias;
   B.grid_long = (int)std::min<int64_t>(
       B.n_long_items, form.add >= 0 ? (int64_t)db->d->n_cus * std::max(1, 16 / W2p) : kIntraGridLong);
+  const PairRows long_rows = pair_rows(form.add >= 0 ? kBatchRing : 1, B.grid_long, 2, B.n_long_items,
+                                       db->d->plan.max_long_len);
+  B.grid_long = long_rows.grid;
+  B.ring_long = long_rows.ring;
   if ((e = db->rb_batch.reserve((size_t)B.grid_b * (size_t)(db->d->plan.max_all_bin_len / 4) * 128)) !=
           hipSuccess ||
       (e = db->counter.reserve(2)) != hipSuccess ||
       (e = reserve_flags(db, ((db->d->plan.n_bins + db->d->plan.n_long_bins) * (int64_t)SW_BIN_SEQS +
                               db->d->plan.n_vlong) * std::max(n_nz, 1))) != hipSuccess ||
-      (e = reserve_long_scratch(db, std::max(B.grid_long, 1) * (form.add >= 0 ? kBatchRing : 1))) !=
-          hipSuccess)
+      (e = reserve_long_scratch(db, (int)long_rows.rows)) != hipSuccess)
     return fail(SW_ENOMEM, std::string("batch scratch: ") + hipGetErrorString(e));
   B.qoffs = qv;
   B.mat = mat;
@@ -1696,7 +1691,7 @@ int enqueue_batch_kernels(Searcher* db, hipStream_t s) {
       pa.sat_limit = effective_limit(B.sat_limit);
       pa.lim2 = both(pa.sat_limit);
       pa.over2 = both(32768 - pa.sat_limit);
-      pa.ring = kBatchRing;
+      pa.ring = B.ring_long;
       pa.scratch = reinterpret_cast<uint2*>(db->rb_long.p);
       pa.scratch_stride = std::max<int64_t>(db->d->plan.max_long_len, 1);
       pa.out = B.d_out;
@@ -2502,10 +2497,9 @@ static int impl_search_hybrid(swdb::Searcher* db, const uint8_t* query, int32_t 
   // kernel): the host takes sequences from the back of the same order
   Matrix mat;
   memcpy(mat.v, matrix, sizeof(mat.v));
-  SearchShape sh = search_shape(db, query_len, mat, gap_extend);
-  sh.off_bins = 0;
+  const SearchShape sh = search_shape(db, query_len, mat, gap_extend, false);
   SearchScratch X;
-  if ((rc = reserve_search_scratch(db, sh, query_len, &X)) != SW_OK) return rc;
+  if ((rc = reserve_search_scratch(db, sh, &X)) != SW_OK) return rc;
 
   // the plan: expected time of the short bins with both sides working, the
   // host's expected share, and the deadline by which a host thread must be
@@ -2767,8 +2761,7 @@ static int impl_search_async_noalloc(swdb::Searcher* db, const uint8_t* d_query,
   // sized for the long list only
   Matrix mat;
   memcpy(mat.v, matrix, sizeof(mat.v));
-  SearchShape sh = search_shape(db, query_len, mat, gap_extend);
-  sh.off_bins = 0;
+  const SearchShape sh = search_shape(db, query_len, mat, gap_extend, false);
   NoAllocLayout L;
   if ((rc = noalloc_layout(db, sh, base, &L)) != SW_OK) return rc;
   // the short bins in chunks whose boundary rows fit the 96 MiB part; each

@@ -40,6 +40,14 @@ void p_mode_pairs(int m, int64_t longest, const int8_t* v, int go, int ge, int m
   out[6] = s.base;
   out[7] = s.pad;
 }
+// {ring, grid, rows}
+void p_rows(int ring, int grid, int n_pass, int64_t items, int64_t stride, int64_t have, int64_t* out) {
+  const PairRows r = pair_rows(ring, grid, n_pass, items, stride, have);
+  out[0] = r.ring;
+  out[1] = r.grid;
+  out[2] = r.rows;
+}
+int p_ring(int n_pass, int W) { return pair_ring(n_pass, W); }
 }
 """
 _lib = None
@@ -94,3 +102,10 @@ def mode_pairs(m, longest, matrix, go, ge, mode, R):
     lib().p_mode_pairs(m, _i64(longest), _mat(matrix), go, ge, mode, R,
                        out.ctypes.data_as(ctypes.c_void_p))
     return dict(zip(PAIR + ("base", "pad"), out.tolist()))
+
+
+def rows(n_pass, W, grid, items, stride, have=-1):
+    out = np.zeros(3, np.int64)
+    lib().p_rows(lib().p_ring(n_pass, W), grid, n_pass, _i64(items), _i64(stride), _i64(have),
+                 out.ctypes.data_as(ctypes.c_void_p))
+    return dict(zip(("ring", "grid", "rows"), out.tolist()))

@@ -144,3 +144,26 @@ def test_modes_long_sequences(sw, m):
             want = ocpu.search_mode(q, res, offs, B62, 10, 2, mode)
             for _ in range(2):
                 _same(db.search_mode(q, B62, 10, 2, mode), want, mode)
+
+
+# a long pair's row buffers: for the workgroups that are launched, and never more
+# than a row for each pair (what the binary16 form takes) or half a gigabyte
+def test_row_buffers_stay_small(sw):
+    import torch
+    rng = np.random.default_rng(9)
+    lens = np.concatenate([[400_000], np.full(500, 2100)]).astype(np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    q = swinputs.random_residues(1000, rng)
+    most = max(251 * 400_000 * 8, 512 << 20) + (96 << 20)       # and profiles, flags, stages
+    with sw.Database(res, offs) as db:
+        for what, call in (("search", lambda: db.search(q, B62, 10, 2)),
+                           ("global", lambda: db.search_mode(q, B62, 10, 2, "global")),
+                           ("batch", lambda: db.search_batch([q, q[:900]], B62, 10, 2))):
+            torch.cuda.synchronize()
+            before = torch.cuda.mem_get_info()[0]
+            got = call()
+            used = before - torch.cuda.mem_get_info()[0]
+            say("rows of %s: %d MiB" % (what, used >> 20))
+            assert used <= most, (what, used)
+            if what == "search":
+                _same(got, ocpu.search(q, res, offs, B62, 10, 2), what)

@@ -128,3 +128,25 @@ def test_mode_values_stay_in_range(mode, go, ge, matrix, cols):
             for q, b in _worst(mat, m, cols, rng):
                 lo, hi = _values(q, b, mat, gap, ge, mode, p["base"], p["pad"], pad_score, lanes)
                 assert 0 <= lo and hi <= TOP, (m, gap, lanes, lo, hi)
+
+
+def test_pair_rows_fit_what_is_launched():
+    for n_pass in (1, 2, 3, 8, 40):
+        for W in (1, 8, 16):
+            for grid in (1, 15, 256):
+                for items in (grid, 4000):
+                    for stride in (5000, 35_000, 1 << 24):
+                        for have in (-1, 1, 7, 3000):
+                            r = plans.rows(n_pass, W, grid, items, stride, have)
+                            assert r["ring"] >= 1 and 1 <= r["grid"] <= grid
+                            if n_pass == 1:
+                                assert r["rows"] == 0 and r["grid"] == grid
+                                continue
+                            assert r["rows"] == r["ring"] * r["grid"]
+                            if have > 0:
+                                assert r["rows"] <= have
+                                continue
+                            assert r["grid"] == grid
+                            assert r["rows"] <= max(min(items, 1024), (512 << 20) // (8 * stride))
+    # the usual case holds every pair that the waves can be at
+    assert plans.rows(2, 16, 15, 1000, 35_000) == {"ring": 9, "grid": 15, "rows": 135}
