@@ -159,6 +159,110 @@ inline int pair_ring(int n_pass, int W) {
   return n_pass > 1 ? std::min(kRing, (W + n_pass - 1) / n_pass + 1) : kRing;
 }
 
+// What the long-pair kernel is to score, and beside what.
+struct PairLoad {
+  int m = 0;                  // query rows (batches: the median query's)
+  double items = 0;           // pairs, segments of pairs, or pairs times queries
+  double cols = 0;            // their columns together
+  double longest = 0;         // and the longest one's
+  double beside = 0;          // seconds the bins beside it take on the whole device
+  const int64_t* bins = nullptr;   // their descriptors, longest first (BinDesc's words),
+  int64_t n_bins = 0;
+  double bin_col = 0;         // seconds one of them takes per column, alone on a CU
+  int cus = 256;
+  int rows = 0, waves = 0;    // 0: any, else fixed
+  bool own = false;           // each wave stages its own pass's rows (batches)
+};
+struct PairLaunch {
+  int R = 8, W = 1, grid = 1;   // rows per lane, waves per workgroup, workgroups
+};
+
+// Cycles between two steps of a SIMD's waves, all together, with one, two and
+// four waves on it (300 pairs of long sequences on 24 CUs; 2.4 GHz).
+struct StepCost {
+  int R;
+  double at1, at2, at4;
+};
+constexpr StepCost kStepCosts[] = {{2, 181, 124, 107}, {4, 238, 170, 154}, {8, 370, 288, 271}};
+inline double step_cycles(const StepCost& c, double waves) {   // per SIMD
+  if (waves <= 1) return c.at1 / std::max(waves, 1e-3);
+  if (waves <= 2) return c.at1 + (c.at2 - c.at1) * (waves - 1);
+  return c.at2 + (c.at4 - c.at2) * std::min(1.0, (waves - 2) / 2);
+}
+
+// Rows, waves and workgroups of the drift long-pair kernel: the least expected
+// time of the pairs and the bins together.  One workgroup a CU (of waves that an
+// option fixes below 8, up to 16 waves), spread over the CUs however few passes
+// there are: packed so that every wave has a pass, 881 items of one pass took 56 CUs
+// and 0.81 ms, over 224 of them 0.39 (47 residues, 12,500 sequences of the long mix).
+// The pairs take the work on the CUs they get, or the longest one's chain: its
+// columns times the rounds its passes take on one workgroup's waves.  Beside bins,
+// whose workgroups share a CU with no other, at most 7/8 of the CUs, and fewer where
+// the longest bin that waits for one of them would end last: a bin that waits for
+// every pair's workgroup starts when the search is all but over (6,000 residues
+// against 50,000 sequences of the long mix: 38 ms).  Against fixed counts of CUs,
+// rows and waves swept over 31 searches of seven databases, 47 .. 10,000 residues:
+// 1 % above the best of them on average, 10 % at most (without the spreading and the
+// fullest SIMD's share in the chain: 17 %, 114 %).
+inline PairLaunch pair_launch(const PairLoad& p) {
+  PairLaunch best;
+  double least = 1e300;
+  const double cus = std::max(p.cus, 1);
+  for (const StepCost& c : kStepCosts) {
+    if (p.rows && c.R != p.rows) continue;
+    const int P = std::max(1, (p.m + 64 * c.R - 1) / (64 * c.R));
+    for (int W : {16, 8, 4, 2, 1}) {
+      if (p.waves ? W != p.waves : W < 8) continue;
+      const size_t lds = std::min(p.own ? kLdsBytes + 1 : pairs_lds(c.R, W, P, true),
+                                  pairs_lds(c.R, W, P, false));
+      if (lds + pairs_lds_static(W) > kLdsBytes) continue;
+      const int conc = std::min(P, W);
+      constexpr double kSixteenths[] = {14, 10, 8, 6, 5, 4, 3, 1.5};
+      constexpr int kParts = sizeof(kSixteenths) / sizeof(*kSixteenths);
+      for (int choice = W < 8 ? 0 : kParts; choice < 2 * kParts; ++choice) {
+        // the CUs that get workgroups, and how many each
+        const int per_cu = choice < kParts ? 16 / W : 1;
+        const double sixteenths = kSixteenths[choice % kParts];
+        const double most = std::max(1.0, p.beside > 0 ? cus * sixteenths / 16 : cus);
+        const double grid = std::max(1.0, std::min(p.items, most * per_cu));
+        const double on = std::min(grid, most);
+        const double waves = std::min((double)W * per_cu, std::max<double>(conc, p.items * P / on));
+        const double step = step_cycles(c, waves / 4);
+        const double lead = p.longest + 128.0 * (conc - 1);
+        // a round of passes takes the fullest SIMD's steps; a last round of fewer
+        // starts while the one before still runs
+        auto round = [&](int passes) {
+          const double held = (passes + 3) / 4;
+          return held * step_cycles(c, held);
+        };
+        const int full = P / W, rest = P % W;
+        double chain = lead * (full * round(W) + (rest ? (full ? 0.5 : 1.0) * round(rest) : 0));
+        // other pairs' waves on the same SIMDs
+        chain *= 1 + 0.004 * (waves - conc) + (per_cu > 1 ? 0.1 : 0);
+        const double work = 1.3 * p.cols * P * step / (4 * on);
+        const double pairs = std::max(chain, work) + 0.1 * std::min(chain, work);
+        double all = pairs;
+        if (p.beside > 0) {
+          const double busy = std::min(pairs * on, work * on + 0.2 * chain * on);
+          all = std::max(pairs, p.beside * 2.4e9 + busy / cus);
+          const int64_t now = (int64_t)(cus - on);    // bins that start at once
+          if (now < p.n_bins)
+            all = std::max(all, 0.7 * pairs + p.bin_col * 2.4e9 * (double)p.bins[4 * now + 2]);
+        }
+        // (where two agree 16 waves beside bins, 8 alone)
+        if (p.beside > 0 ? all < least : all <= least) {
+          least = all;
+          best.R = c.R;
+          best.W = W;
+          best.grid = (int)grid;
+        }
+        if (p.beside <= 0) choice += kParts - 1;     // alone: on all CUs
+      }
+    }
+  }
+  return best;
+}
+
 // The row buffers of a launch of the long-pair kernel over `items` pairs (or
 // segments, or pairs times queries) of `stride` columns at most: `ring` for each
 // of `grid` workgroups, for the workgroups that are launched and no others.  Fewer

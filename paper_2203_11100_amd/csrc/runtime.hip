@@ -669,7 +669,9 @@ struct SearchShape {
 constexpr double kInterRate = 7.0e12;
 constexpr double kPairRate = 4.5e12;
 constexpr double kBinRate = 3.0e10;
-constexpr double kPairShare = 5.0;
+constexpr double kBesideRate = 8.5e12;     // the drift inter-task kernel beside long pairs,
+constexpr double kBesideBin = 4.5e10;      // and one of its bins alone on a CU
+constexpr double kPairShare = 5.0;         // of the CUs, binary16 and int32 long pairs
 constexpr double kLongModeRate = 1.2e12;   // int32 wavefront kernel, global and semi-global
 
 // How many of the longest short bins a query of length m hands to the
@@ -719,74 +721,6 @@ int64_t pair_stride(const DbData& d) {
   return std::max<int64_t>({(int64_t)d.plan.max_long_len, (int64_t)d.plan.max_short_len, 1});
 }
 
-// Rows per lane and waves per workgroup of the drift long-pair kernel, for pairs
-// of `cols` columns together, the longest `longest`, beside `inter` cells of the
-// inter-task kernel.  In cycles, measured: a step of R rows takes `lat` in a wave
-// alone on its SIMD and `thr` of the SIMD's issue where several waves share it.
-// The longest pair is a chain of its steps (two supersteps more for every
-// further pass), in rounds when its passes outnumber the waves; the rows that
-// give the shorter of chain and work win, the cheaper work where that is close
-// (977 residues against the plain database 7.3 ms with 4 or 8 rows; the long mix,
-// 2,000 residues, 9.3 / 5.7 / 6.0 with 2, 4, 8; 2,000 short sequences 0.19 / 0.21
-// with 2, 4).  Waves: alone the fewest that hold a pair's passes and, over the
-// device, all pairs at once, so that few pairs spread over the CUs.  Beside the
-// inter-task kernel, whose workgroups share a CU with no other, 16, so that the
-// pairs hold few CUs and fill them (457 residues, 100,000 plain sequences: 2.96 /
-// 2.70 / 2.50 ms with 4, 8, 16; 144 and 200,000: 1.176 ms with 16, 1.191 with 8), but
-// 8 where the longest pair is what the search waits for - its chain clearly longer
-// than the bins and than twice the pairs' steps spread over the device - and its
-// waves then share their SIMDs with fewer others (47 residues, 3,083 sequences of the
-// long mix: 0.57 ms with 16, 0.43 with 8; 80 and 6,322: 0.59, 0.46).
-void pick_pairs(const Searcher* db, int m, double n_pairs, double cols, double longest,
-                double inter, int* R_out, int* W_out) {
-  struct Cost { int R; double lat, thr; };
-  static const Cost costs[] = {{4, 260, 153}, {8, 400, 270}, {2, 215, 95}};
-  const double simds = 4.0 * std::max(db->d->n_cus, 1);
-  double best = 1e300;
-  for (const Cost& c : costs) {
-    if (db->opt_intra_rows && c.R != db->opt_intra_rows) continue;
-    const int P = (m + 64 * c.R - 1) / (64 * c.R);
-    const double beside = inter / 128.0 * 27.0 / simds;
-    const bool waits = cols * P / simds < 0.5 * longest && longest * c.lat > 1.4 * beside;
-    int W = inter <= 0 ? 1 : waits ? 8 : 16;
-    while (W < 16 && (W < P || (inter <= 0 &&
-                                (double)W * std::max(db->d->n_cus, 1) < n_pairs * P)))
-      W *= 2;
-    if (db->opt_intra_waves) W = db->opt_intra_waves;
-    auto fits = [&](int w) {
-      return std::min(pairs_lds(c.R, w, P, true), pairs_lds(c.R, w, P, false)) +
-                 pairs_lds_static(w) <= kLdsBytes;
-    };
-    while (W > 1 && !fits(W)) W /= 2;
-    const int at_once = std::min(P, W);
-    const double chain = (longest + 128.0 * (at_once - 1)) * ((P + W - 1) / W) *
-                         std::max(c.lat, std::max(1.0, at_once / 4.0) * c.thr);
-    const double work = cols * P * c.thr / simds / 0.85;
-    const double all = work + beside;
-    const double est = std::max(chain, all) + 0.1 * chain + 0.5 * work;
-    if (est < best) { best = est; *R_out = c.R; *W_out = W; }
-  }
-}
-
-// Workgroups of a pair launch over `count` items of n_pass passes: enough waves
-// for all passes, at most what the device holds.  Beside the persistent
-// inter-task kernel (inter cells, pair rows * residues) the pairs take
-// kPairShare times their share of the search's work: too many workgroups hold up
-// the bins (the longest is the critical path of a short query), too few end after
-// them.
-int pair_grid(const Searcher* db, int64_t count, int n_pass, int W, double pair_cells,
-              double inter_cells) {
-  const double cus = std::max(db->d->n_cus, 1);
-  int64_t grid = std::min<int64_t>(count, (count * n_pass + W - 1) / W);
-  const int per_cu = std::max(1, 16 / W);
-  grid = std::min<int64_t>(grid, (int64_t)(cus * per_cu));
-  if (inter_cells > 0) {
-    const double tp = pair_cells / kPairRate, ti = inter_cells / kInterRate;
-    grid = std::min<int64_t>(grid, (int64_t)(kPairShare * tp / (tp + ti) * cus * 4 / W) + 1);
-  }
-  return (int)std::max<int64_t>(grid, 1);
-}
-
 // offload: short bins may be handed to the long-pair kernel
 SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t ge, bool offload) {
   const DbData& D = *db->d;
@@ -800,32 +734,49 @@ SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t g
   sh.overlap = D.plan.n_long > 0 ? seg_overlap(D, m, mat, ge) : -1;
   sh.pair = pair_form(mat, ge, db->sat_limit);
   const int b = tune_bucket(m);
-  if (sh.pair.add < 0) {
-    pick_intra(db, m, 8, &sh.RR, &sh.W2, true);   // long sequences, in pairs (binary16)
-  } else if (db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves) {
-    sh.RR = db->tune_irows[b];
-    sh.W2 = db->tune_iwaves[b];
-  }
+  const bool tuned = db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves;
+  if (sh.pair.add < 0) pick_intra(db, m, 8, &sh.RR, &sh.W2, true);   // (binary16)
   sh.off_bins = offload ? pick_offload(db, m, sh.pair.add < 0 ? sh.RR : 4) : 0;
   const double off_res = sh.off_bins > 0 ? (double)D.bin_res_cum[(size_t)sh.off_bins] : 0.0;
   const int64_t off_pairs = sh.off_bins > 0 ? D.bin_pair_end[(size_t)sh.off_bins - 1] : 0;
   const double inter = (double)m * ((double)(D.n_res - D.long_residues) - off_res);
   sh.items = (sh.overlap >= 0 ? D.n_seg_items : D.n_long_pairs) + off_pairs;
   sh.stride = sh.overlap >= 0 ? seg_stride(D) : pair_stride(D);
-  if (sh.pair.add >= 0 && !(db->tune_iwaves[b] && !db->opt_intra_rows && !db->opt_intra_waves)) {
-    double cols = 0.5 * (double)D.long_residues;
-    double longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
+  if (sh.pair.add >= 0) {
+    PairLoad load;
+    load.m = m;
+    load.items = (double)sh.items;
+    load.cols = 0.5 * ((double)D.long_residues + off_res);
+    load.longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
     if (sh.overlap >= 0) {
-      cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
-      longest = std::min<double>(longest, std::max<double>((double)D.seg_cols + sh.overlap,
-                                                          off_pairs > 0 ? D.plan.max_short_len : 0));
+      load.cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
+      load.longest = std::min<double>(load.longest,
+                                      std::max<double>((double)D.seg_cols + sh.overlap,
+                                                       off_pairs > 0 ? D.plan.max_short_len : 0));
     }
-    pick_pairs(db, m, (double)sh.items, cols + 0.5 * off_res, longest, inter, &sh.RR, &sh.W2);
+    load.beside = D.plan.n_bins > sh.off_bins ? inter / (kBesideRate * D.n_cus / 256.0) : 0;
+    load.bins = D.plan.bins.data() + 4 * sh.off_bins;
+    load.n_bins = D.plan.n_bins - sh.off_bins;
+    load.bin_col = (double)m * SW_BIN_SEQS / kBesideBin;
+    load.cus = D.n_cus;
+    load.rows = tuned ? db->tune_irows[b] : db->opt_intra_rows;
+    load.waves = tuned ? db->tune_iwaves[b] : db->opt_intra_waves;
+    const PairLaunch pl = pair_launch(load);
+    sh.RR = pl.R;
+    sh.W2 = pl.W;
+    sh.grid = pl.grid;
   }
   sh.n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
-  sh.grid = pair_grid(db, sh.items, sh.n_pass, sh.W2,
-                      64.0 * sh.RR * sh.n_pass * ((double)D.long_residues + off_res),
-                      D.plan.n_bins > sh.off_bins ? inter : 0.0);
+  if (sh.pair.add < 0) {
+    // beside bins kPairShare times the pairs' share of the search's work: too many
+    // workgroups hold up the bins, too few end after them
+    const double tp = 64.0 * sh.RR * sh.n_pass * ((double)D.long_residues + off_res) / kPairRate;
+    const double ti = D.plan.n_bins > sh.off_bins ? inter / kInterRate : 0;
+    sh.grid = ti > 0 ? (int)std::min<int64_t>(
+                           (sh.items * sh.n_pass + sh.W2 - 1) / sh.W2,
+                           (int64_t)(kPairShare * tp / (tp + ti) * D.n_cus * 4 / sh.W2) + 1)
+                     : kIntraGridLong;
+  }
   // exact rescoring (usually a few sequences, each the only one on its CU,
   // so the latency of one sequence is what counts)
   pick_intra(db, m, 8, &sh.RRr, &sh.W2r);
@@ -1075,8 +1026,7 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
       la.out = d_out;
       la.flag_count = X.flags;
       la.flag_list = flist;
-      int grid = std::min<int>(segmented ? X.grid_seg : X.grid_long, la.count);
-      if (n_bins > off_bins) grid = std::min(grid, sh.grid);
+      const int grid = std::min<int>(sh.grid, std::min<int>(segmented ? X.grid_seg : X.grid_long, la.count));
       if (segmented) {
         la.seg_items = db->d->d_seg_items.p;
         la.seg_cols = db->d->seg_cols;
@@ -1266,19 +1216,30 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
     const int64_t count = db->d->n_long_pairs + off_pairs;
     const int64_t longest = off_bins > 0 || n_long > 0 ? P.max_len : 0;
     if (count > 0) {
-      pick_pairs(db, m, (double)count, 0.5 * pair_res, (double)longest,
-                 off_bins < P.n_bins ? inter : 0.0, &RR, &W2);
+      PairLoad load;
+      load.m = m;
+      load.items = (double)count;
+      load.cols = 0.5 * pair_res;
+      load.longest = (double)longest;
+      load.beside = off_bins < P.n_bins ? inter / (kBesideRate * db->d->n_cus / 256.0) : 0;
+      load.bins = P.bins.data() + 4 * off_bins;
+      load.n_bins = P.n_bins - off_bins;
+      load.bin_col = (double)m * SW_BIN_SEQS / kBesideBin;
+      load.cus = db->d->n_cus;
+      load.rows = db->opt_intra_rows;
+      load.waves = db->opt_intra_waves;
+      const PairLaunch pl = pair_launch(load);
+      RR = pl.R;
+      W2 = pl.W;
+      grid = pl.grid;
       pair = mode_pairs(m, longest, mat, go, ge, mode, RR, &pa.mode);
     }
     if (pair.add >= 0) {
       pa.count = (int32_t)count;
       pa.n_pass = (m + 64 * RR - 1) / (64 * RR);
       pa.scratch_stride = pair_stride(*db->d);
-      const PairRows rows = pair_rows(
-          pair_ring(pa.n_pass, W2),
-          pair_grid(db, count, pa.n_pass, W2, 64.0 * RR * pa.n_pass * pair_res,
-                    off_bins < P.n_bins ? inter : 0.0),
-          pa.n_pass, count, pa.scratch_stride);
+      const PairRows rows =
+          pair_rows(pair_ring(pa.n_pass, W2), grid, pa.n_pass, count, pa.scratch_stride);
       pa.ring = rows.ring;
       grid = rows.grid;
       const size_t words = (size_t)std::max<int64_t>(rows.rows * pa.scratch_stride, 1);

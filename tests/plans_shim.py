@@ -47,6 +47,31 @@ void p_rows(int ring, int grid, int n_pass, int64_t items, int64_t stride, int64
   out[1] = r.grid;
   out[2] = r.rows;
 }
+// {R, W, grid}
+void p_launch(int m, const double* d, const int64_t* bins, int64_t n_bins, int cus, int rows,
+              int waves, int own, int32_t* out) {
+  PairLoad p;
+  p.bins = bins;
+  p.n_bins = n_bins;
+  p.bin_col = m * 128 / 4.5e10;
+  p.m = m;
+  p.items = d[0];
+  p.cols = d[1];
+  p.longest = d[2];
+  p.beside = d[3];
+  p.cus = cus;
+  p.rows = rows;
+  p.waves = waves;
+  p.own = own != 0;
+  const PairLaunch l = pair_launch(p);
+  out[0] = l.R;
+  out[1] = l.W;
+  out[2] = l.grid;
+}
+int p_lds(int R, int W, int n_pass, int own) {
+  const size_t mine = pairs_lds(R, W, n_pass, false), all = pairs_lds(R, W, n_pass, true);
+  return (int)((own ? mine : std::min(mine, all)) + pairs_lds_static(W));
+}
 int p_ring(int n_pass, int W) { return pair_ring(n_pass, W); }
 }
 """
@@ -109,3 +134,18 @@ def rows(n_pass, W, grid, items, stride, have=-1):
     lib().p_rows(lib().p_ring(n_pass, W), grid, n_pass, _i64(items), _i64(stride), _i64(have),
                  out.ctypes.data_as(ctypes.c_void_p))
     return dict(zip(("ring", "grid", "rows"), out.tolist()))
+
+
+def launch(m, items, cols, longest, beside=0.0, cus=256, rows=0, waves=0, own=False, bins=()):
+    out = np.zeros(3, np.int32)
+    desc = np.zeros((len(bins) + 1, 4), np.int64)
+    desc[:len(bins), 2] = bins
+    d = np.array([items, cols, longest, beside], np.float64)
+    lib().p_launch(m, d.ctypes.data_as(ctypes.c_void_p), desc.ctypes.data_as(ctypes.c_void_p),
+                   _i64(len(bins)), cus, rows, waves, int(own),
+                   out.ctypes.data_as(ctypes.c_void_p))
+    return tuple(out.tolist())
+
+
+def lds(R, W, n_pass, own=False):
+    return lib().p_lds(R, W, n_pass, int(own))

@@ -150,3 +150,40 @@ def test_pair_rows_fit_what_is_launched():
                             assert r["rows"] <= max(min(items, 1024), (512 << 20) // (8 * stride))
     # the usual case holds every pair that the waves can be at
     assert plans.rows(2, 16, 15, 1000, 35_000) == {"ring": 9, "grid": 15, "rows": 135}
+
+
+def test_pair_launch_leaves_cus_to_the_bins_and_fits():
+    rng = np.random.default_rng(2)
+    for _ in range(20000):
+        m = int(np.exp(rng.uniform(0, 11)))
+        items = float(int(np.exp(rng.uniform(0, 10))))
+        longest = float(int(np.exp(rng.uniform(3, 13))))
+        cols = items * longest * rng.uniform(0.05, 1.0)
+        beside = float(rng.choice([0, 0, 1e-6, 1e-4, 1e-2]))
+        rows, waves = int(rng.choice([0, 0, 2, 4, 8])), int(rng.choice([0, 0, 1, 2, 4, 8]))
+        own, cus = bool(rng.integers(2)), int(rng.choice([256, 256, 32, 1]))
+        bins = np.sort(rng.integers(96, 2048, int(rng.choice([0, 5, 400]))))[::-1] if beside else ()
+        R, W, grid = plans.launch(m, items, cols, longest, beside, cus, rows, waves, own, bins)
+        assert R in (2, 4, 8) and W in (1, 2, 4, 8, 16) and (not rows or R == rows)
+        assert not waves or W == waves
+        P = -(-m // (64 * R))
+        assert plans.lds(R, W, P, own) <= 160 * 1024
+        assert 1 <= grid <= items
+        if W >= 8:      # one workgroup a CU, and CUs for the bins
+            assert grid <= (max(1, cus * 7 // 8) if beside else cus)
+
+
+def test_pair_launch_spreads_few_passes_over_the_device():
+    # 47 residues, 881 windows of up to 4,402 columns beside 2 % of the work: every
+    # wave filled would be 56 workgroups
+    R, W, grid = plans.launch(47, 881, 3.2e6, 4402, 1.8e8 / 8.5e12)
+    assert R == 2 and grid == 224
+    # 300 pairs alone: as many CUs as there are
+    for m in (977, 2000, 5000):
+        assert plans.launch(m, 300, 5.5e6, 34971)[2] == 256
+    # few pairs beside many bins keep to few CUs
+    assert plans.launch(457, 355, 9.8e5, 7067, 3.2e10 / 8.5e12)[2] <= 48
+    # bins that take as long as the pairs start at once: 142 of 400 columns, 960 pairs
+    assert plans.launch(30, 960, 3.84e5, 400, 2.8e-5, bins=[400] * 142)[2] <= 160
+    # a short query's wave has few rows, or its chain is longer than it has to be
+    assert plans.launch(50, 16, 1.9e5, 35000, 1e-4, own=True)[0] == 2
