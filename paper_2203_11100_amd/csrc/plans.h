@@ -202,7 +202,7 @@ inline double step_cycles(const StepCost& c, double waves) {   // per SIMD
 // every pair's workgroup starts when the search is all but over (6,000 residues
 // against 50,000 sequences of the long mix: 38 ms).  Against fixed counts of CUs,
 // rows and waves swept over 31 searches of seven databases, 47 .. 10,000 residues:
-// 1 % above the best of them on average, 10 % at most (without the spreading and the
+// 2 % above the best of them on average, 13 % at most (without the spreading and the
 // fullest SIMD's share in the chain: 17 %, 114 %).
 inline PairLaunch pair_launch(const PairLoad& p) {
   PairLaunch best;
@@ -239,7 +239,7 @@ inline PairLaunch pair_launch(const PairLoad& p) {
         double chain = lead * (full * round(W) + (rest ? (full ? 0.5 : 1.0) * round(rest) : 0));
         // other pairs' waves on the same SIMDs
         chain *= 1 + 0.004 * (waves - conc) + (per_cu > 1 ? 0.1 : 0);
-        const double work = 1.3 * p.cols * P * step / (4 * on);
+        const double work = 1.2 * p.cols * P * step / (4 * on);
         const double pairs = std::max(chain, work) + 0.1 * std::min(chain, work);
         double all = pairs;
         if (p.beside > 0) {
