@@ -161,7 +161,7 @@ inline int pair_ring(int n_pass, int W) {
 
 // What the long-pair kernel is to score, and beside what.
 struct PairLoad {
-  int m = 0;                  // query rows (batches: the median query's)
+  int m = 0;                  // query rows (batches: the longest query's)
   double items = 0;           // pairs, segments of pairs, or pairs times queries
   double cols = 0;            // their columns together
   double longest = 0;         // and the longest one's

@@ -670,7 +670,8 @@ constexpr double kInterRate = 7.0e12;
 constexpr double kPairRate = 4.5e12;
 constexpr double kBinRate = 3.0e10;
 constexpr double kBesideRate = 8.5e12;     // the drift inter-task kernel beside long pairs,
-constexpr double kBesideBin = 4.5e10;      // and one of its bins alone on a CU
+constexpr double kBesideBin = 4.5e10;      // one of its bins alone on a CU, and the
+constexpr double kBesideCol = 2.5e-7;      // least seconds such a bin takes a column
 constexpr double kPairShare = 5.0;         // of the CUs, binary16 and int32 long pairs
 constexpr double kLongModeRate = 1.2e12;   // int32 wavefront kernel, global and semi-global
 
@@ -757,7 +758,7 @@ SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t g
     load.beside = D.plan.n_bins > sh.off_bins ? inter / (kBesideRate * D.n_cus / 256.0) : 0;
     load.bins = D.plan.bins.data() + 4 * sh.off_bins;
     load.n_bins = D.plan.n_bins - sh.off_bins;
-    load.bin_col = (double)m * SW_BIN_SEQS / kBesideBin;
+    load.bin_col = std::max((double)m * SW_BIN_SEQS / kBesideBin, kBesideCol);
     load.cus = D.n_cus;
     load.rows = tuned ? db->tune_irows[b] : db->opt_intra_rows;
     load.waves = tuned ? db->tune_iwaves[b] : db->opt_intra_waves;
@@ -1224,7 +1225,7 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
       load.beside = off_bins < P.n_bins ? inter / (kBesideRate * db->d->n_cus / 256.0) : 0;
       load.bins = P.bins.data() + 4 * off_bins;
       load.n_bins = P.n_bins - off_bins;
-      load.bin_col = (double)m * SW_BIN_SEQS / kBesideBin;
+      load.bin_col = std::max((double)m * SW_BIN_SEQS / kBesideBin, kBesideCol);
       load.cus = db->d->n_cus;
       load.rows = db->opt_intra_rows;
       load.waves = db->opt_intra_waves;

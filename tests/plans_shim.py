@@ -53,7 +53,7 @@ void p_launch(int m, const double* d, const int64_t* bins, int64_t n_bins, int c
   PairLoad p;
   p.bins = bins;
   p.n_bins = n_bins;
-  p.bin_col = m * 128 / 4.5e10;
+  p.bin_col = std::max(m * 128 / 4.5e10, 2.5e-7);
   p.m = m;
   p.items = d[0];
   p.cols = d[1];

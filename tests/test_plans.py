@@ -184,6 +184,6 @@ def test_pair_launch_spreads_few_passes_over_the_device():
     # few pairs beside many bins keep to few CUs
     assert plans.launch(457, 355, 9.8e5, 7067, 3.2e10 / 8.5e12)[2] <= 48
     # bins that take as long as the pairs start at once: 142 of 400 columns, 960 pairs
-    assert plans.launch(30, 960, 3.84e5, 400, 2.8e-5, bins=[400] * 142)[2] <= 256 - 142
+    assert plans.launch(30, 960, 3.84e5, 400, 2.57e-5, bins=[400] * 142)[2] <= 256 - 142
     # a short query's wave has few rows, or its chain is longer than it has to be
     assert plans.launch(50, 16, 1.9e5, 35000, 1e-4, own=True)[0] == 2
