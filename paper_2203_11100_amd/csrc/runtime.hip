@@ -1382,8 +1382,10 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
 }
 
 // Pairs of very long sequences in flight per workgroup of a batch's long-pair
-// kernel, each with a row buffer of the longest sequence.
+// kernel, at least (queries differ in their passes), each with a row buffer of the
+// longest sequence; and the cells per second of the batched kernel beside it.
 constexpr int kBatchRing = 4;
+constexpr double kBatchRate = 1.2e13;
 
 // Builds (or keeps) the batch plan for these queries, matrix, gaps and
 // buffers: pairs of length-sorted queries, pair and per-query descriptors,
@@ -1465,15 +1467,35 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
   // kernel's (long sequences of the i32 form, rescoring) and the packed
   // long-pair kernel's
   const int64_t m_med = n_nz ? ms[order[n_nz / 2]] : 1;
-  int RR = 8, W2 = 1, RRp = 8, W2p = 1;
+  int RR = 8, W2 = 1, RRp = 8, W2p = 1, grid_long = kIntraGridLong, ring_long = 1;
   pick_intra(db, (int)m_med, 8, &RR, &W2);
   const PairForm form = pair_form(mat, ge, db->sat_limit);
   if (form.add < 0) {
     pick_intra(db, (int)m_med, 8, &RRp, &W2p, true);
   } else {
-    // each wave stages its pass's rows, as the queries differ
-    RRp = db->opt_intra_rows ? db->opt_intra_rows : m_med > 256 ? 8 : 4;
-    W2p = db->opt_intra_waves ? db->opt_intra_waves : 8;
+    // as for single searches, every pair with every query; each wave stages its
+    // pass's rows, as the queries differ (four rows for every short query: two
+    // queries of 50 residues against 20,001 plain sequences 3.4 ms, the
+    // 35,000-residue one's chain, 2.7 with two)
+    PairLoad load;
+    double rows = 0;
+    for (int32_t q : order) rows += (double)ms[q];
+    load.m = n_nz ? (int)ms[order[0]] : 1;      // the longest pair's chain
+    load.items = (double)((db->d->plan.n_vlong + 1) / 2) * n_nz;
+    load.cols = 0.5 * (double)db->d->vlong_residues * rows / load.m;
+    load.longest = db->d->plan.max_long_len;
+    load.beside = rows * (double)(db->d->n_res - db->d->vlong_residues) /
+                  (kBatchRate * db->d->n_cus / 256.0);
+    load.cus = db->d->n_cus;
+    load.rows = db->opt_intra_rows;
+    load.waves = db->opt_intra_waves;
+    load.own = true;
+    const PairLaunch pl = pair_launch(load);
+    RRp = pl.R;
+    W2p = pl.W;
+    grid_long = pl.grid;
+    const int P = (int)((m_med + 64 * RRp - 1) / (64 * RRp));   // the usual query's passes
+    ring_long = std::max(kBatchRing, pair_ring(std::max(P, 2), W2p));
   }
   const int W2r = W2;
   const bool has_vlong = db->d->plan.n_vlong > 0;
@@ -1564,10 +1586,9 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
   B.grid_b = db->d->n_cus * batch_workgroups_per_cu(R, W);
   B.pair = form;
   B.pair_bias = form.bias;
-  B.grid_long = (int)std::min<int64_t>(
-      B.n_long_items, form.add >= 0 ? (int64_t)db->d->n_cus * std::max(1, 16 / W2p) : kIntraGridLong);
-  const PairRows long_rows = pair_rows(form.add >= 0 ? kBatchRing : 1, B.grid_long, 2, B.n_long_items,
-                                       db->d->plan.max_long_len);
+  B.grid_long = (int)std::min<int64_t>(B.n_long_items, grid_long);
+  const PairRows long_rows =
+      pair_rows(ring_long, B.grid_long, 2, B.n_long_items, db->d->plan.max_long_len);
   B.grid_long = long_rows.grid;
   B.ring_long = long_rows.ring;
   if ((e = db->rb_batch.reserve((size_t)B.grid_b * (size_t)(db->d->plan.max_all_bin_len / 4) * 128)) !=

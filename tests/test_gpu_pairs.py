@@ -167,3 +167,49 @@ def test_row_buffers_stay_small(sw):
             assert used <= most, (what, used)
             if what == "search":
                 _same(got, ocpu.search(q, res, offs, B62, 10, 2), what)
+
+
+# the chosen rows and waves against forced ones: short queries and the long list's
+# few passes (searches, batches), pairs alone.  Medians of a dozen calls; the rule's
+# own spread over swept searches is 13 %
+@pytest.mark.parametrize("what", ["search-47", "batch-2x50", "alone-977"])
+def test_chosen_launch_is_no_slower_than_forced_ones(sw, what):
+    import torch
+    rng = np.random.default_rng(11)
+    if what == "alone-977":
+        lens = rng.integers(2048, 35001, 600)
+    else:
+        lens = np.concatenate([swinputs.lognormal_lengths(6000, 350.0, 0.75, 20, 9999, rng),
+                               rng.integers(10000, 35001, 120)])
+    res, offs = swinputs.make_database(np.asarray(lens, dtype=np.int64), rng)
+    m = int(what.rsplit("-", 1)[1].split("x")[-1])
+    nq = 2 if what.startswith("batch") else 1
+    q = torch.from_numpy(swinputs.random_residues(nq * m, rng)).cuda()
+    qo = np.arange(nq + 1, dtype=np.int64) * m
+    out = torch.empty((nq, len(lens)), dtype=torch.int32, device="cuda")
+
+    def run():
+        if nq > 1:
+            db.search_batch_async(q, qo, B62, 10, 2, out)
+        else:
+            db.search_async(q, B62, 10, 2, out[0])
+
+    def median():
+        ms = []
+        for _ in range(14):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            run()
+            b.record()
+            b.synchronize()
+            ms.append(a.elapsed_time(b))
+        return float(np.median(ms[2:]))
+
+    times = {}
+    for rows, waves in ((0, 0), (2, 4), (2, 8), (4, 4), (4, 8), (8, 4), (8, 8)):
+        with sw.Database(res, offs) as db:
+            db.set_option(sw.SW_OPT_INTRA_ROWS, rows)
+            db.set_option(sw.SW_OPT_INTRA_WAVES, waves)
+            times[rows, waves] = median()
+    say(what, times)
+    assert times[0, 0] <= 1.2 * min(times.values()), times
