@@ -263,6 +263,41 @@ inline PairLaunch pair_launch(const PairLoad& p) {
   return best;
 }
 
+// The binary16 long-pair kernel (k_intra_f16): a workgroup's W waves take one
+// pair's passes in rounds, three supersteps a wave apart with their barriers.  The
+// expected time of a search's pairs, in units of an instruction: the longest one's
+// chain, or the work on 256 CUs, which idle waves in a last round, the start and
+// end of a pair, and few waves on a CU (the profiles in LDS) lengthen.
+inline double half_estimate(int m, double items, double cols, double longest, int R, int W) {
+  const int P = std::max(1, (m + 64 * R - 1) / (64 * R)), rounds = (P + W - 1) / W;
+  const double step = 8.0 * R + 32;
+  const double steps = std::max(1.0, cols / std::max(items, 1.0) / 64);   // supersteps a pair
+  const int per_cu = std::max(1, std::min<int>(16 / W, (int)(kLdsBytes / (W * 3200 * R + 2000))));
+  const double few = 1 + 0.05 * std::max(0, 12 - per_cu * W);
+  const double work = cols * rounds * W * step / 1024 * (steps + 3 * (W - 1)) / steps * few;
+  const double chain = longest * rounds * step * 1.6;
+  return std::max(chain, work) + 0.1 * std::min(chain, work);
+}
+// The rows and waves that end first by that estimate where they do so clearly,
+// else R and W as they are (the shortest chain of one pair).  Many short pairs ask
+// for few waves: gaps 200/130, 20,001 plain sequences, 977 residues 3.24 ms with 4 x
+// 4, 2.35 with 8 x 2; 25 searches of five databases never slower than before.
+inline void half_rows(int m, double items, double cols, double longest, int* R, int* W) {
+  double least = 0.8 * half_estimate(m, items, cols, longest, *R, *W);
+  int r = *R, w = *W;
+  for (int rows : {2, 4, 8})
+    for (int waves : {1, 2, 4}) {
+      const double est = half_estimate(m, items, cols, longest, rows, waves);
+      if (est < least) {
+        least = est;
+        r = rows;
+        w = waves;
+      }
+    }
+  *R = r;
+  *W = w;
+}
+
 // The row buffers of a launch of the long-pair kernel over `items` pairs (or
 // segments, or pairs times queries) of `stride` columns at most: `ring` for each
 // of `grid` workgroups, for the workgroups that are launched and no others.  Fewer

@@ -743,18 +743,18 @@ SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t g
   const double inter = (double)m * ((double)(D.n_res - D.long_residues) - off_res);
   sh.items = (sh.overlap >= 0 ? D.n_seg_items : D.n_long_pairs) + off_pairs;
   sh.stride = sh.overlap >= 0 ? seg_stride(D) : pair_stride(D);
+  PairLoad load;
+  load.m = m;
+  load.items = (double)sh.items;
+  load.cols = 0.5 * ((double)D.long_residues + off_res);
+  load.longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
+  if (sh.overlap >= 0) {
+    load.cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
+    load.longest = std::min<double>(load.longest,
+                                    std::max<double>((double)D.seg_cols + sh.overlap,
+                                                     off_pairs > 0 ? D.plan.max_short_len : 0));
+  }
   if (sh.pair.add >= 0) {
-    PairLoad load;
-    load.m = m;
-    load.items = (double)sh.items;
-    load.cols = 0.5 * ((double)D.long_residues + off_res);
-    load.longest = std::max<double>(D.plan.max_long_len, off_pairs > 0 ? D.plan.max_short_len : 0);
-    if (sh.overlap >= 0) {
-      load.cols += (double)(D.n_seg_items - D.n_long_pairs) * sh.overlap;
-      load.longest = std::min<double>(load.longest,
-                                      std::max<double>((double)D.seg_cols + sh.overlap,
-                                                       off_pairs > 0 ? D.plan.max_short_len : 0));
-    }
     load.beside = D.plan.n_bins > sh.off_bins ? inter / (kBesideRate * D.n_cus / 256.0) : 0;
     load.bins = D.plan.bins.data() + 4 * sh.off_bins;
     load.n_bins = D.plan.n_bins - sh.off_bins;
@@ -766,6 +766,8 @@ SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t g
     sh.RR = pl.R;
     sh.W2 = pl.W;
     sh.grid = pl.grid;
+  } else if (!tuned && !db->opt_intra_rows && !db->opt_intra_waves) {
+    half_rows(m, load.items, load.cols, load.longest, &sh.RR, &sh.W2);
   }
   sh.n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
   if (sh.pair.add < 0) {

@@ -187,3 +187,12 @@ def test_pair_launch_spreads_few_passes_over_the_device():
     assert plans.launch(30, 960, 3.84e5, 400, 2.57e-5, bins=[400] * 142)[2] <= 256 - 142
     # a short query's wave has few rows, or its chain is longer than it has to be
     assert plans.launch(50, 16, 1.9e5, 35000, 1e-4, own=True)[0] == 2
+
+
+def test_binary16_pairs_take_fewer_waves_for_many_short_pairs():
+    # 20,001 plain sequences, 5,484 pairs of 529 columns on average, windows of 5,156
+    assert plans.half_rows(977, 5484, 2.9e6, 5156, 4, 4) == (8, 2)
+    assert plans.half_rows(2500, 5548, 2.9e6, 6808, 4, 4) == (8, 2)
+    # long pairs, few of them: the shortest chain, as it was
+    assert plans.half_rows(2500, 1494, 8.8e6, 6808, 4, 4) == (4, 4)
+    assert plans.half_rows(977, 1, 35000, 35000, 4, 4) == (4, 4)
