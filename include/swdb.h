@@ -416,7 +416,9 @@ int sw_get_stats(sw_db* db, sw_stats* out);
  *  - the same schedules of the batched kernel on a pair of such queries;
  *  - every (rows per lane, waves) of the long-sequence kernel of single
  *    searches (SW_TUNE_INTRA_CANDIDATES, when the database has long
- *    sequences), keeping the shortest kernel time.
+ *    sequences), reporting the kernel's time and keeping the form with the
+ *    shortest search; searches use it only where that is clearly shorter than
+ *    with the launch fitted to each query.
  * Later searches on the handle (and contexts created afterwards) use the
  * tuned entries of their query's bucket unless SW_OPT_ROWS / SW_OPT_WAVES /
  * SW_OPT_INTRA_ROWS / SW_OPT_INTRA_WAVES are set.  sw_autotune uses the
@@ -431,9 +433,10 @@ int sw_get_stats(sw_db* db, sw_stats* out);
  *                none stay untuned (fitted schedules) - lengths that are all
  *                0 measure nothing and clear an earlier tuning;
  *   cache_path : NULL, or a text file of tuning results keyed by the GPU
- *                architecture name, its compute-unit count, a digest of the
- *                database's shape (sequence count, residues, long threshold,
- *                histogram of log2 lengths) and the representative lengths.
+ *                architecture name, its compute-unit count, the version of
+ *                the kernels, a digest of the database's shape (sequence
+ *                count, residues, long threshold, histogram of log2 lengths)
+ *                and the representative lengths.
  *                A matching entry is applied without measuring (report
  *                from_cache = 1); otherwise the measured result is appended.
  *                An unreadable or unwritable file returns SW_EINVAL. */

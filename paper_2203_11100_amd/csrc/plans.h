@@ -263,6 +263,10 @@ inline PairLaunch pair_launch(const PairLoad& p) {
   return best;
 }
 
+// Whether searches with a launch that measuring found (milliseconds of whole
+// searches) are to use it: clearly shorter than with the one fitted to each query.
+inline bool tuned_beats_fitted(double tuned, double fitted) { return tuned < 0.97 * fitted; }
+
 // The binary16 long-pair kernel (k_intra_f16): a workgroup's W waves take one
 // pair's passes in rounds, three supersteps a wave apart with their barriers.  The
 // expected time of a search's pairs, in units of an instruction: the longest one's

@@ -2961,8 +2961,12 @@ static const int kTuneW[SW_TUNE_CANDIDATES] = {0, 12, 12, 12, 12, 12, 16, 16};
 static const int kTuneIR[SW_TUNE_INTRA_CANDIDATES] = {2, 4, 8, 2, 4, 8, 2, 4, 8, 2, 4};
 static const int kTuneIW[SW_TUNE_INTRA_CANDIDATES] = {1, 1, 1, 2, 2, 2, 4, 4, 4, 8, 8};
 
-// Key of a tuning-cache entry: GPU architecture, compute units, a digest of
-// the database's shape and the representative query lengths.
+// Counts the changes of the kernels after which measured choices no longer hold: 2
+// for the drift cells and the rule that chooses the long pairs' launch.
+constexpr int kTuneKernels = 2;
+
+// Key of a tuning-cache entry: GPU architecture, compute units, the kernels, a
+// digest of the database's shape and the representative query lengths.
 static std::string tune_key(const swdb::Searcher* db, const int (&rep_len)[SW_TUNE_BUCKETS]) {
   const swdb::DbData& d = *db->d;
   char arch[256] = "unknown";
@@ -2990,18 +2994,21 @@ static std::string tune_key(const swdb::Searcher* db, const int (&rep_len)[SW_TU
   mix((uint64_t)d.plan.long_threshold);
   for (int64_t v : hist) mix((uint64_t)v);
   char buf[512];
-  snprintf(buf, sizeof(buf), "%s cus=%d db=%016llx lens=%d,%d,%d,%d", arch, d.n_cus,
-           (unsigned long long)h, rep_len[0], rep_len[1], rep_len[2], rep_len[3]);
+  snprintf(buf, sizeof(buf), "%s cus=%d kernels=%d db=%016llx lens=%d,%d,%d,%d", arch, d.n_cus,
+           kTuneKernels, (unsigned long long)h, rep_len[0], rep_len[1], rep_len[2], rep_len[3]);
   return buf;
 }
 
-// Sums the recorded kernel times of one kind and recycles the events.
-static float drain_timed(swdb::Searcher* db, int kind) {
+// Sums the recorded kernel times of one kind (and of another) and recycles the
+// events.
+static float drain_timed(swdb::Searcher* db, int kind, int kind2 = -1, float* total2 = nullptr) {
   float total = 0;
   for (auto& t : db->timed) {
     (void)hipEventSynchronize(t.b);
     float ms = 0;
     if (t.kind == kind && hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) total += ms;
+    if (total2 && t.kind == kind2 && hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess)
+      *total2 += ms;
     db->ev_pool.push_back(t.a);
     db->ev_pool.push_back(t.b);
   }
@@ -3045,14 +3052,17 @@ static int impl_autotune(swdb::Searcher* db, const int32_t* query_lens, int32_t 
     }
   }
   for (int b = 0; b < SW_TUNE_BUCKETS; ++b) local.query_len[b] = rep_len[b];
+  // buckets whose searches end earlier with the long pairs' launch fitted to each
+  // query than with the best of the candidates (in the cache: negative waves)
+  bool keep_fitted[SW_TUNE_BUCKETS] = {};
   auto apply = [&]() {
     for (int b = 0; b < SW_TUNE_BUCKETS; ++b) {
       db->tune_rows[b] = local.rows[b];
       db->tune_waves[b] = local.waves[b];
       db->tune_brows[b] = local.batch_rows[b];
       db->tune_bwaves[b] = local.batch_waves[b];
-      db->tune_irows[b] = local.intra_rows[b];
-      db->tune_iwaves[b] = local.intra_waves[b];
+      db->tune_irows[b] = keep_fitted[b] ? 0 : local.intra_rows[b];
+      db->tune_iwaves[b] = keep_fitted[b] ? 0 : local.intra_waves[b];
     }
   };
   const std::string key = cache_path ? tune_key(db, rep_len) : std::string();
@@ -3078,7 +3088,8 @@ static int impl_autotune(swdb::Searcher* db, const int32_t* query_lens, int32_t 
           local.batch_rows[b] = v[6 * b + 2];
           local.batch_waves[b] = v[6 * b + 3];
           local.intra_rows[b] = v[6 * b + 4];
-          local.intra_waves[b] = v[6 * b + 5];
+          local.intra_waves[b] = std::abs(v[6 * b + 5]);
+          keep_fitted[b] = v[6 * b + 5] < 0;
         }
         found = true;
       }
@@ -3169,21 +3180,31 @@ static int impl_autotune(swdb::Searcher* db, const int32_t* query_lens, int32_t 
       if (bgc > bbest) { bbest = bgc; bpick = c; }
     }
     // the long-pair kernel of single searches, beside the chosen inter-task
-    // schedule
     db->opt_rows = kTuneR[pick];
     db->opt_waves = kTuneW[pick];
-    for (int c = 0; has_long && c < SW_TUNE_INTRA_CANDIDATES && rc == SW_OK; ++c) {
-      db->opt_intra_rows = kTuneIR[c];
-      db->opt_intra_waves = kTuneIW[c];
-      for (int rpt = 0; rpt < 2 && rc == SW_OK; ++rpt) {
-        if (rpt == 1) (void)drain_timed(db, kTimeIntra);
+    // schedule: whole searches are compared, as the kernel shares the device with
+    // the bins (its own time is reported), and with the launch that is fitted to
+    // each query (candidate -1)
+    double fitted = 0;
+    for (int c = -1; has_long && c < SW_TUNE_INTRA_CANDIDATES && rc == SW_OK; ++c) {
+      db->opt_intra_rows = c < 0 ? 0 : kTuneIR[c];
+      db->opt_intra_waves = c < 0 ? 0 : kTuneIW[c];
+      float total = 0, ms = 0;
+      for (int rpt = 0; rpt < 4 && rc == SW_OK; ++rpt) {
         rc = enqueue_search(db, dq.p, m, mat, 10, 2, dout.p, s);
+        float t = 0;
+        ms = drain_timed(db, kTimeIntra, kTimeTotal, &t);
+        if (rpt > 0) total += t;
       }
       if (rc != SW_OK) break;
-      const float ms = drain_timed(db, kTimeIntra);
+      if (c < 0) {
+        fitted = total;
+        continue;
+      }
       local.intra_ms[b][c] = ms;
-      if (ms > 0 && ms < ibest) { ibest = ms; ipick = c; }
+      if (ms > 0 && total < ibest) { ibest = total; ipick = c; }
     }
+    keep_fitted[b] = ipick >= 0 && !tuned_beats_fitted(ibest, fitted);
     local.rows[b] = kTuneR[pick];
     local.waves[b] = kTuneW[pick];
     local.batch_rows[b] = kTuneR[bpick];
@@ -3211,7 +3232,8 @@ static int impl_autotune(swdb::Searcher* db, const int32_t* query_lens, int32_t 
     fprintf(f, "%s\t", key.c_str());
     for (int b = 0; b < SW_TUNE_BUCKETS; ++b)
       fprintf(f, "%d %d %d %d %d %d ", local.rows[b], local.waves[b], local.batch_rows[b],
-              local.batch_waves[b], local.intra_rows[b], local.intra_waves[b]);
+              local.batch_waves[b], local.intra_rows[b],
+              keep_fitted[b] ? -local.intra_waves[b] : local.intra_waves[b]);
     fprintf(f, "\n");
     if (fclose(f) != 0)
       return fail(SW_EINVAL, std::string("cannot write the tuning cache ") + cache_path);

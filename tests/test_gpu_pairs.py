@@ -213,3 +213,41 @@ def test_chosen_launch_is_no_slower_than_forced_ones(sw, what):
             times[rows, waves] = median()
     say(what, times)
     assert times[0, 0] <= 1.2 * min(times.values()), times
+
+
+# tuning must not take searches off a launch that suits them better: the long pairs'
+# candidates have 8 waves at most, and the shortest kernel is not the shortest search
+def test_autotune_makes_no_search_slower(sw, tmp_path):
+    import torch
+    rng = np.random.default_rng(11)
+    lens = np.concatenate([swinputs.lognormal_lengths(6000, 350.0, 0.75, 20, 9999, rng),
+                           rng.integers(10000, 35001, 120)]).astype(np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    cache = str(tmp_path / "tune.txt")
+    out = torch.empty(len(lens), dtype=torch.int32, device="cuda")
+
+    def medians(db):
+        got = []
+        for m in (200, 500, 2000):
+            q = torch.from_numpy(swinputs.random_residues(m, np.random.default_rng(m))).cuda()
+            ms = []
+            for _ in range(12):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                db.search_async(q, B62, 10, 2, out)
+                b.record()
+                b.synchronize()
+                ms.append(a.elapsed_time(b))
+            got.append(float(np.median(ms[2:])))
+        return np.array(got)
+
+    with sw.Database(res, offs) as db:
+        fitted = medians(db)
+        rep = db.autotune([200, 500, 2000], cache=cache)
+        tuned = medians(db)
+    with sw.Database(res, offs) as db:              # the cache says the same
+        assert db.autotune([200, 500, 2000], cache=cache)["from_cache"]
+        cached = medians(db)
+    say("fitted", fitted, "tuned", tuned, "cached", cached,
+        [b["intra_chosen"] for b in rep["buckets"]])
+    assert (tuned <= 1.1 * fitted).all() and (cached <= 1.1 * fitted).all()
