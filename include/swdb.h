@@ -228,12 +228,13 @@ int sw_search_topk_async(sw_db* db, const uint8_t* d_query, int32_t query_len,
  * search reports them for its best hits), ending at the end sw_search_topk
  * reports.  The exact 32-bit intra-task kernel recomputes each sequence's
  * matrix, keeping one traceback code per cell in device memory (query
- * length rounded up to 512 bytes per sequence residue; sequences go in
- * groups of up to 1 GiB of codes), and a second kernel walks back from the
- * end, one wave per sequence.  Of several optimal
- * alignments it returns the one that, walking back, prefers a matched pair,
- * then a query residue against a gap, then a database residue against a
- * gap, and ends a gap at the first place it can.
+ * length rounded up to 512 bytes per sequence residue, and as many for each
+ * of 63 columns before and after a sequence, which neighbours share;
+ * sequences go in groups of up to 1 GiB of codes, one alone may take more),
+ * and a second kernel walks back from the end, one wave per sequence.  Of
+ * several optimal alignments it returns the one that, walking back, prefers a
+ * matched pair, then a query residue against a gap, then a database residue
+ * against a gap, and ends a gap at the first place it can.
  *   query, matrix : host, as sw_search.
  *   seqs      : host, n_items database sequence indices (any order,
  *               repeats allowed), 0 <= n_items <= SW_MAX_TOPK.
@@ -247,8 +248,8 @@ int sw_search_topk_async(sw_db* db, const uint8_t* d_query, int32_t query_len,
  *   ops_used  : host, or NULL: the runs all alignments take (also when
  *               ops_cap is too small: then SW_ERANGE and nothing written).
  * A score of 0 has no alignment: begins and ends -1, no runs.  A sequence
- * whose codes would exceed 4 GiB returns SW_ERANGE; codes that do not form
- * a path (a fault) return SW_EDEVICE.  Synchronous. */
+ * whose own columns' codes would exceed 4 GiB returns SW_ERANGE; codes that do
+ * not form a path (a fault) return SW_EDEVICE.  Synchronous. */
 typedef struct sw_alignment {
   int32_t seq;          /* database sequence index */
   int32_t score;        /* the alignment's score (the sequence's search score) */

@@ -116,7 +116,8 @@ struct IntraArgs {
 };
 
 // Columns of traceback codes before and after a sequence's: what the lanes of a
-// wave store before their first column and after the last one.
+// wave store before their first column and after the last one.  Nothing reads
+// them, so neighbours in memory may share them.
 constexpr int kTracePad = 63;
 
 // Traceback walk (k_trace.hip), one item per workgroup.

@@ -2177,7 +2177,8 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
     const int64_t box = (offs[(size_t)seqs[t] + 1] - offs[(size_t)seqs[t]]) * ld;
     if (box > kTraceMaxBox)
       return fail(SW_ERANGE, "traceback codes of sequence " + std::to_string(seqs[t]) + " (" +
-                                 std::to_string(box) + " bytes) exceed 4 GiB");
+                                 std::to_string(box) + " bytes beside " + std::to_string(2 * kTracePad) +
+                                 " columns of padding) exceed 4 GiB");
   }
   std::unique_lock<std::mutex> lk(db->mtx, std::try_to_lock);
   if (!lk.owns_lock()) return fail(SW_EBUSY, "another call is running on this handle");
@@ -2187,9 +2188,13 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
   std::vector<int32_t> qb((size_t)n_items, -1), dbb((size_t)n_items, -1);
   hipError_t e;
   hipStream_t s = db->own_stream;
-  if (query_len == 0 || n_items == 0) {
-    for (int32_t t = 0; t < n_items; ++t) ends[(size_t)t] = make_int4(seqs[t], 0, -1, -1);
-  } else {
+  // an empty query or sequence has no alignment and takes no codes
+  std::vector<int32_t> todo;
+  for (int32_t t = 0; t < n_items; ++t) {
+    ends[(size_t)t] = make_int4(seqs[t], 0, -1, -1);
+    if (query_len > 0 && offs[(size_t)seqs[t] + 1] > offs[(size_t)seqs[t]]) todo.push_back(t);
+  }
+  if (!todo.empty()) {
     int RR = 8, W2 = 1;
     pick_intra(db, query_len, 8, &RR, &W2);
     if ((e = db->prof2.reserve((size_t)kIntraCodes * ld)) != hipSuccess)
@@ -2197,16 +2202,19 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
     Matrix mat;
     memcpy(mat.v, matrix, sizeof(mat.v));
     int32_t t0 = 0;
-    while (t0 < n_items) {
-      // a group: as many sequences as fit kTraceGroupBytes (at least one)
+    const int32_t n_todo = (int32_t)todo.size();
+    auto seq_of = [&](int32_t x) { return seqs[todo[(size_t)x]]; };
+    while (t0 < n_todo) {
+      // a group: as many sequences as fit kTraceGroupBytes (at least one), the
+      // columns between two neighbours serving both
       int32_t t1 = t0;
-      int64_t bytes = 0, rev_words = 0;
+      int64_t bytes = kTracePad * ld, rev_words = 0;
       std::vector<int64_t> off;
-      while (t1 < n_items) {
-        const int64_t len = offs[(size_t)seqs[t1] + 1] - offs[(size_t)seqs[t1]];
-        const int64_t box = (len + 2 * kTracePad) * ld;
+      while (t1 < n_todo) {
+        const int64_t len = offs[(size_t)seq_of(t1) + 1] - offs[(size_t)seq_of(t1)];
+        const int64_t box = (len + kTracePad) * ld;
         if (t1 > t0 && bytes + box > kTraceGroupBytes) break;
-        off.push_back(bytes);
+        off.push_back(bytes - kTracePad * ld);
         bytes += box;
         rev_words += len + query_len + 2;
         ++t1;
@@ -2230,7 +2238,7 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
       int2* const u_items = reinterpret_cast<int2*>(up.data() + items_at);
       int64_t rev_at = 0;
       for (int32_t x = 0; x < k; ++x) {
-        const int32_t sid = seqs[t0 + x];
+        const int32_t sid = seq_of(t0 + x);
         u_off[x] = off[(size_t)x];
         u_off[k + x] = rev_at;
         u_items[x] = make_int2(sid, 0);
@@ -2309,11 +2317,12 @@ static int impl_traceback(swdb::Searcher* db, const uint8_t* query, int32_t quer
       const uint32_t* const h_runs = reinterpret_cast<const uint32_t*>(down.data() + runs_at);
       for (int32_t x = 0; x < k; ++x) {
         const int4 hd = h_ends[k + x];
-        ends[(size_t)(t0 + x)] = h_ends[x];
-        qb[(size_t)(t0 + x)] = hd.y;
-        dbb[(size_t)(t0 + x)] = hd.z;
+        const size_t t = (size_t)todo[(size_t)(t0 + x)];
+        ends[t] = h_ends[x];
+        qb[t] = hd.y;
+        dbb[t] = hd.z;
         try {
-          runs[(size_t)(t0 + x)].assign(h_runs + hd.w, h_runs + hd.w + hd.x);
+          runs[t].assign(h_runs + hd.w, h_runs + hd.w + hd.x);
         } catch (...) {
           return fail(SW_ENOMEM, "host allocation failed");
         }

@@ -59,3 +59,43 @@ def test_many_runs(sw):
         got = db.traceback(q, B62, 0, 0, list(range(len(lens))))
     assert sum(len([1 for x, y in zip(a["ops"], a["ops"][1:]) if x != y]) for a in got) > 8192
     _same(got, q, res, offs, 0, 0)
+
+
+# what a sequence's codes take beside its own columns: nothing for an empty one, and
+# the columns between neighbours once
+def test_code_memory_and_empty_sequences(sw):
+    import torch
+    rng = np.random.default_rng(8)
+    lens = np.array([0, 12, 0, 40, 1, 0], np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    m = 1_000_000                                    # a column: a megabyte
+    q = swinputs.random_residues(m, rng)
+    with sw.Database(res, offs) as db:
+        db.search(q[:100], B62, 10, 2)
+        for seqs, columns in (([0, 2, 5, 0], 0), ([1, 0, 3, 4], 12 + 40 + 1 + 4 * 63)):
+            before = torch.cuda.mem_get_info()[0]
+            got = db.traceback(q, B62, 10, 2, seqs)
+            used = before - torch.cuda.mem_get_info()[0]
+            print("traceback of %s: %d MB" % (seqs, used / 1e6), file=sys.stderr, flush=True)
+            assert used <= (columns + 80) * 1_000_448      # profile, runs, rounding
+            for al, sid in zip(got, seqs):
+                assert al["seq"] == sid
+                if lens[sid] == 0:
+                    assert (al["score"], al["query_begin"], al["query_end"], al["db_begin"],
+                            al["db_end"], al["ops"]) == (0, -1, -1, -1, -1, "")
+                else:
+                    b = res[offs[sid]:offs[sid + 1]]
+                    at = al["query_begin"] - 100 if al["query_begin"] > 100 else 0
+                    part = q[at:al["query_end"] + 1]
+                    want = oracle.sw_gotoh_traceback(part, b, B62, 10, 2)
+                    assert al["score"] == want[0] and al["ops"] == want[5]
+    # groups of neighbours, empty ones among them, equal each alone
+    lens = np.array([70, 0, 200, 64, 0, 63, 1, 300], np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    q = swinputs.random_residues(130, rng)
+    with sw.Database(res, offs) as db:
+        some = [t for t in range(8) if lens[t]]
+        _same(db.traceback(q, B62, 4, 1, some), q, res, offs, 4, 1)
+        together = db.traceback(q, B62, 4, 1, list(range(8)) * 2)
+        for t, al in enumerate(together):
+            assert al == db.traceback(q, B62, 4, 1, [t % 8])[0]
