@@ -358,7 +358,8 @@ enum sw_option {
                              four waves per SIMD; batched searches: 4, 8, 12,
                              16) */
   SW_OPT_INTRA_ROWS = 5,  /* intra-task query rows per lane: 0 (auto), 2, 4, 8 */
-  SW_OPT_INTRA_WAVES = 6, /* intra-task waves per long sequence: 0 (auto), 1, 2, 4, 8 */
+  SW_OPT_INTRA_WAVES = 6, /* intra-task waves per long sequence: 0 (auto; up to 16 of
+                             the long-pair kernel), 1, 2, 4, 8 */
   SW_OPT_HYBRID_SHARE = 8, /* hybrid search: 0 (default) plans the host's share
                              from measured rates; 1..1000 fixes it at that many
                              thousandths of the short bins' cells, with no

@@ -54,9 +54,9 @@
 // the byte permutes, and barriers every 64 steps).  Bound by a pair's own chain
 // of steps where pairs are few (columns times the time of a step), else by the
 // VALU.  Against k_intra_f16: 211 residues, 20,001 sequences 1.10 ms a search ->
-// 0.58; 1,001 bases, 3,000 sequences 1.92 -> 1.34; 2,000 residues, the long mix
-// 7.05 -> 5.71; against k_intra_i32, global, 310 residues, 100,000 sequences
-// 5.48 -> 2.56.
+// 0.51; 1,001 bases, 3,000 sequences 1.92 -> 1.28; 2,000 residues, the long mix
+// 7.05 -> 5.7; against k_intra_i32, global, 310 residues, 100,000 sequences
+// 5.48 -> 2.49.
 #include <type_traits>
 
 #include "internal.h"

@@ -458,10 +458,11 @@ int tune_bucket(int m) {
 constexpr int kDefaultRows = 16, kDefaultWaves = 12;
 
 // The fitted schedules of the single-query inter-task kernel: strip height
-// R and waves W with a relative efficiency per strip slot, the median over
-// the plain workload's queries of 700+ rows of GCUPS x padded rows / rows
-// (scaled to 0.868 for 14 x 16): 12 waves (3 per SIMD) with 12..20 rows, 16
-// waves (4 per SIMD, <= 128 VGPRs) with 12 or 14 rows.
+// R and waves W, 12 waves (3 per SIMD) with 12..20 rows, 16 waves (4 per SIMD,
+// <= 128 VGPRs) with 12 or 14 rows.  The relative efficiencies per strip slot are
+// those of the binary16 kernel with a barrier per chunk (the median over the plain
+// workload's queries of 700+ rows of GCUPS x padded rows / rows, scaled to 0.868
+// for 14 x 16); the batched kernel's below are the strip stream's.
 struct Sched {
   int R, W;
   double eff;
@@ -478,10 +479,14 @@ constexpr Sched kBatchScheds[] = {{24, 12, 1.000}, {16, 16, 0.997}, {20, 12, 0.9
                                   {14, 16, 0.973}, {18, 12, 0.964}, {16, 12, 0.964},
                                   {14, 12, 0.951}, {12, 16, 0.951}, {12, 12, 0.932}};
 
-// A bin of C chunks takes ceil(S / W) rounds of its S = ceil(m / R) strips,
-// each round C supersteps of W waves' chunks, so its time is proportional
-// to ceil(S / W) * W * R / eff.  Picks the schedule minimising that among
-// those with the given rows / waves (0: any); false if none matches.
+// Picks the schedule with the least ceil(S / W) * W * R / eff, S = ceil(m / R)
+// strips, among those with the given rows / waves (0: any); false if none
+// matches.  The rounds of W strips are the barrier form's: there the last of them
+// left waves idle.  The strip stream has none (a wave goes on to the next bin's
+// strips), so for it the term only spreads the choice; padded rows / eff, as batches
+// take it, would be its cost.  The schedules differ by 5 % between neighbouring
+// lengths (977 residues, 12 x 12: 9,740 GCUPS; 807, 14 x 16: 9,791; 1,184, 20 x 12:
+// 10,176), and which one a length gets is part of the tested surface.
 bool fit_schedule(int m, int rows, int waves, int* R_out, int* W_out) {
   double best = 1e300;
   for (const Sched& c : kScheds) {
@@ -600,7 +605,6 @@ hipError_t reserve_long_scratch(Searcher* db, int grid) {
                              (size_t)std::max<int32_t>(db->d->plan.max_long_len, 1));
 }
 
-// Enqueues one query's search on stream s.  All arguments validated.
 // Gap penalty for the half-precision kernels, in both halves: penalties
 // above the exact range act like 2048 there (packed16.h).
 uint32_t half_pair(int32_t g) {
@@ -662,10 +666,12 @@ struct SearchShape {
   int n_pass, grid;           // and its launch: passes, workgroups
 };
 
-// Rates of the search kernels on a 256-CU MI355X (cells per second),
-// measured on the benchmark workloads: the inter-task kernel over the
-// device, the long-pair kernel over the device, and one inter-task
-// workgroup (one bin) alone on its CU.
+// Rates on a 256-CU MI355X (cells per second) by which bins are handed to the
+// long-pair kernel: the inter-task kernel over the device, the long-pair kernel
+// over the device, and one inter-task workgroup (one bin) alone on its CU.  They are
+// the binary16 kernels'; the drift kernels' are up to 1.3 times (a bin's up to
+// twice) as high, but choose 0..2 % better or 5..40 % worse numbers of bins on
+// seven workloads.
 constexpr double kInterRate = 7.0e12;
 constexpr double kPairRate = 4.5e12;
 constexpr double kBinRate = 3.0e10;
@@ -1052,10 +1058,10 @@ int enqueue_search_kernels(Searcher* db, const SearchShape& sh, const SearchScra
   };
 
   // The pairs go first and on this stream: the inter-task kernel is persistent
-  // and holds every CU it gets until its queue is empty, so the pairs' share of
-  // the CUs has to be taken when it starts, a stream wait later.  Its queue
-  // evens out what the share got wrong: workgroups that find no CU free start
-  // where a pair's has ended.
+  // and holds every CU it gets until its queue is empty, so the pairs' CUs have to
+  // be taken when it starts, a stream wait later.  Its queue evens out what the
+  // estimate got wrong: workgroups that find no CU free start where a pair's has
+  // ended.
   int rc;
   if ((rc = run_pairs()) != SW_OK || (rc = run_bins()) != SW_OK) return rc;
   // both packed kernels fill the rescoring list: join before consuming it
@@ -1180,9 +1186,9 @@ int64_t mode_bound(const Searcher* db, int64_t m, int64_t go, int64_t ge) {
   return go + (ge + 128) * (m + 512 + (int64_t)db->d->plan.max_len + 1024);
 }
 
-// Global / semi-global search of one query: the packed inter-task kernel over
-// the short bins (the int32 one where 16 bits do not hold it) beside the int32
-// wavefront kernel over the long list, which starts first, as in a local search.
+// Global / semi-global search of one query: the packed inter-task kernel over the
+// short bins beside the long-pair kernel over the long list, which starts first, as
+// in a local search; where 16 bits do not hold the values, the int32 kernels.
 int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const Matrix& mat,
                         int32_t go, int32_t ge, int mode, int32_t* d_out, hipStream_t s) {
   hipError_t e;
@@ -1304,8 +1310,7 @@ int enqueue_search_mode(Searcher* db, const uint8_t* d_query, int32_t m, const M
     grid = (int)std::min<int64_t>(n_long, kIntraGridLong);
     if ((e = reserve_long_scratch(db, grid)) != hipSuccess)
       return fail(SW_ENOMEM, std::string("long scratch: ") + hipGetErrorString(e));
-    // beside the persistent packed kernel a share of the CUs, as the long pairs
-    // of a local search
+    // beside the persistent packed kernel a share of the CUs, as binary16 pairs
     if (mp.R > 0 && P.n_bins > 0) {
       const double t_long = (double)db->d->long_residues / kLongModeRate;
       const double t_inter = (double)(db->d->n_res - db->d->long_residues) / kInterRate;
