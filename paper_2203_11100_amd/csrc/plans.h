@@ -200,10 +200,10 @@ inline double step_cycles(const StepCost& c, double waves) {   // per SIMD
 // whose workgroups share a CU with no other, at most 7/8 of the CUs, and fewer where
 // the longest bin that waits for one of them would end last: a bin that waits for
 // every pair's workgroup starts when the search is all but over (6,000 residues
-// against 50,000 sequences of the long mix: 38 ms).  Against fixed counts of CUs,
-// rows and waves swept over 31 searches of seven databases, 47 .. 10,000 residues:
-// 2 % above the best of them on average, 13 % at most (without the spreading and the
-// fullest SIMD's share in the chain: 17 %, 114 %).
+// against 50,000 sequences of the long mix: 48 ms with every CU taken, 37 so).
+// Against fixed counts of CUs, rows and waves swept over 37 searches of eight
+// databases, 47 .. 10,000 residues: 2 % above the best of them on average, 13 % at
+// most (without the spreading and the fullest SIMD's share in the chain: 17 %, 114 %).
 inline PairLaunch pair_launch(const PairLoad& p) {
   PairLaunch best;
   double least = 1e300;
@@ -249,8 +249,9 @@ inline PairLaunch pair_launch(const PairLoad& p) {
           if (now < p.n_bins)
             all = std::max(all, 0.7 * pairs + p.bin_col * 2.4e9 * (double)p.bins[4 * now + 2]);
         }
-        // (where two agree 16 waves beside bins, 8 alone)
-        if (p.beside > 0 ? all < least : all <= least) {
+        // (where two agree the more CUs; 16 waves beside bins, 8 alone)
+        const bool same = best.R == c.R && best.W == W;
+        if (p.beside > 0 ? all < (same ? 0.995 : 1.0) * least : all <= least) {
           least = all;
           best.R = c.R;
           best.W = W;

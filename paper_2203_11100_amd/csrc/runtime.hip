@@ -772,7 +772,8 @@ SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t g
     sh.RR = pl.R;
     sh.W2 = pl.W;
     sh.grid = pl.grid;
-  } else if (!tuned && !db->opt_intra_rows && !db->opt_intra_waves) {
+  } else if (offload && !tuned && !db->opt_intra_rows && !db->opt_intra_waves) {
+    // (the allocation-free search has rows for few workgroups)
     half_rows(m, load.items, load.cols, load.longest, &sh.RR, &sh.W2);
   }
   sh.n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
