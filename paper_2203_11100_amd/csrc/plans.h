@@ -159,6 +159,48 @@ inline int pair_ring(int n_pass, int W) {
   return n_pass > 1 ? std::min(kRing, (W + n_pass - 1) / n_pass + 1) : kRing;
 }
 
+// A schedule of an inter-task kernel: strips of R rows, W waves, relative efficiency.
+struct Sched {
+  int R, W;
+  double eff;
+};
+
+// The batched kernel's fitted schedules, with relative efficiencies: padded
+// rows / kernel time of 24 queries of 50 .. 5,000 residues against 100,000
+// plain sequences, every form forced (186.8 ms at 24 x 12, 200.0 at 12 x 12).
+// Taller strips pay less for boundary rows and chunk starts, four waves a SIMD
+// (16 waves, <= 128 VGPRs) hide more than three.
+constexpr Sched kBatchScheds[] = {{24, 12, 1.000}, {16, 16, 0.997}, {20, 12, 0.987},
+                                  {14, 16, 0.973}, {18, 12, 0.964}, {16, 12, 0.964},
+                                  {14, 12, 0.951}, {12, 16, 0.951}, {12, 12, 0.932}};
+
+// The batched kernel's rows and waves (0: any; false if none matches) for queries of
+// these lengths, longest first, over half bins of `cols` columns together: the least
+// of the work on all CUs, the pairs' padded rows, and the longest half bin with the
+// longest pair on its one workgroup, whose strips lie on the four SIMDs round robin:
+// the fullest one's rows set its time.  Two queries of 144 residues against 100,000
+// plain sequences (longest half bin 8,188 columns), kernel ms: 24 x 12 (6 strips) 4.06,
+// 16 x 12 (9) 4.03, 14 x 12 (11) 3.65, 18 x 12 (8) 3.26, 12 x 12 (12) 2.94.
+inline bool batch_schedule(const int64_t* lens, int64_t n, double cols, double longest, int cus,
+                           int rows, int waves, int* R_out, int* W_out) {
+  double best = 1e300;
+  for (const Sched& c : kBatchScheds) {
+    if ((rows && c.R != rows) || (waves && c.W != waves)) continue;
+    double padded = 0;
+    for (int64_t i = 0; i < n; i += 2) padded += (double)((lens[i] + c.R - 1) / c.R * c.R);
+    const int64_t strips = n > 0 ? (lens[0] + c.R - 1) / c.R : 0;
+    const double work = padded / 4 * cols / std::max(cus, 1);
+    const double chain = (double)((strips + 3) / 4 * c.R) * longest;
+    const double cost = (std::max(work, chain) + 0.1 * std::min(work, chain)) / c.eff;
+    if (cost < best) {
+      best = cost;
+      *R_out = c.R;
+      *W_out = c.W;
+    }
+  }
+  return best < 1e300;
+}
+
 // What the long-pair kernel is to score, and beside what.
 struct PairLoad {
   int m = 0;                  // query rows (batches: the longest query's)

@@ -462,22 +462,9 @@ constexpr int kDefaultRows = 16, kDefaultWaves = 12;
 // <= 128 VGPRs) with 12 or 14 rows.  The relative efficiencies per strip slot are
 // those of the binary16 kernel with a barrier per chunk (the median over the plain
 // workload's queries of 700+ rows of GCUPS x padded rows / rows, scaled to 0.868
-// for 14 x 16); the batched kernel's below are the strip stream's.
-struct Sched {
-  int R, W;
-  double eff;
-};
+// for 14 x 16); the batched kernel's (plans.h) are the strip stream's.
 constexpr Sched kScheds[] = {{20, 12, 0.835}, {18, 12, 0.821}, {16, 12, 0.838}, {14, 12, 0.810},
                              {12, 12, 0.814}, {14, 16, 0.868}, {12, 16, 0.863}};
-
-// The batched kernel's fitted schedules, with relative efficiencies: padded
-// rows / kernel time of 24 queries of 50 .. 5,000 residues against 100,000
-// plain sequences, every form forced (186.8 ms at 24 x 12, 200.0 at 12 x 12).
-// Taller strips pay less for boundary rows and chunk starts, four waves a SIMD
-// (16 waves, <= 128 VGPRs) hide more than three.
-constexpr Sched kBatchScheds[] = {{24, 12, 1.000}, {16, 16, 0.997}, {20, 12, 0.987},
-                                  {14, 16, 0.973}, {18, 12, 0.964}, {16, 12, 0.964},
-                                  {14, 12, 0.951}, {12, 16, 0.951}, {12, 12, 0.932}};
 
 // Picks the schedule with the least ceil(S / W) * W * R / eff, S = ceil(m / R)
 // strips, among those with the given rows / waves (0: any); false if none
@@ -1416,19 +1403,12 @@ int prepare_batch(Searcher* db, const uint8_t* d_queries, const int64_t* qoffs, 
       if (db->tune_brows[b]) { R = db->tune_brows[b]; W = db->tune_bwaves[b]; tuned = true; }
     }
     if (!tuned && !lens.empty()) {
-      // a pair of neighbouring lengths costs its ceil(m / R) strips (m the
-      // longer query) for every half bin: the waves take strips without a seam,
-      // so no round of W is left short
-      double best = 1e300;
-      for (const Sched& c : kBatchScheds) {
-        if ((db->opt_rows && c.R != db->opt_rows) || (db->opt_waves && c.W != db->opt_waves))
-          continue;
-        double cost = 0;
-        for (size_t i = 0; i < lens.size(); i += 2) {
-          cost += (double)((lens[i] + c.R - 1) / c.R * c.R) / c.eff;
-        }
-        if (cost < best) { best = cost; R = c.R; W = c.W; }
-      }
+      const Plan& P = db->d->plan;
+      double cols = 0;       // of all half bins
+      for (int64_t x = 0; x < P.n_bins + P.n_long_bins; ++x)
+        cols += 2.0 * (double)P.bins[(size_t)x * 4 + 2];
+      batch_schedule(lens.data(), (int64_t)lens.size(), cols, P.max_all_bin_len, db->d->n_cus,
+                     db->opt_rows, db->opt_waves, &R, &W);
     }
   }
   if (db->opt_rows == 12 || db->opt_rows == 14 || db->opt_rows == 16 || db->opt_rows == 18 ||

@@ -68,6 +68,9 @@ void p_launch(int m, const double* d, const int64_t* bins, int64_t n_bins, int c
   out[1] = l.W;
   out[2] = l.grid;
 }
+int p_batch(const int64_t* lens, int64_t n, const double* d, int cus, int rows, int waves, int32_t* rw) {
+  return batch_schedule(lens, n, d[0], d[1], cus, rows, waves, rw, rw + 1);
+}
 void p_half(int m, const double* d, int32_t* rw) { half_rows(m, d[0], d[1], d[2], rw, rw + 1); }
 int p_lds(int R, int W, int n_pass, int own) {
   const size_t mine = pairs_lds(R, W, n_pass, false), all = pairs_lds(R, W, n_pass, true);
@@ -156,3 +159,12 @@ def half_rows(m, items, cols, longest, rows, waves):
     rw, d = np.array([rows, waves], np.int32), np.array([items, cols, longest], np.float64)
     lib().p_half(m, d.ctypes.data_as(ctypes.c_void_p), rw.ctypes.data_as(ctypes.c_void_p))
     return tuple(rw.tolist())
+
+
+def batch(lens, cols, longest, cus=256, rows=0, waves=0):
+    rw, d = np.zeros(2, np.int32), np.array([cols, longest], np.float64)
+    v = np.array(sorted(lens, reverse=True), np.int64)
+    ok = lib().p_batch(v.ctypes.data_as(ctypes.c_void_p), _i64(len(v)),
+                       d.ctypes.data_as(ctypes.c_void_p), cus, rows, waves,
+                       rw.ctypes.data_as(ctypes.c_void_p))
+    return tuple(rw.tolist()) if ok else None

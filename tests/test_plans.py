@@ -196,3 +196,22 @@ def test_binary16_pairs_take_fewer_waves_for_many_short_pairs():
     # long pairs, few of them: the shortest chain, as it was
     assert plans.half_rows(2500, 1494, 8.8e6, 6808, 4, 4) == (4, 4)
     assert plans.half_rows(977, 1, 35000, 35000, 4, 4) == (4, 4)
+
+
+def test_batches_bound_by_their_longest_half_bin_fill_the_simds():
+    plain = dict(cols=5.6e5, longest=8188)       # 100,000 plain sequences
+    # kernel ms of the forms, each forced, for two queries of a length
+    for m, ms in ((144, {(12, 12): 2.94, (14, 12): 3.65, (16, 12): 4.03, (18, 12): 3.26,
+                         (20, 12): 3.53, (12, 16): 3.22, (14, 16): 3.73, (24, 12): 4.06}),
+                  (200, {(12, 12): 4.34, (14, 12): 4.22, (16, 12): 4.74, (18, 12): 4.17,
+                         (20, 12): 4.87, (12, 16): 4.55, (14, 16): 4.73}),
+                  (256, {(12, 12): 5.86, (14, 12): 5.15, (16, 12): 4.81, (18, 12): 5.33,
+                         (20, 12): 5.76, (12, 16): 5.39, (14, 16): 5.25, (16, 16): 4.87}),
+                  (400, {(12, 12): 8.87, (14, 12): 8.37, (16, 12): 8.42, (18, 12): 8.38,
+                         (20, 12): 7.03, (12, 16): 8.39, (14, 16): 8.75, (16, 16): 7.87})):
+        form = plans.batch([m, m], **plain)
+        assert form in ms and ms[form] <= 1.12 * min(ms.values()), (m, form)
+    # many queries: the work decides, and taller strips cost less a row
+    assert plans.batch([50 + 215 * i for i in range(24)], **plain) in ((24, 12), (16, 16), (20, 12))
+    assert plans.batch([300, 300], **plain, rows=14, waves=16) == (14, 16)
+    assert plans.batch([300, 300], **plain, rows=32, waves=8) is None
