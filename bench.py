@@ -41,8 +41,8 @@ METRIC = "GCUPS on 1 MI355X (plain vs batched/served) + p50/p99 query latency"
 # converted to bytes with the counters' readings for a 1 GiB device copy.
 # Valid only for the kernel and schedule-selection code it was taken on: bench
 # reports null when the digest of that code (comments removed) differs.
-TRAFFIC = {"bytes_per_launch": 2.4847e+10, "fetch_bytes": 92.28e9, "write_bytes": 404.66e9,
-           "launches": 20, "sources_sha256": "abc21c8dc0a0cceb5b2940deee35a398ea47c176ff507f88938ccabd877416bb"}
+TRAFFIC = {"bytes_per_launch": 2.4834e+10, "fetch_bytes": 92.06e9, "write_bytes": 404.62e9,
+           "launches": 20, "sources_sha256": "a73048fb37a138ddc4fadd7353a4c119e067e6b85b8e03efe699a8c330629e38"}
 TRAFFIC_SOURCES = ("k_inter.hip", "packed16.h", "internal.h", "runtime.hip")
 # of runtime.hip only the schedule selection (the fitted tables and the
 # choice of rows and waves per query) shapes the inter-task kernel's traffic
