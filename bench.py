@@ -52,17 +52,17 @@ SCHEDULE_SECTION = ("constexpr int kDefaultRows", "enum TimedKind")
 PEAK_HALF_TOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 # Algorithmic integer operations per cell of Gotoh's recurrence: 1 add
 # (H_diag + S), 3 max (E, F, 0), 1 max (running best), 1 subtract (H - open),
-# 2 subtract (E - extend, F - extend), 2 max (new E, new F).  The roofline
-# fraction `frac` counts these 10 per cell against the packed 16-bit peak.
+# 2 subtract (E - extend, F - extend), 2 max (new E, new F).  `achieved` counts
+# these 10 per cell.
 OPS_PER_CELL = 10
 # Packed 16-bit instructions the inter-task kernel issues per cell (half-ops per
 # cell), drift form: 1 three-input addition forming H_diag + S for both halves, 2
 # three-input max (H; E with its floor), 1 subtract, 1 max (F), 1/2 three-input max
 # for the running maximum (two cells per op); gaps are extended for nothing.  A
 # three-input max does two of the 10 algorithmic maxima in one issue slot and the
-# drift takes 2 subtractions out, so 10 ops take 5.5 slots and `frac` can exceed 1;
-# `frac_issue` is the fraction of the issue slots the kernel's own instruction
-# count needs.
+# drift takes 2 subtractions out, so 10 ops take 5.5 slots: the roofline's `peak` is
+# the rate of the 10 ops with every slot issued, and `frac` (and `frac_issue`, the
+# same number from the slots) the part of the slots that the cells need.
 ISSUE_PER_CELL = 5.5
 
 
@@ -208,8 +208,9 @@ def main():
     inter_s = st["ms_inter"] / 1e3
     achieved = st["inter_cells"] * OPS_PER_CELL / inter_s / 1e12 if inter_s > 0 else None
     issued = st["inter_cells"] * ISSUE_PER_CELL / inter_s / 1e12 if inter_s > 0 else None
-    roof = {"bound": "alu", "achieved": achieved, "peak": PEAK_HALF_TOPS, "unit": "Tops/s",
-            "frac": (achieved / PEAK_HALF_TOPS) if achieved else None,
+    peak = PEAK_HALF_TOPS * OPS_PER_CELL / ISSUE_PER_CELL
+    roof = {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "Tops/s",
+            "frac": (achieved / peak) if achieved else None,
             "frac_issue": (issued / PEAK_HALF_TOPS) if issued else None,
             "ops_per_cell": OPS_PER_CELL, "issue_per_cell": ISSUE_PER_CELL,
             "traffic": measured_traffic(),
@@ -354,15 +355,18 @@ def topk_leg(db, w, k=1000, queries=(0, 8, 19)):
 
 # Operations per cell of the global / semi-global recurrence (no floor, no
 # running maximum): 1 add, 2 max for H, 1 subtract for the open, 2 subtract for
-# the extends, 2 max for E and F; counted against the packed 16-bit peak
+# the extends, 2 max for E and F; the packed mode forms issue 5 slots for them
 MODE_OPS_PER_CELL = 8
+MODE_ISSUE_PER_CELL = 5
 
 
 def modes_leg(db, w, queries=(0, 8, 14)):
-    """Global and semi-global searches (int32 kernels) of three plain queries."""
+    """Global and semi-global searches of three plain queries (packed kernels, 32-bit
+    ones where the values pass 16 bits)."""
     import torch
     import paper_2203_11100_amd as sw
     out = {}
+    peak = PEAK_HALF_TOPS * MODE_OPS_PER_CELL / MODE_ISSUE_PER_CELL
     for mode in ("global", "semiglobal"):
         cells, ms_tot, inter_ms, inter_cells = 0, 0.0, 0.0, 0
         for qi in queries:
@@ -383,10 +387,11 @@ def modes_leg(db, w, queries=(0, 8, 14)):
         out[mode] = {"gcups": cells / ms_tot / 1e6, "ms": ms_tot,
                      "queries": [len(w.queries[i]) for i in queries],
                      "roofline": {"bound": "alu", "kernel": "k_inter (mode forms; k_mode_inter past 16 bits)",
-                                  "achieved": achieved, "peak": PEAK_HALF_TOPS,
+                                  "achieved": achieved, "peak": peak,
                                   "unit": "Tops/s",
-                                  "frac": achieved / PEAK_HALF_TOPS if achieved else None,
-                                  "ops_per_cell": MODE_OPS_PER_CELL}}
+                                  "frac": achieved / peak if achieved else None,
+                                  "ops_per_cell": MODE_OPS_PER_CELL,
+                                  "issue_per_cell": MODE_ISSUE_PER_CELL}}
     log("modes: %s" % out)
     return out
 
