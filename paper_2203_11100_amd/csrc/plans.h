@@ -313,23 +313,32 @@ inline bool tuned_beats_fitted(double tuned, double fitted) { return tuned < 0.9
 // The binary16 long-pair kernel (k_intra_f16): a workgroup's W waves take one
 // pair's passes in rounds, three supersteps a wave apart with their barriers.  The
 // expected time of a search's pairs, in units of an instruction: the longest one's
-// chain, or the work on 256 CUs, which idle waves in a last round, the start and
-// end of a pair, and few waves on a CU (the profiles in LDS) lengthen.
+// chain, or the work on 256 CUs, which idle waves in a last round (they issue
+// little and hold their place: 0.35 of a pass), the start and end of a pair, and few
+// waves on a CU (the profiles in LDS) lengthen.
 inline double half_estimate(int m, double items, double cols, double longest, int R, int W) {
   const int P = std::max(1, (m + 64 * R - 1) / (64 * R)), rounds = (P + W - 1) / W;
   const double step = 8.0 * R + 32;
   const double steps = std::max(1.0, cols / std::max(items, 1.0) / 64);   // supersteps a pair
   const int per_cu = std::max(1, std::min<int>(16 / W, (int)(kLdsBytes / (W * 3200 * R + 2000))));
   const double few = 1 + 0.05 * std::max(0, 12 - per_cu * W);
-  const double work = cols * rounds * W * step / 1024 * (steps + 3 * (W - 1)) / steps * few;
+  const double slots = 0.35 * rounds * W + 0.65 * P;
+  const double work = cols * slots * step / 1024 * (steps + 3 * (W - 1)) / steps * few;
   const double chain = longest * rounds * step * 1.6;
   return std::max(chain, work) + 0.1 * std::min(chain, work);
 }
 // The rows and waves that end first by that estimate where they do so clearly,
-// else R and W as they are (the shortest chain of one pair).  Many short pairs ask
+// else R and W as they are (the shortest chain of one pair), also where the bins
+// beside the pairs (`beside` residues) are most of the search.  Many short pairs ask
 // for few waves: gaps 200/130, 20,001 plain sequences, 977 residues 3.24 ms with 4 x
-// 4, 2.35 with 8 x 2; 25 searches of five databases never slower than before.
-inline void half_rows(int m, double items, double cols, double longest, int* R, int* W) {
+// 4, 2.35 with 8 x 2.  Of 38 searches of seven databases for which full rounds in the
+// place of `slots` named another form, 10 were 1 to 30 % slower with it (long mix of
+// 50,000, 690 residues: 7.89 ms with 4 x 4, 9.00 with 4 x 1); of these, one still
+// takes it and loses more than 3 % (two pairs of 2,000,000 residues, 450 residues:
+// 1.26 ms with 2 x 4, 1.42 with 4 x 2), and one gain above 6 % is given up.
+inline void half_rows(int m, double items, double cols, double longest, int* R, int* W,
+                      double beside = 0) {
+  if (beside > 4 * cols) return;
   double least = 0.8 * half_estimate(m, items, cols, longest, *R, *W);
   int r = *R, w = *W;
   for (int rows : {2, 4, 8})

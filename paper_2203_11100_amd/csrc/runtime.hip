@@ -761,7 +761,7 @@ SearchShape search_shape(const Searcher* db, int m, const Matrix& mat, int32_t g
     sh.grid = pl.grid;
   } else if (offload && !tuned && !db->opt_intra_rows && !db->opt_intra_waves) {
     // (the allocation-free search has rows for few workgroups)
-    half_rows(m, load.items, load.cols, load.longest, &sh.RR, &sh.W2);
+    half_rows(m, load.items, load.cols, load.longest, &sh.RR, &sh.W2, inter / std::max(m, 1));
   }
   sh.n_pass = (m + 64 * sh.RR - 1) / (64 * sh.RR);
   if (sh.pair.add < 0) {

@@ -71,7 +71,7 @@ void p_launch(int m, const double* d, const int64_t* bins, int64_t n_bins, int c
 int p_batch(const int64_t* lens, int64_t n, const double* d, int cus, int rows, int waves, int32_t* rw) {
   return batch_schedule(lens, n, d[0], d[1], cus, rows, waves, rw, rw + 1);
 }
-void p_half(int m, const double* d, int32_t* rw) { half_rows(m, d[0], d[1], d[2], rw, rw + 1); }
+void p_half(int m, const double* d, int32_t* rw) { half_rows(m, d[0], d[1], d[2], rw, rw + 1, d[3]); }
 int p_lds(int R, int W, int n_pass, int own) {
   const size_t mine = pairs_lds(R, W, n_pass, false), all = pairs_lds(R, W, n_pass, true);
   return (int)((own ? mine : std::min(mine, all)) + pairs_lds_static(W));
@@ -155,8 +155,8 @@ def lds(R, W, n_pass, own=False):
     return lib().p_lds(R, W, n_pass, int(own))
 
 
-def half_rows(m, items, cols, longest, rows, waves):
-    rw, d = np.array([rows, waves], np.int32), np.array([items, cols, longest], np.float64)
+def half_rows(m, items, cols, longest, rows, waves, beside=0.0):
+    rw, d = np.array([rows, waves], np.int32), np.array([items, cols, longest, beside], np.float64)
     lib().p_half(m, d.ctypes.data_as(ctypes.c_void_p), rw.ctypes.data_as(ctypes.c_void_p))
     return tuple(rw.tolist())
 

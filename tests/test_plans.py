@@ -198,6 +198,21 @@ def test_binary16_pairs_take_fewer_waves_for_many_short_pairs():
     assert plans.half_rows(977, 1, 35000, 35000, 4, 4) == (4, 4)
 
 
+def test_binary16_pairs_keep_their_rows_where_others_are_slower():
+    # {m, pairs, their columns, longest, bins' residues, form}: measured with the other
+    # form that an estimate of full rounds names 1.14, 1.18, 1.18 and 1.30 times as long
+    for m, items, cols, longest, beside, form in (
+            (690, 3394, 1.38e7, 4845, 1.57e7, (4, 4)), (2500, 3458, 1.88e7, 6808, 1.55e7, (4, 4)),
+            (1400, 1494, 7.33e6, 5615, 0, (8, 4)), (310, 1513, 2.39e6, 4433, 1.2e5, (2, 4))):
+        assert plans.half_rows(m, items, cols, longest, *form, beside) == form, m
+    # 100,000 plain sequences: the bins are the search (2.18 ms, 2.29 with 4 x 2)
+    assert plans.half_rows(310, 2237, 3.03e6, 4433, 2, 4, 2.95e7) == (2, 4)
+    # and 1.4 to 2.8 times shorter with other rows
+    assert plans.half_rows(450, 5164, 2.8e6, 4585, 2, 4, 1.53e6) == (4, 2)
+    assert plans.half_rows(450, 10000, 4e6, 400, 2, 4) == (8, 1)
+    assert plans.half_rows(2000, 5548, 2.91e6, 6266, 8, 4, 1.34e6) == (8, 2)
+
+
 def test_batches_bound_by_their_longest_half_bin_fill_the_simds():
     plain = dict(cols=5.6e5, longest=8188)       # 100,000 plain sequences
     # kernel ms of the forms, each forced, for two queries of a length
