@@ -3179,8 +3179,11 @@ static int impl_autotune(swdb::Searcher* db, const int32_t* query_lens, int32_t 
     db->opt_waves = kTuneW[pick];
     // schedule: whole searches are compared, as the kernel shares the device with
     // the bins (its own time is reported), and with the launch that is fitted to
-    // each query (candidate -1)
+    // each query (candidate -1); bins handed over as the searches will hand them (with
+    // none, 6,000 sequences of the long mix at 200 residues take 1.44 ms with every
+    // form, and one that then takes 0.64 instead of 0.55 ms may be chosen)
     double fitted = 0;
+    db->opt_offload = saved_off;
     for (int c = -1; has_long && c < SW_TUNE_INTRA_CANDIDATES && rc == SW_OK; ++c) {
       db->opt_intra_rows = c < 0 ? 0 : kTuneIR[c];
       db->opt_intra_waves = c < 0 ? 0 : kTuneIW[c];
@@ -3199,6 +3202,7 @@ static int impl_autotune(swdb::Searcher* db, const int32_t* query_lens, int32_t 
       local.intra_ms[b][c] = ms;
       if (ms > 0 && total < ibest) { ibest = total; ipick = c; }
     }
+    db->opt_offload = 0;
     keep_fitted[b] = ipick >= 0 && !tuned_beats_fitted(ibest, fitted);
     local.rows[b] = kTuneR[pick];
     local.waves[b] = kTuneW[pick];

@@ -251,3 +251,34 @@ def test_autotune_makes_no_search_slower(sw, tmp_path):
     say("fitted", fitted, "tuned", tuned, "cached", cached,
         [b["intra_chosen"] for b in rep["buckets"]])
     assert (tuned <= 1.1 * fitted).all() and (cached <= 1.1 * fitted).all()
+
+
+def test_autotune_times_the_searches_that_are_made(sw):
+    """A form of the long-pair kernel is timed in the search that later calls make, bins
+    handed over to it included: the reported times are those of the same forms fixed by
+    option (the same launches timed twice: a few per cent apart, a fifth allowed; with
+    no bins handed over the kernel has half the pairs, and a third less time)."""
+    import torch
+    rng = np.random.default_rng(11)
+    lens = np.concatenate([swinputs.lognormal_lengths(6000, 350.0, 0.75, 20, 9999, rng),
+                           rng.integers(10000, 35001, 120)]).astype(np.int64)
+    res, offs = swinputs.make_database(lens, rng)
+    out = torch.empty(len(lens), dtype=torch.int32, device="cuda")
+    q = torch.from_numpy(swinputs.random_residues(200, np.random.default_rng(2))).cuda()
+    with sw.Database(res, offs) as db:
+        said = db.autotune([200])["buckets"][0]["intra_ms"]
+        for name in ("4x2", "2x4", "4x4"):
+            r, w = map(int, name.split("x"))
+            db.set_option(sw.SW_OPT_INTRA_ROWS, r)
+            db.set_option(sw.SW_OPT_INTRA_WAVES, w)
+            db.set_option(sw.SW_OPT_TIMING, 1)
+            got = []
+            for _ in range(7):
+                db.stats()
+                db.search_async(q, B62, 10, 2, out)
+                torch.cuda.synchronize()
+                got.append(db.stats()["ms_intra"])
+            db.set_option(sw.SW_OPT_TIMING, 0)
+            got = float(np.median(got[2:]))
+            say(name, "tuned", said[name], "search", got)
+            assert abs(said[name] / got - 1) <= 0.2, name
